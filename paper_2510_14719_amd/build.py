@@ -24,7 +24,7 @@ LIB = os.path.join(HERE, "libattn_fwd.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["attn_fwd_kernel.hip", "attn_fwd_pipe_kernel.hip", "attn_fwd_fp8_kernel.hip", "mfma_probe.hip", "attn_api.cpp",
-           "gemm_nt_kernel.hip", "gemm_nt_fp8_kernel.hip", "gemm_api.cpp"]
+           "gemm_nt_kernel.hip", "gemm_nt_fp8_kernel.hip", "gemm_nt_tile_kernel.hip", "gemm_api.cpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -10,7 +10,8 @@
 // byte geometry as in the 16-bit kernel (16-row pieces of 1 KiB, row-major, the 16-byte columns of row r
 // rotated by (r/4)%4), and one K tile is one k-step of the 32x32x64 MFMA (64 cycles each).
 //
-// Two shapes of the workgroup are compiled, and the launcher picks by K:
+// Two shapes of the workgroup are compiled, and the launcher picks by K (where a 256 x 256 tile is the right
+// size at all: gemm_tile_shape in gemm_nt_tile_kernel.hip):
 //   short products: 8 waves (two per SIMD), a wave owns 128 (m) x 64 (n) = 8 accumulator blocks; ring of 4
 //     stages, one stage copied per tile, three tiles ahead;
 //   K >= 2048: 4 waves (one per SIMD), a wave owns 128 x 128 = 16 accumulator blocks in the AGPRs; ring of 5
@@ -385,7 +386,14 @@ int launch8_out(const GemmLaunchArgs& a)
 
 }  // namespace
 
-int gemm_fp8_launch(const GemmLaunchArgs& a) { return a.dtype == 0 ? launch8_out<0>(a) : launch8_out<1>(a); }
+int gemm_fp8_launch(const GemmLaunchArgs& a)
+{
+    if (GEMM8_CONFIG == 0 && a.config == 0) {
+        const int shape = gemm_tile_shape(a.M, a.N, a.K);
+        if (shape != 0) return gemm_tile_launch(a, 2, shape);
+    }
+    return a.dtype == 0 ? launch8_out<0>(a) : launch8_out<1>(a);
+}
 
 // Reported for the configuration a large K takes.
 int gemm_fp8_launch_tile_param(int which)

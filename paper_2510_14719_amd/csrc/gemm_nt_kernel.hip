@@ -21,7 +21,8 @@
 //   the request path from the L2 into the CU; so even tiles issue the pieces of stages j+4 and j+5
 //   alternately and odd tiles none: the two halves of a line are requested back to back and the L1 merges
 //   them into one request to the L2 (+9-13 % at K >= 2048).
-// The launcher takes the 4-wave paired kernel from K = 2048 on and the 8-wave paired kernel below.
+// The launcher takes the 4-wave paired kernel from K = 2048 on and the 8-wave paired kernel below, where a
+// 256 x 256 tile is the right size at all (gemm_tile_shape in gemm_nt_tile_kernel.hip).
 //
 // Measured on the device (M = N = 8192, K = 8192, fp16 N(0,1) operands, same box and session), 8 waves,
 // unpaired: 1.16 PFLOP/s; with the copies left out (wrong results, timing only) 1.40; with the
@@ -423,7 +424,14 @@ extern "C" int gemm_dbg_read(unsigned long long* host, int n)
 }
 #endif
 
-int gemm_launch(const GemmLaunchArgs& a) { return a.dtype == 0 ? launch_dtype<0>(a) : launch_dtype<1>(a); }
+int gemm_launch(const GemmLaunchArgs& a)
+{
+    if (GEMM_CONFIG == 0 && a.config == 0) {
+        const int shape = gemm_tile_shape(a.M, a.N, 2LL * a.K);
+        if (shape != 0) return gemm_tile_launch(a, a.dtype, shape);
+    }
+    return a.dtype == 0 ? launch_dtype<0>(a) : launch_dtype<1>(a);
+}
 
 // Reported for the configuration a large K takes.
 int gemm_launch_tile_param(int which)

@@ -1,0 +1,372 @@
+// NT matrix products with small tiles of C for gfx950 (MI355X): the same contract as gemm_nt_kernel.hip (16-bit operands)
+// and gemm_nt_fp8_kernel.hip (E4M3 operands, 16-bit result), for shapes whose 256 x 256 tiles leave compute units idle
+// or whose K is too short to hide the prologue and the epilogue of one big workgroup per compute unit.
+//
+// One kernel serves every element type, because everything but the MFMA is about bytes: a stage of the LDS ring
+// holds 128 bytes (one memory line) of every row of the A tile and of the B tile, so a copy instruction moves 8 whole
+// lines, and the fragments of a stage are 8 columns of 16 bytes per row: four k-steps of the 32x32x16 MFMA (16-bit) or
+// two of the 32x32x64 MFMA (E4M3).  A row is a multiple of 64 bytes (the contract's K step); in a last stage that is
+// only half filled the copies fetch the first half twice and the k-steps of the second half are left out.
+//
+// Waves: WM x WN of them split the tile, and WK of them split the k-steps of a stage (their accumulators are added
+// in the LDS before the epilogue): with one or two workgroups per CU this is what keeps two waves on every SIMD
+// when the tile is small.
+//
+// Ring of S stages.  The fragments of stage j are read into registers during tile j - 1, so at barrier j the slots of
+// all stages <= j are free (every wave waits for its reads before the barrier) and stage j + 1 is complete (every
+// wave waits for its own copies of it); the copies of stage j + S go out during tile j.
+//
+// LDS: row r of a stage at r * 128 bytes, its 16-byte column c at slot c ^ ((r / 2) % 8): the 16 rows that one pass of a
+// fragment read touches cover all 64 banks.
+//
+// Epilogue: the product is computed transposed (a lane holds one row m of C and runs of four n).  The 16-bit results go
+// through the LDS and leave as whole row segments of the tile (16 bytes per lane, or single elements side by side
+// when N or the pointer does not allow wider stores): stored straight from the registers, an instruction would
+// touch 32 rows with 16 bytes each.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include <type_traits>
+
+#include "gemm_launch.h"
+#include "gfx950_prims.h"
+#include "launch_once.h"
+#include "tile_schedule.h"
+
+namespace {
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int T_GROUP_M = 8;                    // tile rows per raster group: see tile_coords in gemm_nt_kernel.hip
+
+// Workgroup barrier that no LDS access of the compiler's moves across (the copies' arrival is not visible to it).
+__device__ __forceinline__ void ring_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// One k-step of one 32-row block: 16 bytes per lane (16-bit operands) or 32 (E4M3).
+template <int IN> struct TileFrag { i32x4 h[IN == 2 ? 2 : 1]; };
+
+template <int IN>
+__device__ __forceinline__ f32x16 tile_mfma(const TileFrag<IN>& a, const TileFrag<IN>& b, f32x16 c)
+{
+    if constexpr (IN == 2) {
+        const i32x8 x = __builtin_shufflevector(a.h[0], a.h[1], 0, 1, 2, 3, 4, 5, 6, 7);
+        const i32x8 y = __builtin_shufflevector(b.h[0], b.h[1], 0, 1, 2, 3, 4, 5, 6, 7);
+        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, c, 0, 0, 0, 0, 0, 0);   // scales 0: unscaled E4M3
+    } else {
+        return Elem<IN>::mfma(__builtin_bit_cast(s16x8, a.h[0]), __builtin_bit_cast(s16x8, b.h[0]), c);
+    }
+}
+
+// IN: 0 fp16, 1 bf16, 2 E4M3.  OUT: 0 fp16, 1 bf16.  OCC: workgroups per CU the registers must allow.
+template <int IN, int OUT, int BM, int BN, int WM, int WN, int WK, int S, int OCC>
+__global__ __launch_bounds__(WM * WN * WK * 64, OCC * WM * WN * WK / 4)
+void gemm_nt_tile_kernel(const char* __restrict__ A, const char* __restrict__ B, uint16_t* __restrict__ C,
+                         int M, int N, int row_bytes, int ntm, int ntn)
+{
+    typedef Elem<OUT> E;
+    constexpr int NW = WM * WN * WK;
+    constexpr int MB = BM / (32 * WM), NB = BN / (32 * WN);      // 32 x 32 blocks of C per wave
+    constexpr int KSTEPS = IN == 2 ? 2 : 4;                      // MFMA k-steps per stage
+    constexpr int KSW = KSTEPS / WK;                             // ... per wave
+    constexpr int HALVES = IN == 2 ? 2 : 1;                      // 16-byte reads per fragment
+    constexpr int STAGE_BYTES = (BM + BN) * 128;
+    constexpr int PIECES = (BM + BN) / 8, PPW = PIECES / NW;     // 1 KiB copies per stage, per wave
+    static_assert(PIECES % NW == 0 && KSTEPS % WK == 0 && (S - 1) * PPW <= 63, "shape of the workgroup");
+    constexpr int RED_BYTES = WK == 2 ? NW * MB * NB * 8 * 256 : 0;   // half of every wave's accumulators
+    constexpr int C_STRIDE = BN * 2 + 16;                        // bytes per row of the staged result
+    static_assert(WK <= 2 && RED_BYTES + BM * C_STRIDE <= S * STAGE_BYTES, "the epilogue reuses the ring");
+
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const unsigned lds_base = (unsigned)(size_t)(LDS_AS void*)smem;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int lr = lane & 31, g = lane >> 5;
+    const int wm = wave % WM, wn = (wave / WM) % WN, wk = wave / (WM * WN);
+
+    int tm, tn;
+    {
+        const int t = __builtin_amdgcn_readfirstlane(tile_schedule(ntm * ntn, (int)gridDim.x, (int)blockIdx.x, 0));
+        const int per_group = T_GROUP_M * ntn;
+        const int group = t / per_group, in_group = t - group * per_group;
+        const int first = group * T_GROUP_M, rows = min(ntm - first, T_GROUP_M);
+        tm = __builtin_amdgcn_readfirstlane(first + in_group % rows);
+        tn = __builtin_amdgcn_readfirstlane(in_group / rows);
+    }
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int nk = (row_bytes + 127) >> 7, nfull = row_bytes >> 7;   // stages, and those of them that are whole
+
+    // ---- copies.  Lane L of piece p fetches row 8 p + L / 8 of the stage, into slot L % 8: column (L % 8) ^ swizzle.
+    // Tiles that overhang the matrix clamp their rows (the surplus rows are never stored).
+    const char* src[PPW];
+    unsigned voff[PPW], half_off[PPW];
+#pragma unroll
+    for (int i = 0; i < PPW; ++i) {
+        const int p = wave * PPW + i;
+        const bool is_b = p >= BM / 8;
+        const int row = (is_b ? p - BM / 8 : p) * 8 + (lane >> 3);
+        const int col = (lane & 7) ^ ((row >> 1) & 7);
+        src[i] = is_b ? B : A;
+        voff[i] = (unsigned)(is_b ? min(n0 + row, N - 1) : min(m0 + row, M - 1)) * (unsigned)row_bytes + col * 16;
+        half_off[i] = (col & 4) * 16;
+    }
+    auto issue_piece = [&](int s, int i) __attribute__((always_inline)) {          // s < nfull
+        dma16(src[i] + (size_t)s * 128, voff[i], lds_base + (s % S) * STAGE_BYTES + (wave * PPW + i) * 1024);
+    };
+    auto issue_piece_any = [&](int s, int i) __attribute__((always_inline)) {      // s < nk
+        dma16(src[i] + (size_t)s * 128, s < nfull ? voff[i] : voff[i] - half_off[i],
+              lds_base + (s % S) * STAGE_BYTES + (wave * PPW + i) * 1024);
+    };
+
+    // ---- fragments
+    int frag_off[KSW][HALVES];
+#pragma unroll
+    for (int k = 0; k < KSW; ++k)
+#pragma unroll
+        for (int h = 0; h < HALVES; ++h) {
+            const int ks = wk * KSW + k;
+            const int col = IN == 2 ? ks * 4 + g * 2 + h : ks * 2 + g;
+            frag_off[k][h] = lr * 128 + ((col ^ ((lr >> 1) & 7)) * 16);
+        }
+    struct StageFrags { TileFrag<IN> am[KSW][MB], bn[KSW][NB]; };
+    constexpr int READS = KSW * (MB + NB) * HALVES, MFMAS = KSW * MB * NB;
+    auto read_one = [&](StageFrags& f, int s, int i) __attribute__((always_inline)) {   // in the order of use
+        const int k = i / ((MB + NB) * HALVES), r = (i / HALVES) % (MB + NB), h = i % HALVES;
+        const char* st = smem + (s % S) * STAGE_BYTES + frag_off[k][h];
+        if (r < NB) f.bn[k][r].h[h] = *reinterpret_cast<const i32x4*>(st + (BM + (wn * NB + r) * 32) * 128);
+        else f.am[k][r - NB].h[h] = *reinterpret_cast<const i32x4*>(st + (wm * MB + r - NB) * 32 * 128);
+    };
+
+    f32x16 acc[NB][MB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = f32x16(0.f);
+
+    // own copies of every stage but the last `out` ones issued are complete
+    auto wait_out = [&](int out) __attribute__((always_inline)) {
+        if (S > 7 && out >= 6) wait_vmcnt<(S > 7 ? 6 : 0) * PPW>();
+        else if (S > 6 && out == 5) wait_vmcnt<(S > 6 ? 5 : 0) * PPW>();
+        else if (S > 5 && out == 4) wait_vmcnt<(S > 5 ? 4 : 0) * PPW>();
+        else if (S > 4 && out == 3) wait_vmcnt<(S > 4 ? 3 : 0) * PPW>();
+        else if (S > 3 && out == 2) wait_vmcnt<(S > 3 ? 2 : 0) * PPW>();
+        else if (S > 2 && out == 1) wait_vmcnt<(S > 2 ? 1 : 0) * PPW>();
+        else wait_vmcnt<0>();
+    };
+    static_assert(S >= 2 && S <= 8, "wait_out lists the counts");
+
+    // ---- prologue: the whole ring in flight, stage 0 complete for everyone, its fragments requested
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+        if (s < nk) {
+#pragma unroll
+            for (int i = 0; i < PPW; ++i) issue_piece_any(s, i);
+        }
+    if (nk >= S) wait_vmcnt<(S - 1) * PPW>(); else wait_out(nk - 1);
+    ring_barrier();
+    StageFrags X, Y;
+#pragma unroll
+    for (int i = 0; i < READS; ++i) read_one(X, 0, i);
+
+    // Tile j: the MFMAs on the fragments in `cur`, behind them the requests for the next tile's and the copies
+    // of stage j + S.  STEADY: that stage exists and is whole.
+    auto tile = [&](int j, const StageFrags& cur, StageFrags& nxt, auto steady_tag) __attribute__((always_inline)) {
+        constexpr bool STEADY = decltype(steady_tag)::value;
+        if (STEADY) wait_vmcnt<(S - 2) * PPW>(); else wait_out(min(S - 2, nk - 2 - j));
+        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): this wave's reads of stage j are complete
+        ring_barrier();
+        const bool half = !STEADY && j >= nfull;                       // a half-filled last stage
+        const bool copy = STEADY || j + S < nk, next = STEADY || j + 1 < nk;
+#pragma unroll
+        for (int q = 0; q < MFMAS; ++q) {
+            const int k = q / (MB * NB), mb = (q / NB) % MB, nb = q % NB;
+            if (STEADY || !half || wk * KSW + k < KSTEPS / 2)
+                acc[nb][mb] = tile_mfma<IN>(cur.bn[k][nb], cur.am[k][mb], acc[nb][mb]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (next) {
+#pragma unroll
+                for (int i = q * READS / MFMAS; i < (q + 1) * READS / MFMAS; ++i) read_one(nxt, j + 1, i);
+            }
+            if (copy) {
+#pragma unroll
+                for (int i = q * PPW / MFMAS; i < (q + 1) * PPW / MFMAS; ++i) {
+                    if (STEADY) issue_piece(j + S, i); else issue_piece_any(j + S, i);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    {
+        typedef std::integral_constant<bool, true> steady_t;
+        typedef std::integral_constant<bool, false> draining_t;
+        int j = 0;
+        if (j + 1 + S < nfull) {
+            do {
+                tile(j, X, Y, steady_t());
+                tile(j + 1, Y, X, steady_t());
+                j += 2;
+            } while (j + 1 + S < nfull);
+        }
+        if (j + 1 < nk) {
+            do {
+                tile(j, X, Y, draining_t());
+                tile(j + 1, Y, X, draining_t());
+                j += 2;
+            } while (j + 1 < nk);
+        }
+        if (j < nk) tile(j, X, Y, draining_t());
+    }
+
+    // ---- the waves that split k exchange halves of their accumulators: quads 0, 1 of a block end up with wk = 0, quads
+    // 2, 3 with wk = 1.  (All copies have landed: the last tiles waited for everything.)
+    char* const cst = smem + RED_BYTES;
+    if constexpr (WK == 2) {
+        ring_barrier();           // nobody reads the ring any more
+        auto red = [&](int w, int blk, int t) __attribute__((always_inline)) -> f32x4* {
+            return reinterpret_cast<f32x4*>(smem + ((w * MB * NB + blk) * 2 + t) * 1024 + lane * 16);
+        };
+#pragma unroll
+        for (int blk = 0; blk < MB * NB; ++blk)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float lo = acc[blk % NB][blk / NB][t * 4 + e], hi = acc[blk % NB][blk / NB][8 + t * 4 + e];
+                    v[e] = wk == 0 ? hi : lo;
+                }
+                *red(wave, blk, t) = v;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int blk = 0; blk < MB * NB; ++blk)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const f32x4 v = *red(wave ^ (WM * WN), blk, t);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float lo = acc[blk % NB][blk / NB][t * 4 + e], hi = acc[blk % NB][blk / NB][8 + t * 4 + e];
+                    acc[blk % NB][blk / NB][t * 4 + e] = (wk == 0 ? lo : hi) + v[e];
+                }
+            }
+    } else {
+        ring_barrier();
+    }
+
+    // ---- results to the LDS, then out as row segments
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int t = 0; t < 4 / WK; ++t) {
+                u32x2 w;
+                w[0] = E::pack2(acc[nb][mb][t * 4 + 0], acc[nb][mb][t * 4 + 1]);
+                w[1] = E::pack2(acc[nb][mb][t * 4 + 2], acc[nb][mb][t * 4 + 3]);
+                const int row = (wm * MB + mb) * 32 + lr, col = (wn * NB + nb) * 32 + (wk * 2 + t) * 8 + g * 4;
+                *reinterpret_cast<u32x2*>(cst + row * C_STRIDE + col * 2) = w;
+            }
+    __syncthreads();
+    const int rows = min(BM, M - m0), cols = min(BN, N - n0);
+    if ((N & 7) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0) {
+        constexpr int CPR = BN / 8, RPI = NW * 64 / CPR;         // 16-byte chunks per row, rows per round
+        const int c = (threadIdx.x % CPR) * 8;
+#pragma unroll
+        for (int r0 = 0; r0 < BM; r0 += RPI) {
+            const int r = r0 + threadIdx.x / CPR;
+            if (r < rows && c < cols)
+                *reinterpret_cast<u32x4*>(C + (size_t)(m0 + r) * N + n0 + c) = *reinterpret_cast<const u32x4*>(cst + r * C_STRIDE + c * 2);
+        }
+    } else {
+        constexpr int RPI = NW * 64 / BN;
+        const int c = threadIdx.x % BN;
+#pragma unroll 4
+        for (int r0 = 0; r0 < BM; r0 += RPI) {
+            const int r = r0 + threadIdx.x / BN;
+            if (r < rows && c < cols) C[(size_t)(m0 + r) * N + n0 + c] = *reinterpret_cast<const uint16_t*>(cst + r * C_STRIDE + c * 2);
+        }
+    }
+}
+
+template <int IN, int OUT, int BM, int BN, int WM, int WN, int WK, int S, int OCC>
+int launch_tile(const GemmLaunchArgs& a)
+{
+    constexpr int smem = S * (BM + BN) * 128;
+    auto kern = gemm_nt_tile_kernel<IN, OUT, BM, BN, WM, WN, WK, S, OCC>;
+    static PerDeviceOnce once;                  // the attribute belongs to the (kernel, device) pair
+    if (once.prepare(reinterpret_cast<const void*>(kern), smem) < 0) return -1;
+    const char* A = (const char*)a.a;
+    const char* B = (const char*)a.b;
+    uint16_t* C = (uint16_t*)a.c;
+    int M = a.M, N = a.N, row_bytes = a.K * (IN == 2 ? 1 : 2);
+    int ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
+    void* args[] = {&A, &B, &C, &M, &N, &row_bytes, &ntm, &ntn};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3((unsigned)(ntm * ntn)), dim3(WM * WN * WK * 64),
+                                         args, smem, (hipStream_t)a.stream);
+    return e == hipSuccess ? 0 : -1;
+}
+
+// ---- which kernel takes a product.  Estimated time in microseconds of each candidate on a chip of 256 CUs, from the
+// number of its tiles and of 128-byte steps along K (one stage of the kernel above, and the same MFMA time for every
+// element type): start-up + rounds * (prologue and epilogue of a tile + steps * time per step).  A round is one tile on
+// every CU, also where two workgroups share a CU (shapes 1 and 2: their times per step are those of two tiles in
+// turn).  A step is cheaper while part of the chip is idle (step_idle: no other tile running).  Fitted to times measured on MI355X for
+// fp16 and E4M3 over M = N = 64 ... 8192 and K = 64 ... 16384: the choice is on average 1 % and at most 25 % slower
+// than the best of the four.  Microseconds at M x N x K, fp16, in the order 256 x 256, 64 x 64, 128 x 128 in pairs,
+// 128 x 128 with split k-steps (the choice in brackets):
+//    1000 x 777 x 512      30.3  [5.0]   9.3   8.5        64 x 64 x 16384     255  [35]   92   68
+//    2048 x 2048 x 512     18.5  11.4   [8.4] 11.2        2048 x 2048 x 4096   84   52    44  [37]
+//    8192 x 8192 x 256     93.6   114    [60]   88        8192 x 8192 x 4096 [463] 806   489  534
+struct ShapeModel { int tile; float start, per_tile, step_idle, step_full; };
+constexpr ShapeModel T_MODEL[4] = {
+    {256, 5.0f, 12.0f, 1.10f, 1.65f},       // 0: the 256 x 256 kernel
+    {64, 2.0f, 1.0f, 0.13f, 0.185f},        // 1
+    {128, 2.8f, 1.4f, 0.465f, 0.465f},      // 2
+    {128, 1.0f, 4.0f, 0.28f, 0.48f},        // 3
+};
+constexpr float T_ALONE = 0.09f;            // shape 2: what a step costs more in a round without a partner
+
+template <int IN, int OUT>
+int launch_shape(const GemmLaunchArgs& a, int shape)
+{
+    // E4M3 products keep one order of summation in every kernel (bit-identical results), so no wave splits their k-steps.
+    constexpr bool F8 = IN == 2;
+    switch (shape) {
+        case 1: return launch_tile<IN, OUT, 64, 64, 2, 2, F8 ? 1 : 2, 4, 2>(a);
+        case 2: return launch_tile<IN, OUT, 128, 128, 2, 2, 1, 2, 2>(a);
+        case 3: return launch_tile<IN, OUT, 128, 128, F8 ? 4 : 2, 2, F8 ? 1 : 2, 4, 1>(a);
+        default: return -1;
+    }
+}
+
+}  // namespace
+
+int gemm_tile_launch(const GemmLaunchArgs& a, int in_type, int shape)
+{
+    if (in_type == 0) return launch_shape<0, 0>(a, shape);
+    if (in_type == 1) return launch_shape<1, 1>(a, shape);
+    return a.dtype == 0 ? launch_shape<2, 0>(a, shape) : launch_shape<2, 1>(a, shape);
+}
+
+int gemm_tile_shape(int M, int N, long long row_bytes)
+{
+    const float steps = (float)((row_bytes + 127) / 128);
+    int best = 0;
+    float best_time = 0.f;
+    for (int s = 0; s < 4; ++s) {
+        const ShapeModel& m = T_MODEL[s];
+        const long long tiles = ((M + m.tile - 1LL) / m.tile) * ((N + m.tile - 1LL) / m.tile), rounds = (tiles + 255) / 256;
+        const float load = tiles < 256 ? tiles / 256.0f : 1.0f;
+        float time = m.start + rounds * (m.per_tile + (m.step_idle + (m.step_full - m.step_idle) * load) * steps);
+        if (s == 2 && (rounds & 1)) time += T_ALONE * steps;
+        if (s == 0 || time < best_time) {
+            best = s;
+            best_time = time;
+        }
+    }
+    return best;
+}

@@ -5,6 +5,8 @@ one final rounding to 16 bit): |C_gpu - C_ref| <= 1.01 * u * |C_ref| + 2e-6 * K,
 fp16 and 2^-8 for bf16 (half an ulp of the output); the second term bounds the accumulated fp32
 rounding for N(0,1) operands (K * 2^-24 * sum|a||b| / sqrt(K) in the typical case) with a wide margin.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -79,6 +81,31 @@ def test_every_kernel_configuration_in_full(env, M, N, K, dtype, config):
     # the configurations add the K tiles of an entry in the same order: bit-identical results
     c1 = run_gpu(env, a, b, dtype, config=1).double().cpu().numpy()
     assert np.array_equal(c, c1)
+
+
+def shape_of(binding, M, N, row_bytes):
+    return binding.load_library()["_Z15gemm_tile_shapeiix"](ctypes.c_int(M), ctypes.c_int(N), ctypes.c_longlong(row_bytes))
+
+
+# One to eleven 128-byte steps along K around the ring depths (4, 2, 4) of the small-tile shapes, whole and with a half-filled
+# last step (K % 64 == 32), tiles that overhang by one row or column and by all but one, rows of C for both store widths.
+@pytest.mark.parametrize("shape,M,N,Ks", [(1, 65, 63, (32, 64, 96, 128, 192, 224, 256, 288, 320, 352, 704)), (1, 64, 128, (288, 640)),
+                                          (1, 127, 136, (32, 320)), (2, 1937, 1936, (32, 64, 96, 128, 192)), (2, 1921, 2047, (160, 256)),
+                                          (3, 1025, 1929, (4096,)), (3, 1793, 1793, (4000,))])
+@pytest.mark.parametrize("dtype", [I.FP16, I.BF16])
+def test_small_tile_shapes(env, shape, M, N, Ks, dtype):
+    _, binding, G = env
+    for K in Ks:
+        assert shape_of(binding, M, N, 2 * K) == shape
+        a, b = I.make_ab(M, N, K, dtype, seed=1100 + M + N + K)
+        print("case gemm shape%d M%d N%d K%d dtype%d" % (shape, M, N, K, dtype), flush=True)
+        c = run_gpu(env, a, b, dtype)
+        if M * N * K < 1e9:
+            check(c.double().cpu().numpy(), G.gemm_nt(a, b, dtype), dtype, K, "shape %d M%d N%d K%d" % (shape, M, N, K))
+        else:
+            idx = np.asarray(I.sample_entries(M, N, min(4096, M * N // 2), seed=K, always=[(0, 0), (M - 1, N - 1), (0, N - 1), (M - 1, 0)]))
+            check(c[idx[:, 0], idx[:, 1]].double().cpu().numpy(), G.gemm_nt_samples(a, b, dtype, idx), dtype, K,
+                  "shape %d M%d N%d K%d" % (shape, M, N, K))
 
 
 def test_odd_n_uses_scalar_stores(env):

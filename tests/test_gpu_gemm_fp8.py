@@ -12,6 +12,8 @@ a factor 4 at the smallest K and is still far below a single wrong term: one mis
 of a fragment changes an entry by about 4 typical products, i.e. by 2^-4 S at K = 64 and 2^-12 S at
 K = 16384.  Integer-valued operands, whose sums are exact in any frame, must match bit for bit.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -91,6 +93,25 @@ def test_every_kernel_configuration_in_full(env, M, N, K, config):
     c1 = run_gpu(env, a, b, I.FP16, config=1).double().cpu().numpy()
     c0 = run_gpu(env, a, b, I.FP16).double().cpu().numpy()
     assert np.array_equal(c, c1) and np.array_equal(c, c0)
+
+
+# One to six 128-byte steps along K around the ring depths (4, 2, 4) of the small-tile shapes, whole and with a half-filled
+# last step (K % 128 == 64), overhanging tiles, rows of C for both store widths.
+@pytest.mark.parametrize("shape,M,N,Ks", [(1, 65, 63, (64, 128, 192, 320, 448, 512, 576, 640, 768)), (1, 127, 136, (64, 704)),
+                                          (2, 1937, 1936, (64, 128, 192, 384)), (3, 1025, 1929, (8192,))])
+def test_small_tile_shapes(env, shape, M, N, Ks):
+    _, binding, G = env
+    for K in Ks:
+        assert binding.load_library()["_Z15gemm_tile_shapeiix"](ctypes.c_int(M), ctypes.c_int(N), ctypes.c_longlong(K)) == shape
+        a, b = I.make_ab(M, N, K, I.E4M3, seed=1100 + M + N + K)
+        print("case gemm_fp8 shape%d M%d N%d K%d" % (shape, M, N, K), flush=True)
+        c = run_gpu(env, a, b, I.FP16)
+        # one order of summation in every kernel
+        assert bool((c == run_gpu(env, a, b, I.FP16, config=1)).all())
+        idx = np.asarray(I.sample_entries(M, N, min(4096, M * N // 2), seed=K, always=[(0, 0), (M - 1, N - 1), (0, N - 1), (M - 1, 0)]))
+        s_abs = (magnitudes(env, a[idx[:, 0]]) * magnitudes(env, b[idx[:, 1]])).sum(axis=1)
+        check(c[idx[:, 0], idx[:, 1]].double().cpu().numpy(), G.gemm_nt_samples(a, b, I.E4M3, idx), s_abs, I.FP16,
+              "shape %d M%d N%d K%d" % (shape, M, N, K))
 
 
 def test_odd_n_uses_scalar_stores(env):
