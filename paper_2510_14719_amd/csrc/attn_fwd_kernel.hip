@@ -75,6 +75,11 @@ constexpr float RESCALE_LOG2 = 8.0f;
 #define ATTN_D64_TWO_WG 0
 #endif
 
+// 1: small grids take the form that splits the keys of a tile between the wave groups (see launch_d).
+#ifndef ATTN_KEY_SPLIT
+#define ATTN_KEY_SPLIT 1
+#endif
+
 // Which wave group issues the global -> LDS copies (see COPY_WAVES in the kernel).
 #ifndef ATTN_COPY_GROUP
 #define ATTN_COPY_GROUP 0
@@ -131,15 +136,20 @@ __device__ __forceinline__ float xor32_sum(float x) {
 
 // (d = 64: the LDS ring is 64 KiB, two workgroups fit a CU; the second launch bound, waves per SIMD, asks the
 // compiler for the 128 registers per lane that let their 16 waves be resident together)
-template <int DTYPE, int D, int NW, int MB, int BN, int STAGES, bool CAUSAL, bool PERSIST>
+// KS = 2 (small grids): the two wave groups of a workgroup work on the SAME NW / 2 * 32 query rows and share out the keys of
+// every tile, group A the first half and group B the second, each with a softmax state of its own; at the end
+// partner waves (w and w + 4) exchange halves of O and their maxima and sums through the LDS and each stores half of
+// the features.  A workgroup then covers 128 rows in about half the time of 256, twice as many of them are there to
+// fill the chip, and both groups keep their phases (one on the matrix cores while the other does its softmax).
+template <int DTYPE, int D, int NW, int MB, int BN, int STAGES, bool CAUSAL, bool PERSIST, int KS = 1>
 __global__ __launch_bounds__(NW * 64, (D == 64 && ATTN_D64_TWO_WG) ? 4 : 1)
 void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                      uint16_t* __restrict__ o, float* __restrict__ lse, int N, int nqt, int total,
                      float scale, float scale_log2e)
 {
     typedef Elem<DTYPE> E;
-    constexpr int BM = NW * MB * 32;            // query rows per workgroup
-    constexpr int KB = BN / 32;                 // 32-key blocks per K/V tile
+    constexpr int BM = NW * MB * 32 / KS;       // query rows per workgroup
+    constexpr int KB = BN / 32 / KS;            // 32-key blocks of a K/V tile that a wave computes on
     constexpr int KK = D / 16;                  // contraction steps of Q K^T
     constexpr int DB = D / 32;                  // 32-wide feature blocks of O
     constexpr int ROW_BYTES = D * 2;
@@ -154,6 +164,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     constexpr int LPG = 2 * CPW;                // copies such a wave issues per stage (K part + V part)
     static_assert(CHUNKS % COPY_WAVES == 0, "tile must split evenly over the copying waves");
     static_assert(STAGES == 4, "the ring protocol below keeps four stages");
+    static_assert(KS == 1 || (KS == 2 && NW == 8 && !PERSIST && D / 32 % 2 == 0), "the key split pairs the two wave groups");
     static_assert(NW == 8 || NW == 12, "two or three groups of four waves, one wave of each group per SIMD");
 
 #ifdef ATTN_TIMING
@@ -167,6 +178,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     const int lr = lane & 31, g = lane >> 5;
     const int group = __builtin_amdgcn_readfirstlane(wave >> 2);   // waves w, w + 4 (, w + 8) share a SIMD
     const bool group_b = group == NG - 1;       // the group that does its softmax first
+    const int kb0 = KS == 2 ? group * KB : 0;   // first 32-key block of a tile that this wave computes on
 
     // ---- which (batch*head, query tile) the workgroup works on: set per round of the tile schedule
     int round = 0;
@@ -181,7 +193,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         int qt = tile - bh * nqt;
         if (CAUSAL) qt = nqt - 1 - qt;          // long rows first
         const int q0 = qt * BM;
-        wq0 = q0 + wave * (MB * 32);            // first query row of this wave
+        wq0 = q0 + (KS == 2 ? wave & 3 : wave) * (MB * 32);   // first query row of this wave
         head_off = (size_t)bh * N * D;
         qh = q + head_off;
         kh = reinterpret_cast<const char*>(k + head_off);
@@ -193,6 +205,10 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         }
         nt_w = nt;
         if (CAUSAL) nt_w = min(nt, (wq0 + MB * 32 - 1) / BN + 1);   // later tiles are wholly hidden from this wave's rows
+        if (KS == 2) {                          // the same for this wave's share of the keys (may be 0 for group B)
+            const int last_key = (CAUSAL ? min(wq0 + MB * 32, N) : N) - 1 - kb0 * 32;
+            nt_w = last_key < 0 ? 0 : min(nt, last_key / BN + 1);
+        }
         // All of these are wave-uniform; say so, or values that cross the tile loop end up in vector registers.
         nt = __builtin_amdgcn_readfirstlane(nt);
         nt_w = __builtin_amdgcn_readfirstlane(nt_w);
@@ -277,8 +293,8 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     float m_run[MB], l_run[MB];
 
     // per-lane LDS read offsets (the rest of every address is an immediate)
-    const int k_lane = (lr >> 4) * 1024 + g * 256 + (lr & 15) * 16;
-    const int v_lane = TILE_BYTES + (4 * g + ((lane & 15) >> 2)) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    const int k_lane = kb0 * 2048 + (lr >> 4) * 1024 + g * 256 + (lr & 15) * 16;
+    const int v_lane = TILE_BYTES + kb0 * 32 * 64 + (4 * g + ((lane & 15) >> 2)) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
 
     // K fragment (A operand of T): keys kb*32 + lane%32, features (kk*2 + lane/32)*8 .. +7
     auto read_kf = [&](const char* sk, int kb, int kk) __attribute__((always_inline)) -> s16x8 {
@@ -350,7 +366,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         constexpr int PART = decltype(part)::value;
         constexpr int NPAIR = KB * 8, NCOPY = 2 * CPW, PER = NPAIR / NCOPY;
         static_assert(!SPREAD || (PER >= 1 && PER * NCOPY == NPAIR), "copies spread evenly over the exponentials");
-        const int kv0 = j * BN;
+        const int kv0 = j * BN;                 // first key of the tile; the wave's own start at block kb0
         if (PART != 2 && ((kv0 + BN > N) || (CAUSAL && kv0 + BN - 1 > wq0))) {
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
@@ -360,7 +376,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                 for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const int key = kv0 + kb * 32 + (i >> 2) * 8 + g * 4 + (i & 3);
+                        const int key = kv0 + (kb0 + kb) * 32 + (i >> 2) * 8 + g * 4 + (i & 3);
                         if (key > lim) S[mb][kb][i] = -__builtin_inff();
                     }
             }
@@ -456,10 +472,11 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         const float inv = 1.0f / l_tot;
         const int row = ep_wq0 + mb * 32 + lr;
         if (row < N) {
-            if (g == 0) lh[row] = m_run[mb] * scale + __builtin_logf(l_tot);
+            if (g == 0 && !(KS == 2 && group_b)) lh[row] = m_run[mb] * scale + __builtin_logf(l_tot);
             uint16_t* orow = oh + (size_t)row * D;
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+            for (int db = 0; db < DB; ++db) {
+                if (KS == 2 && (db >= DB / 2) != group_b) continue;
 #pragma unroll
                 for (int i4 = 0; i4 < 4; ++i4) {
                     u32x2 w;
@@ -467,6 +484,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                     w[1] = E::pack2(O[mb][db][i4 * 4 + 2] * inv, O[mb][db][i4 * 4 + 3] * inv);
                     *reinterpret_cast<u32x2*>(orow + db * 32 + i4 * 8 + g * 4) = w;
                 }
+            }
         }
     }
     };
@@ -474,6 +492,46 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // ---- end of a tile: when the schedule has another tile for this workgroup, its prologue is issued
     // first (after a barrier: every wave is then done reading the ring), so that its copies and Q
     // loads are in flight while the epilogue of the finished tile normalises and stores.
+    // ---- KS = 2: O, row sum and reference of this wave become those of all keys, for the half of the features that it
+    // stores.  The reference of a wave without any visible key is -inf and weighs 0.
+    auto merge_groups = [&](auto upper) __attribute__((always_inline)) {
+        constexpr int SEND = decltype(upper)::value ? 0 : DB / 2, KEEP = DB / 2 - SEND;   // feature blocks
+        constexpr int FLOATS = DB / 2 * 16 + 2;
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        static_assert(NW * MB * FLOATS * 256 <= STAGES * STAGE_BYTES, "the exchange reuses the ring");
+        char* const mine = smem + wave * (MB * FLOATS * 256);
+        const char* const other = smem + (wave ^ 4) * (MB * FLOATS * 256);
+        __syncthreads();                        // nobody reads the ring any more
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+#pragma unroll
+            for (int t = 0; t < DB / 2 * 4; ++t) {
+                f32x4 x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = O[mb][SEND + t / 4][t % 4 * 4 + e];
+                *reinterpret_cast<f32x4*>(mine + (mb * FLOATS * 4 + t * 16) * 64 + lane * 16) = x;
+            }
+            *reinterpret_cast<f32x2*>(mine + (mb * FLOATS + DB / 2 * 16) * 256 + lane * 8) = f32x2{m_run[mb], l_run[mb]};
+        }
+        __syncthreads();
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            const f32x2 ml = *reinterpret_cast<const f32x2*>(other + (mb * FLOATS + DB / 2 * 16) * 256 + lane * 8);
+            const float m = __builtin_fmaxf(m_run[mb], ml[0]);
+            const float w0 = __builtin_amdgcn_exp2f((m_run[mb] - m) * scale_log2e), w1 = __builtin_amdgcn_exp2f((ml[0] - m) * scale_log2e);
+            l_run[mb] = l_run[mb] * w0 + ml[1] * w1;
+            m_run[mb] = m;
+#pragma unroll
+            for (int t = 0; t < DB / 2 * 4; ++t) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(other + (mb * FLOATS * 4 + t * 16) * 64 + lane * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    O[mb][KEEP + t / 4][t % 4 * 4 + e] = O[mb][KEEP + t / 4][t % 4 * 4 + e] * w0 + x[e] * w1;
+                }
+            }
+        }
+    };
+
     bool more = true;
     auto finish_tile = [&]() __attribute__((always_inline)) {
         const size_t ep_head_off = head_off;
@@ -586,6 +644,15 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             wait_stage(j);
             if (j + 2 < nt) issue_stage(j + 2);
         }
+        if constexpr (KS == 2) merge_groups(std::false_type{});
+        finish_tile();
+    } else if (KS == 2 && nt_w == 0) {
+        // no key of this wave's share is visible to its rows: it only copies
+        for (int j = 0; j < nt; ++j) {
+            wait_stage(j);
+            if (j + 2 < nt) issue_stage(j + 2);
+        }
+        if constexpr (KS == 2) merge_groups(std::true_type{});
         finish_tile();
     } else {
         // group B, iteration j: C_j then [U_j, T_{j+1}]; both contractions read stage j
@@ -622,6 +689,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             wait_stage(j);
             if (j + 2 < nt) issue_stage(j + 2);
         }
+        if constexpr (KS == 2) merge_groups(std::true_type{});
         finish_tile();
     }
     } while (more);
@@ -646,12 +714,12 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 #endif
 }
 
-template <int DTYPE, int D, int NW, int MB, int BN, int STAGES, bool CAUSAL, bool PERSIST>
+template <int DTYPE, int D, int NW, int MB, int BN, int STAGES, bool CAUSAL, bool PERSIST, int KS = 1>
 int launch(const AttnLaunchArgs& a)
 {
-    constexpr int BM = NW * MB * 32;
+    constexpr int BM = NW * MB * 32 / KS;
     constexpr int smem = STAGES * 2 * BN * D * 2;
-    auto kern = attn_fwd_kernel<DTYPE, D, NW, MB, BN, STAGES, CAUSAL, PERSIST>;
+    auto kern = attn_fwd_kernel<DTYPE, D, NW, MB, BN, STAGES, CAUSAL, PERSIST, KS>;
     static PerDeviceOnce once;                  // the attribute belongs to the (kernel, device) pair
     const int dev = once.prepare(reinterpret_cast<const void*>(kern), smem);
     if (dev < 0) return -1;
@@ -685,6 +753,17 @@ template <int DTYPE, int D>
 int launch_d(const AttnLaunchArgs& a)
 {
     constexpr int NW = D == 128 ? ATTN_CFG_NW : 8, MB = D == 64 ? ATTN_CFG_MB_D64 : ATTN_CFG_MB, BN = ATTN_CFG_BN, STAGES = ATTN_CFG_STAGES;
+    // Few tiles: 128-row tiles with the keys shared out between the wave groups (KS = 2).  A step of 64 keys takes 0.75 us
+    // (d = 128) instead of 1.16, at twice the tiles, so it pays while the 128-row tiles still fit the chip in
+    // one round; with the mask and long rows up to two rounds (one 256-row tile per CU would leave most of them waiting for the
+    // longest).  Measured on MI355X, fp16, 256-row against split tiles: 1 head, N 16384, d 128: 296 -> 193 us; 8 heads,
+    // N 2309, d 64: 43 -> 29; 32 heads, N 1024, d 128: 30 -> 25; one step beyond the line, 64 heads, N 1024, d 128: 42
+    // against 50.  Causal: 8 heads, N 8192, d 128: 179 -> 152, d 64: 140 -> 110; 64 heads, N 1024, d 128: 31 against 41.
+    if (ATTN_KEY_SPLIT && NW == 8 && STAGES == 4) {
+        const long long tiles128 = (long long)((a.N + 127) / 128) * a.B * a.H;
+        if (tiles128 <= 256 || (a.causal && a.N >= 2048 && tiles128 <= 512))
+            return a.causal ? launch<DTYPE, D, 8, 1, BN, STAGES, true, false, 2>(a) : launch<DTYPE, D, 8, 1, BN, STAGES, false, false, 2>(a);
+    }
     // When the persistent form is used (d = 128 only: at d = 64 two workgroups share a CU and cover each
     // other's prologue and epilogue, and the next tile's Q fragments would cost the registers that let
     // them co-reside).  Causal: always; measured +2.5 % at N = 8192 (balanced tile lengths, next

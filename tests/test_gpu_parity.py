@@ -96,6 +96,27 @@ def test_whole_heads_of_the_large_configs(G, oracle, name):
         G.check(o[sl], l[sl], o_ref, l_ref, "%s head (%d,%d)" % (name, b, h))
 
 
+# ------------------------------------------------------------ the forms for few and for many tiles
+# Few heads: 128-row tiles whose keys two wave groups share (group B sees keys 32 ... 63 of every 64, none at all up
+# to N = 32 and in the first rows of a causal head); many heads: 256-row tiles.  Lengths around the 32-key shares, the 64-key tiles
+# and the 128- and 256-row tiles; keys with a few dominant rows, so that the two groups end with different references.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,lengths", [(2, (1, 32, 33, 64, 65, 96, 97, 127, 129, 161, 2049)), (300, (33, 97, 129, 257))])
+def test_few_and_many_tiles(G, oracle, H, lengths, d, causal):
+    for N in lengths:
+        dtype = I.BF16 if N % 3 == 0 else I.FP16
+        q, k, v = I.make_qkv(1, H, N, d, dtype, 2000 + N + d, peaky=True)
+        print("case few/many tiles H%d N%d d%d causal%d dtype%d" % (H, N, d, causal, dtype), flush=True)
+        o, l = G.run_gpu(q, k, v, dtype, 1.0 / math.sqrt(d), causal)
+        for h in (0, H - 1):
+            sl = (slice(0, 1), slice(h, h + 1))
+            o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]),
+                                           dtype, 1.0 / math.sqrt(d), causal)
+            # rows that one key dominates carry the rounding of |O| up to ~4 (half a bf16 ulp there is 7.8e-3 ... 1.6e-2) and of P
+            G.check(o[sl], l[sl], o_ref, l_ref, "H%d N%d d%d head %d" % (H, N, d, h), tol_o_max=4e-2 if dtype == I.BF16 else 2e-2)
+
+
 # ------------------------------------------------------------ properties that hold at any size
 def test_c4_properties(G):
     """Non-causal: permuting K and V rows together leaves O and LSE unchanged (up to rounding order)."""
