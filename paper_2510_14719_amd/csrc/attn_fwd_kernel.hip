@@ -463,27 +463,42 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 
     // ---- epilogue: normalise, write O (16-bit) and LSE (natural log).  Expanded at the end of each
     // group's code path, so that the accumulators of the two paths never have to meet in one register set.
-    auto epilogue = [&](size_t ep_head_off, int ep_bh, int ep_wq0) __attribute__((always_inline)) {
+    // A lane holds one query row, a row of O is 2 D bytes: stored straight from the registers, an instruction touches 32
+    // rows with 16 bytes each.  The rows go through a piece of the ring that nobody reads any more, private to the
+    // wave (so no barrier), and leave as whole 64- to 256-byte segments.
+    // `region`: LDS offset of the wave's piece, 32 rows x F features; a row's 16-byte chunks are stored permuted so that
+    // the 8-byte writes and the 16-byte reads cover all banks.
+    constexpr int EPI_F = NW == 12 ? D / 4 : (PERSIST || KS == 2 ? D / 2 : D);   // features staged at a time
+    constexpr int EPI_BYTES = 32 * EPI_F * 2;
+    auto epilogue = [&](size_t ep_head_off, int ep_bh, int ep_wq0, unsigned region) __attribute__((always_inline)) {
+    constexpr int CH = EPI_F / 8, RPB = 16 / CH;                         // 16-byte chunks per staged row, rows per 256 bytes
     uint16_t* oh = o + ep_head_off;
     float* lh = lse + (size_t)ep_bh * N;
+    char* const st = smem + region;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
         const float l_tot = xor32_sum(l_run[mb]);
         const float inv = 1.0f / l_tot;
-        const int row = ep_wq0 + mb * 32 + lr;
-        if (row < N) {
-            if (g == 0 && !(KS == 2 && group_b)) lh[row] = m_run[mb] * scale + __builtin_logf(l_tot);
-            uint16_t* orow = oh + (size_t)row * D;
+        const int row0 = ep_wq0 + mb * 32;
+        if (g == 0 && row0 + lr < N && !(KS == 2 && group_b)) lh[row0 + lr] = m_run[mb] * scale + __builtin_logf(l_tot);
 #pragma unroll
-            for (int db = 0; db < DB; ++db) {
-                if (KS == 2 && (db >= DB / 2) != group_b) continue;
+        for (int part = 0; part < D / EPI_F; ++part) {
+            if (KS == 2 && (part != 0) != group_b) continue;
+            asm volatile("" ::: "memory");      // (order of the LDS accesses: another lane's row is read)
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    u32x2 w;
-                    w[0] = E::pack2(O[mb][db][i4 * 4 + 0] * inv, O[mb][db][i4 * 4 + 1] * inv);
-                    w[1] = E::pack2(O[mb][db][i4 * 4 + 2] * inv, O[mb][db][i4 * 4 + 3] * inv);
-                    *reinterpret_cast<u32x2*>(orow + db * 32 + i4 * 8 + g * 4) = w;
-                }
+            for (int c = 0; c < CH; ++c) {
+                const int db = (part * CH + c) / 4, i4 = c % 4;
+                u32x2 w;
+                w[0] = E::pack2(O[mb][db][i4 * 4 + 0] * inv, O[mb][db][i4 * 4 + 1] * inv);
+                w[1] = E::pack2(O[mb][db][i4 * 4 + 2] * inv, O[mb][db][i4 * 4 + 3] * inv);
+                *reinterpret_cast<u32x2*>(st + lr * (CH * 16) + ((c ^ ((lr / RPB) & (CH - 1))) * 16) + g * 8) = w;
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int p = 0; p < CH / 2; ++p) {                           // (the LDS accesses of a wave complete in order)
+                const int row = (p * 64 + lane) / CH, c = lane % CH;
+                const u32x4 w = *reinterpret_cast<const u32x4*>(st + row * (CH * 16) + ((c ^ ((row / RPB) & (CH - 1))) * 16));
+                if (row0 + row < N) *reinterpret_cast<u32x4*>(oh + (size_t)(row0 + row) * D + part * EPI_F + c * 8) = w;
             }
         }
     }
@@ -491,7 +506,9 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 
     // ---- end of a tile: when the schedule has another tile for this workgroup, its prologue is issued
     // first (after a barrier: every wave is then done reading the ring), so that its copies and Q
-    // loads are in flight while the epilogue of the finished tile normalises and stores.
+    // loads are in flight while the epilogue of the finished tile normalises and stores.  The epilogue stages its rows in
+    // slots that hold neither a stage still being read (nt - 1, or nt - 2) nor one being filled: slot 2 under the next
+    // prologue (stages -1, 0, 1), else those of the stages nt and nt + 1, which no copy targets; with KS = 2 above the exchange area.
     // ---- KS = 2: O, row sum and reference of this wave become those of all keys, for the half of the features that it
     // stores.  The reference of a wave without any visible key is -inf and weighs 0.
     auto merge_groups = [&](auto upper) __attribute__((always_inline)) {
@@ -538,12 +555,26 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         const int ep_bh = bh, ep_wq0 = wq0;
         const int next = PERSIST ? tile_schedule(total, (int)gridDim.x, (int)blockIdx.x, ++round) : -1;
         more = next >= 0;
+        unsigned region;
+        if (PERSIST) {
+            static_assert(!PERSIST || NW * EPI_BYTES <= STAGE_BYTES, "one free slot");
+            region = 2 * STAGE_BYTES + wave * EPI_BYTES;
+        } else if (KS == 2) {
+            constexpr int ABOVE = NW * MB * (D / 4 + 2) * 256;        // what merge_groups used
+            static_assert(PERSIST || KS != 2 || ABOVE + NW * EPI_BYTES <= STAGES * STAGE_BYTES, "above the exchange area");
+            region = ABOVE + wave * EPI_BYTES;
+        } else {
+            static_assert(PERSIST || KS == 2 || NW / 2 * EPI_BYTES <= STAGE_BYTES, "two free slots");
+            region = ((nt + wave / (NW / 2)) % STAGES) * STAGE_BYTES + wave % (NW / 2) * EPI_BYTES;
+        }
         if (more) {
             __builtin_amdgcn_s_barrier();
             set_tile(next);
             prologue();
+        } else if (PERSIST) {
+            __builtin_amdgcn_s_barrier();       // (slot 2 may hold one of the last two stages)
         }
-        epilogue(ep_head_off, ep_bh, ep_wq0);
+        epilogue(ep_head_off, ep_bh, ep_wq0, region);
     };
 
 #ifdef ATTN_TIMING
