@@ -88,6 +88,11 @@ constexpr float RESCALE_LOG2_FP8 = 8.0f;
 #define ATTN8_PERSISTENT 0
 #endif
 
+// 1: small grids take the form that splits the keys of a stage between the waves (see launch_fp8_d).
+#ifndef ATTN8_KEY_SPLIT
+#define ATTN8_KEY_SPLIT 1
+#endif
+
 // 1: in the steady state the copies of a stage are issued inside the pass, one piece behind each of a few
 // MFMAs; 0: all of them right after the barrier.
 #ifndef ATTN8_COPIES_IN_PASS
@@ -115,7 +120,10 @@ __device__ __forceinline__ float xor32_max_fp8(float x) {
     return __builtin_fmaxf(a, b);
 }
 
-template <int OUT, int D, int BN, bool CAUSAL, bool PERSIST>
+// KS = 2 (few tiles): a workgroup covers 128 query rows, a stage holds KS * BN keys, and the waves w and w + 4 work on
+// the same 32 rows, the first on the lower BN keys of every stage, the second on the upper, each with a softmax state of its own.
+// At the end they exchange halves of O and their maxima and sums through the LDS and each stores half of the features.
+template <int OUT, int D, int BN, bool CAUSAL, bool PERSIST, int KS = 1>
 __global__ __launch_bounds__(512)
 void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restrict__ k, const uint8_t* __restrict__ v,
                          uint16_t* __restrict__ o, float* __restrict__ lse, int N, int nqt, int total,
@@ -124,25 +132,29 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     typedef Elem<OUT> EO;
     constexpr int NW = 8, STAGES = ATTN8_STAGES;
     constexpr int AHEAD = STAGES - 2;           // iteration j issues the copies of stage j + AHEAD
-    constexpr int BM = NW * 32;                 // query rows per workgroup
-    constexpr int KB = BN / 32;                 // 32-key blocks per K/V tile
+    constexpr int BM = NW * 32 / KS;            // query rows per workgroup
+    constexpr int TBN = KS * BN;                // keys per K/V tile, of which a wave computes on BN
+    constexpr int KB = BN / 32;                 // 32-key blocks per tile and wave
     constexpr int KC = BN / 64;                 // 64-key contraction steps of U
     constexpr int FK = D / 64;                  // contraction steps of T
     constexpr int DB = D / 32;                  // 32-wide feature blocks of O
     constexpr int CPR = D / 16;                 // 16-byte columns per row
     constexpr int RPB = 256 / D;                // rows per 256 bytes (one sweep over the LDS banks)
     constexpr int RPP = 1024 / D;               // rows per 1 KiB piece (one copy instruction)
-    constexpr int TILE_BYTES = BN * D;          // one K or one V tile
+    constexpr int TILE_BYTES = TBN * D;         // one K or one V tile
     constexpr int STAGE_BYTES = 2 * TILE_BYTES;
     constexpr int CHUNKS = TILE_BYTES / 1024;   // pieces per tile
     constexpr int PPW = 2 * CHUNKS / NW;        // pieces (of K or V) a wave copies per stage
     static_assert(BN % 64 == 0 && (D == 64 || D == 128), "tile shape");
+    static_assert(KS == 1 || (KS == 2 && !PERSIST && BN == 64), "key split");
     static_assert((2 * CHUNKS) % NW == 0 && PPW >= 1, "a stage must split evenly over the eight waves");
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const unsigned lds_base = (unsigned)(size_t)(LDS_AS void*)smem;
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool upper = KS == 2 && wave >= 4;    // this wave works on the upper half of a tile's keys
+    const int key0 = upper ? BN : 0;            // ... which starts here
 
     // ---- which (batch*head, query tile) this workgroup works on.  PERSIST (the causal launch): one workgroup per CU
     // walks the static serpentine schedule of tile_schedule.h round by round (the persistent, statically balanced
@@ -159,15 +171,19 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     int qt = tile - bh * nqt;
     if (CAUSAL) qt = nqt - 1 - qt;              // long rows first
     const int q0 = qt * BM;
-    const int wq0 = __builtin_amdgcn_readfirstlane(q0 + wave * 32);   // first query row of this wave
+    const int wq0 = __builtin_amdgcn_readfirstlane(q0 + (KS == 2 ? wave & 3 : wave) * 32);   // first query row of this wave
     const size_t head_off = (size_t)bh * N * D;
     const uint8_t* qh = q + head_off;
     const char* kh = uniform_ptr(reinterpret_cast<const char*>(k + head_off));
     const char* vh = uniform_ptr(reinterpret_cast<const char*>(v + head_off));
-    int nt = (N + BN - 1) / BN;                 // K/V tiles the workgroup walks
-    if (CAUSAL) nt = min(nt, (min(q0 + BM, N) - 1) / BN + 1);
-    int nt_w = nt;                              // those this wave computes on (1 <= nt_w <= nt)
-    if (CAUSAL) nt_w = min(nt, (wq0 + 31) / BN + 1);
+    int nt = (N + TBN - 1) / TBN;               // K/V tiles the workgroup walks
+    if (CAUSAL) nt = min(nt, (min(q0 + BM, N) - 1) / TBN + 1);
+    int nt_w = nt;                              // those this wave computes on (1 <= nt_w <= nt; 0 too for an upper wave)
+    if (CAUSAL) nt_w = min(nt, (wq0 + 31) / TBN + 1);
+    if (KS == 2) {
+        const int last_key = (CAUSAL ? min(wq0 + 32, N) : N) - 1 - key0;
+        nt_w = last_key < 0 ? 0 : min(nt, last_key / TBN + 1);
+    }
     nt = __builtin_amdgcn_readfirstlane(nt);
     nt_w = __builtin_amdgcn_readfirstlane(nt_w);
     const int last_stage = max(AHEAD - 1, nt - 1);   // stages -2 .. last_stage are copied
@@ -210,7 +226,7 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
         piece_src[i] = uniform_ptr(piece_is_v[i] ? vh : kh + 2 * TILE_BYTES);
     }
     // Stage s lies wholly inside the sequence (K tile s+2 is its last one): scalar address arithmetic only.
-    auto stage_inside = [&](int s) __attribute__((always_inline)) -> bool { return (s + 3) * BN <= N; };
+    auto stage_inside = [&](int s) __attribute__((always_inline)) -> bool { return (s + 3) * TBN <= N; };
     auto issue_inside = [&](int s) __attribute__((always_inline)) {
         const unsigned sbase = lds_base + ((s + 2 * STAGES) % STAGES) * STAGE_BYTES;
 #pragma unroll
@@ -223,7 +239,7 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
             const int t = piece_is_v[i] ? s : s + 2;                   // the tile this piece belongs to
-            const int row = min(max(t * BN + piece_row[i], 0), N - 1);
+            const int row = min(max(t * TBN + piece_row[i], 0), N - 1);
             dma16(piece_is_v[i] ? vh : kh, (unsigned)(row * D + piece_col[i] * 16), sbase + piece_dst[i]);
         }
     };
@@ -267,12 +283,12 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     // with the fragment are disjoint from those that vary with the lane), and a stage starts on a 1 KiB
     // boundary: (stage + offset) ^ constant is the address, one register per tile kind instead of one per
     // fragment column.
-    const int k_lane0 = lr * D + (((g * 2) ^ ((lr / RPB) % CPR)) * 16);
+    const int k_lane0 = key0 * D + lr * D + (((g * 2) ^ ((lr / RPB) % CPR)) * 16);
     int v_lane0;
     {
         const int e = (lane & 15) >> 1, fh = (lane >> 4) & 1;
         const int p = g * 8 + e;
-        v_lane0 = TILE_BYTES + p * D + ((fh ^ (2 * ((p / RPB) % (CPR / 2)))) * 16) + (lane & 1) * 8;
+        v_lane0 = TILE_BYTES + key0 * D + p * D + ((fh ^ (2 * ((p / RPB) % (CPR / 2)))) * 16) + (lane & 1) * 8;
     }
     // (32-bit LDS addresses throughout: an XOR on a generic pointer would hide the address space from the compiler)
     auto lds_addr = [](const char* st, int off0, unsigned c) __attribute__((always_inline)) -> unsigned {
@@ -301,7 +317,7 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     auto softmax_head = [&](auto par, auto masked, int j) __attribute__((always_inline)) {
         constexpr int P = decltype(par)::value;
         if (decltype(masked)::value) {
-            const int kv0 = j * BN;
+            const int kv0 = j * TBN + key0;
             const int qi = wq0 + lr;
             const int lim = CAUSAL ? min(qi, N - 1) : N - 1;   // last visible key
 #pragma unroll
@@ -478,14 +494,17 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     //   j <= nt_w - 2   MFMAs of U_{j-1} and T_{j+1}, softmax C_j in between (no tile before the last needs a mask)
     //   j == nt_w - 1   U_{j-1}, then C_j with the mask (diagonal or ragged end), then U_j (stage j is visible)
     //   j >= nt_w       nothing: the wave only keeps copying its share for the others
-    pass(NO, Y, NO, NO, P1, stage_ptr(-2), 0);                          // T_0 into the scores of parity 0
     int j = 0;
+    if (KS == 2 && nt_w == 0) {
+        for (; j < nt; ++j) step(j);            // no key of this wave's share is visible to its rows: it only copies
+    } else {
+    pass(NO, Y, NO, NO, P1, stage_ptr(-2), 0);                          // T_0 into the scores of parity 0
     if (nt_w >= 2) {
         step(0);
         pass(NO, Y, Y, NO, P0, stage_ptr(-1), 0);                       // T_1 and C_0
         j = 1;
         // first the iterations whose copies (stage j + AHEAD) lie wholly inside the sequence: the pass issues them
-        const int j_in = min(nt_w - 2, N / BN - AHEAD - 3);
+        const int j_in = min(nt_w - 2, N / TBN - AHEAD - 3);
         if (ATTN8_COPIES_IN_PASS && j + 1 <= j_in) {
             do {                                // bottom-tested: the accumulators are updated in place
                 step(j, false);
@@ -526,27 +545,82 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     };
     if (j & 1) tail(P1, P0); else tail(P0, P1);
     for (++j; j < nt; ++j) step(j);                               // idle tail of a causal wave
+    }
     wait_vmcnt<0>();
 
-    // ---- epilogue: normalise, write O (16-bit) and LSE (natural log)
+    // ---- KS = 2: O, row sum and reference become those of all keys, for the half of the features this wave stores (the
+    // upper waves the upper half).  The reference of a wave without any visible key is -inf and weighs 0.
+    constexpr int XFLOATS = DB / 2 * 16 + 2, XBYTES = KS == 2 ? NW * XFLOATS * 256 : 0;
+    if constexpr (KS == 2) {
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        static_assert(XBYTES <= STAGES * STAGE_BYTES, "the exchange reuses the ring");
+        char* const mine = smem + wave * (XFLOATS * 256);
+        const char* const other = smem + (wave ^ 4) * (XFLOATS * 256);
+        auto exchange = [&](auto up) __attribute__((always_inline)) {
+            constexpr int SEND = decltype(up)::value ? 0 : DB / 2, KEEP = DB / 2 - SEND;
+            __syncthreads();                    // nobody reads the ring any more
+#pragma unroll
+            for (int t = 0; t < DB / 2 * 4; ++t) {
+                f32x4 x;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = O[SEND + t / 4][t % 4 * 4 + e];
+                *reinterpret_cast<f32x4*>(mine + t * 1024 + lane * 16) = x;
+            }
+            *reinterpret_cast<f32x2*>(mine + DB / 2 * 4096 + lane * 8) = f32x2{m_run, L[0]};
+            __syncthreads();
+            const f32x2 ml = *reinterpret_cast<const f32x2*>(other + DB / 2 * 4096 + lane * 8);
+            const float m = __builtin_fmaxf(m_run, ml[0]);
+            const float w0 = __builtin_amdgcn_exp2f((m_run - m) * scale_log2e), w1 = __builtin_amdgcn_exp2f((ml[0] - m) * scale_log2e);
+            L[0] = L[0] * w0 + ml[1] * w1;
+            m_run = m;
+#pragma unroll
+            for (int t = 0; t < DB / 2 * 4; ++t) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(other + t * 1024 + lane * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) O[KEEP + t / 4][t % 4 * 4 + e] = O[KEEP + t / 4][t % 4 * 4 + e] * w0 + x[e] * w1;
+            }
+        };
+        if (upper) exchange(std::true_type{}); else exchange(std::false_type{});
+    }
+
+    // ---- epilogue: normalise, write O (16-bit) and LSE (natural log).  A lane holds one query row; the rows go through
+    // a piece of the ring that is private to the wave and leave as whole segments (from the registers an instruction
+    // would touch 32 rows with 16 bytes each).  The pieces lie in the slots of the stages nt and nt + 1, which no wave
+    // reads and no copy targets any more (with KS = 2 above the exchange area).  A staged row's 16-byte chunks are permuted so that the 8-byte
+    // writes and the 16-byte reads cover all banks.
     {
+        constexpr int EPI_F = KS == 2 ? D / 2 : (STAGE_BYTES / 256 < D ? STAGE_BYTES / 256 : D);   // features staged at a time
+        static_assert(KS == 1 || XBYTES + NW * 32 * EPI_F * 2 <= STAGES * STAGE_BYTES, "above the exchange area");
+        constexpr int CH = EPI_F / 8, RPC = 16 / CH;                             // chunks per row, rows per 256 bytes
+        // (the lane id afresh: what follows from it is not computed ahead of the loop, where it would only be spilled)
+        int el;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(el));
+        const int er = el & 31, eg = el >> 5;
         uint16_t* oh = o + head_off;
         float* lh = lse + (size_t)bh * N;
         const float l_tot = L[0];               // every element of the ones block holds the row sum
         const float inv = 1.0f / l_tot;
-        const int row = wq0 + lr;
-        if (row < N) {
-            if (g == 0) lh[row] = m_run * scale + __builtin_logf(l_tot);
-            uint16_t* orow = oh + (size_t)row * D;
+        if (eg == 0 && wq0 + er < N && !upper) lh[wq0 + er] = m_run * scale + __builtin_logf(l_tot);
+        char* const es = smem + (KS == 2 ? XBYTES + wave * (32 * EPI_F * 2) : ((nt + (wave >> 2)) % STAGES) * STAGE_BYTES + (wave & 3) * (32 * EPI_F * 2));
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+        for (int part = 0; part < D / EPI_F; ++part) {
+            if (KS == 2 && (part != 0) != upper) continue;
+            asm volatile("" ::: "memory");      // (order of the LDS accesses: another lane's row is read)
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    u32x2 w;
-                    w[0] = EO::pack2(O[db][i4 * 4 + 0] * inv, O[db][i4 * 4 + 1] * inv);
-                    w[1] = EO::pack2(O[db][i4 * 4 + 2] * inv, O[db][i4 * 4 + 3] * inv);
-                    *reinterpret_cast<u32x2*>(orow + db * 32 + i4 * 8 + g * 4) = w;
-                }
+            for (int c = 0; c < CH; ++c) {
+                const int db = (part * CH + c) / 4, i4 = c % 4;
+                u32x2 w;
+                w[0] = EO::pack2(O[db][i4 * 4 + 0] * inv, O[db][i4 * 4 + 1] * inv);
+                w[1] = EO::pack2(O[db][i4 * 4 + 2] * inv, O[db][i4 * 4 + 3] * inv);
+                *reinterpret_cast<u32x2*>(es + er * (CH * 16) + ((c ^ ((er / RPC) & (CH - 1))) * 16) + eg * 8) = w;
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int p = 0; p < CH / 2; ++p) {  // (the LDS accesses of a wave complete in order)
+                const int row = (p * 64 + el) / CH, c = el % CH;
+                const u32x4 w = *reinterpret_cast<const u32x4*>(es + row * (CH * 16) + ((c ^ ((row / RPC) & (CH - 1))) * 16));
+                if (wq0 + row < N) *reinterpret_cast<u32x4*>(oh + (size_t)(wq0 + row) * D + part * EPI_F + c * 8) = w;
+            }
         }
     }
     if (!PERSIST) break;
@@ -571,12 +645,12 @@ extern "C" int attn8_dbg_read(unsigned long long* host, int n)
 namespace {
 #endif
 
-template <int OUT, int D, int BN, bool CAUSAL, bool PERSIST>
+template <int OUT, int D, int BN, bool CAUSAL, bool PERSIST, int KS = 1>
 int launch_fp8(const AttnLaunchArgs& a)
 {
-    constexpr int BM = 256;
-    constexpr int smem = ATTN8_STAGES * 2 * BN * D;
-    auto kern = attn_fwd_fp8_kernel<OUT, D, BN, CAUSAL, PERSIST>;
+    constexpr int BM = 256 / KS;
+    constexpr int smem = ATTN8_STAGES * 2 * KS * BN * D;
+    auto kern = attn_fwd_fp8_kernel<OUT, D, BN, CAUSAL, PERSIST, KS>;
     static PerDeviceOnce once;                  // the attribute belongs to the (kernel, device) pair
     const int dev = once.prepare(reinterpret_cast<const void*>(kern), smem);
     if (dev < 0) return -1;
@@ -607,6 +681,18 @@ template <int OUT, int D>
 int launch_fp8_d(const AttnLaunchArgs& a)
 {
     constexpr int BN = D == 128 ? ATTN8_CFG_BN_D128 : ATTN8_CFG_BN_D64;
+    // Few tiles: 128-row tiles with the keys of a 128-key stage shared out between the halves of the workgroup (KS = 2).
+    // A step then takes 0.91 us for 128 keys against 0.83 us for 64 (d = 128), at twice the tiles: it pays while the
+    // 128-row tiles fit the chip in one round, and with the mask and long rows (one 256-row tile per CU leaves most of them waiting
+    // for the longest) up to two rounds, at d = 64, whose registers do not spill, up to eight.  Up to 256 keys a tile
+    // has no steps to save.  Measured on MI355X, 256-row tiles against split ones (us): 1 head, N 16384, d 128: 218 -> 121;
+    // 32 heads, N 1024: 21 -> 17, d 64: 16.5 -> 11.4; beyond the line, 64 heads, N 1024, d 128: 24 against 33.  Causal: 8 heads,
+    // N 8192, d 128: 117 -> 87, 64 heads, N 4096, d 64: 156 -> 138; beyond the line, 64 heads, N 2048, d 128: 71 against 78.
+    if constexpr (ATTN8_KEY_SPLIT && BN == 64 && ATTN8_STAGES == 4) {
+        const long long tiles128 = (long long)((a.N + 127) / 128) * a.B * a.H;
+        if ((a.N > 256 && tiles128 <= 256) || (a.causal && a.N >= 2048 && tiles128 <= (D == 64 ? 2048 : 512)))
+            return a.causal ? launch_fp8<OUT, D, BN, true, false, 2>(a) : launch_fp8<OUT, D, BN, false, false, 2>(a);
+    }
     if (a.causal) return ATTN8_PERSISTENT ? launch_fp8<OUT, D, BN, true, true>(a) : launch_fp8<OUT, D, BN, true, false>(a);
     return launch_fp8<OUT, D, BN, false, false>(a);
 }

@@ -52,6 +52,24 @@ def test_many_tiles_ragged_tail(G, oracle, causal):
     _full(G, oracle, 1, 2, 1531, 64, causal, seed=178, out_dtype=I.BF16, what="ragged")
 
 
+# Few tiles: 128-row tiles whose 128-key stages two halves of a workgroup share (the upper half sees keys 64 ... 127 of every
+# 128, none at all in the first rows of a causal head); many tiles: 256-row tiles.  Lengths around those borders.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,lengths", [(2, (257, 319, 321, 383, 385, 449, 513, 2049)), (300, (97, 257))])
+def test_few_and_many_tiles(G, oracle, H, lengths, d, causal):
+    for N in lengths:
+        q, k, v = I.make_qkv(1, H, N, d, E4M3, 1500 + N + d, peaky=N % 2 == 1)
+        print("case fp8 few/many tiles H%d N%d d%d causal%d" % (H, N, d, causal), flush=True)
+        o, l = G.run_gpu_fp8(q, k, v, I.FP16, 1.0 / math.sqrt(d), causal)
+        for h in (0, H - 1):
+            sl = (slice(0, 1), slice(h, h + 1))
+            qh, kh, vh = (np.ascontiguousarray(x[sl]) for x in (q, k, v))
+            o_ref, l_ref, p = oracle.attn_ref(qh, kh, vh, E4M3, 1.0 / math.sqrt(d), causal, return_p=True)
+            bo, bl = G.fp8_bounds(p, G.e4m3_to_f64(vh), o_ref, I.FP16)
+            G.check_fp8(o[sl], l[sl], o_ref, l_ref, bo, bl, "H%d N%d d%d head %d" % (H, N, d, h))
+
+
 def test_config_f1(G, oracle):
     w = I.FP8_WORKLOADS["f1"]
     _full(G, oracle, w.B, w.H, w.N, w.d, w.causal, w.seed, what="f1")
