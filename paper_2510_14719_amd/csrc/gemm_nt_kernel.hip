@@ -10,8 +10,8 @@
 // Workgroup: a 256 x 256 tile of C, by 8 waves (two per SIMD; a wave owns 128 (m) x 64 (n), 8 accumulator
 // blocks) or by 4 waves (one per SIMD; 128 x 128, 16 accumulator blocks in the AGPRs).  The product is
 // computed transposed, D = B_tile A_tile^T, so that a lane ends up with one row m of C and runs of four
-// consecutive n: the 16-bit results leave as 8-byte stores (computed the other way round a lane would
-// hold single elements of 16 different rows).
+// consecutive n, which pack in pairs (computed the other way round a lane would hold single elements of 16
+// different rows); the 16-bit results leave as row segments through the LDS (gemm_store.h).
 //
 // Schedule of one wave, K tile j (32 wide, two MFMA k-steps): wait for its own copies of stage j+1;
 // barrier; then the MFMAs on fragments that were requested during tile j-1, with LDS requests (fragments
@@ -38,6 +38,7 @@
 #include <type_traits>
 
 #include "gemm_launch.h"
+#include "gemm_store.h"
 #include "gfx950_prims.h"
 #include "launch_once.h"
 #include "tile_schedule.h"
@@ -358,30 +359,12 @@ void gemm_nt_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__
     }
 #endif
     }  // !PAIRED
-    // ---- epilogue: lane holds row m of C and, per accumulator register quad, four consecutive n
-    const bool vec_ok = (N & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 7) == 0;
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-        const int m = m0 + wm * 128 + mb * 32 + lr;
-        if (m >= M) continue;
-        uint16_t* crow = C + (size_t)m * N;
-#pragma unroll
-        for (int nb = 0; nb < G_NB; ++nb)
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-                const int n = n0 + wn * (G_NB * 32) + nb * 32 + i4 * 8 + g * 4;
-                u32x2 w;
-                w[0] = E::pack2(acc[nb][mb][i4 * 4 + 0], acc[nb][mb][i4 * 4 + 1]);
-                w[1] = E::pack2(acc[nb][mb][i4 * 4 + 2], acc[nb][mb][i4 * 4 + 3]);
-                if (vec_ok && n + 3 < N) {
-                    *reinterpret_cast<u32x2*>(crow + n) = w;
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (n + e < N) crow[n + e] = (uint16_t)(w[e >> 1] >> ((e & 1) * 16));
-                }
-            }
-    }
+    // ---- epilogue: every copy has landed (the last tiles waited for all of them) and, behind the barrier, nobody reads
+    // the ring any more: each wave stages its block of C in a piece of it.
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    store_wave_block<E, G_NB>(smem + wave * (G_NB * 2048), acc, C, M, N, m0 + wm * 128, n0 + wn * (G_NB * 32), lane);
 }
 
 template <int DTYPE, int NW, bool PAIRED>

@@ -320,10 +320,11 @@ int launch_tile(const GemmLaunchArgs& a)
 // 128 x 128 with split k-steps (the choice in brackets):
 //    1000 x 777 x 512      30.3  [5.0]   9.3   8.5        64 x 64 x 16384     255  [35]   92   68
 //    2048 x 2048 x 512     18.5  11.4   [8.4] 11.2        2048 x 2048 x 4096   84   52    44  [37]
-//    8192 x 8192 x 256     93.6   114    [60]   88        8192 x 8192 x 4096 [463] 806   489  534
+//    8192 x 8192 x 256     74    113    [55]   86        8192 x 8192 x 2048 [233] 396   256  296
+//    8192 x 8192 x 512     92    146    [86]  120        8192 x 8192 x 1024 [132] 225   147  179
 struct ShapeModel { int tile; float start, per_tile, step_idle, step_full; };
 constexpr ShapeModel T_MODEL[4] = {
-    {256, 5.0f, 12.0f, 1.10f, 1.65f},       // 0: the 256 x 256 kernel
+    {256, 5.0f, 7.0f, 1.10f, 1.60f},      // 0: the 256 x 256 kernel
     {64, 2.0f, 1.0f, 0.13f, 0.185f},        // 1
     {128, 2.8f, 1.4f, 0.465f, 0.465f},      // 2
     {128, 1.0f, 4.0f, 0.28f, 0.48f},        // 3

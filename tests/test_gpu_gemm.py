@@ -108,6 +108,23 @@ def test_small_tile_shapes(env, shape, M, N, Ks, dtype):
                   "shape %d M%d N%d K%d" % (shape, M, N, K))
 
 
+# Rows of C that allow 16-, 8- and 2-byte stores, and a C that is aligned to less than its rows are; tiles that overhang by one
+# row and column, by most of a 32-row block and by whole waves; nothing outside C is written.
+@pytest.mark.parametrize("config", [2, 4])
+@pytest.mark.parametrize("M,N,skew", [(256, 264, 0), (255, 260, 0), (289, 131, 0), (97, 512, 4), (257, 256, 1), (33, 392, 8)])
+def test_large_tile_stores(env, config, M, N, skew):
+    torch, binding, G = env
+    K, dtype = 96, I.BF16
+    a, b = I.make_ab(M, N, K, dtype, seed=1300 + M + N)
+    print("case gemm stores config%d M%d N%d skew%d" % (config, M, N, skew), flush=True)
+    ad, bd = (torch.from_numpy(x.view(np.int16)).cuda().view(torch.bfloat16) for x in (a, b))
+    buf = torch.full((M * N + 64,), 7.0, dtype=torch.bfloat16, device="cuda")
+    c = buf[16 + skew:16 + skew + M * N].view(M, N)
+    assert binding.gemm_nt_raw(ad, bd, c, M, N, K, None, dtype, config=config) == 0
+    check(c.double().cpu().numpy(), G.gemm_nt(a, b, dtype), dtype, K, "stores config%d M%d N%d" % (config, M, N))
+    assert bool((buf[:16 + skew] == 7.0).all()) and bool((buf[16 + skew + M * N:] == 7.0).all())
+
+
 def test_odd_n_uses_scalar_stores(env):
     _, _, G = env
     M, N, K = 130, 37, 96                     # N % 4 != 0: rows of C are not 8-byte aligned
