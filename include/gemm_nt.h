@@ -47,7 +47,7 @@ enum { GEMM_NT_FP16 = 0, GEMM_NT_BF16 = 1 };
 int gemm_nt(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int dtype);
 
 /*
- * The same call with the kernel configuration chosen by the caller instead of by K (for tests and
+ * The same call with the kernel configuration chosen by the caller instead of by M, N and K (for tests and
  * measurements; every configuration computes the same product): 0 = as gemm_nt, 1 = 8 waves of 128 x 64,
  * 2 = the same with the copies of two consecutive K tiles issued together, 3 = 4 waves of 128 x 128,
  * 4 = the same with paired copies.  GEMM_NT_ERR_SHAPE for any other value.
@@ -80,7 +80,7 @@ int gemm_nt_check_args(const void *a, const void *b, const void *c, int M, int N
 int gemm_nt_fp8(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int out_dtype);
 
 /*
- * The same call with the kernel configuration chosen by the caller instead of by K (for tests and
+ * The same call with the kernel configuration chosen by the caller instead of by M, N and K (for tests and
  * measurements; every configuration computes the same product): 0 = as gemm_nt_fp8, 1 = 8 waves of 128 x 64,
  * 2 = the same with the copies of two consecutive K tiles issued together, 3 = 4 waves of 128 x 128,
  * 4 = the same with paired copies.  GEMM_NT_ERR_SHAPE for any other value.

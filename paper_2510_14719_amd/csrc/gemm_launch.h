@@ -8,15 +8,16 @@ struct GemmLaunchArgs {
     int M, N, K;
     int dtype;       // 0 = fp16, 1 = bf16 (for the 8-bit product: the type of c; a and b are E4M3 bytes)
     void* stream;    // hipStream_t
-    int config = 0;  // 0 = chosen by M, N and K, 1 ... 4 = a fixed configuration of the 256 x 256 kernel (waves per workgroup, paired copies)
+    int config = 0;  // 0 = chosen by M, N and K, 1 ... 4 = a fixed configuration of gemm_nt_kernel.hip / gemm_nt_fp8_kernel.hip (waves per workgroup, paired copies)
 };
 
 // Enqueue the kernel for already-validated arguments.  0 on success, -1 if HIP refused the launch.
 int gemm_launch(const GemmLaunchArgs& a);
 
-// Small-tile kernel (gemm_nt_tile_kernel.hip), shape 1, 2 or 3; in_type 0 = fp16, 1 = bf16, 2 = E4M3 operands.
+// The kernels that configuration 0 takes (gemm_nt_tile_kernel.hip): shape 0 (256 x 256 of C per workgroup), 1, 2 or 3;
+// in_type 0 = fp16, 1 = bf16, 2 = E4M3 operands.
 int gemm_tile_launch(const GemmLaunchArgs& a, int in_type, int shape);
-// The shape that configuration 0 takes for rows of row_bytes (K elements): 0 = the 256 x 256 kernel.
+// The shape for rows of row_bytes (K elements).
 int gemm_tile_shape(int M, int N, long long row_bytes);
 
 // Rows of C per workgroup (0), columns (1), K tile (2), LDS stages (3), threads per workgroup (4).

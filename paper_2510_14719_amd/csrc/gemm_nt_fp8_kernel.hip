@@ -10,11 +10,11 @@
 // byte geometry as in the 16-bit kernel (16-row pieces of 1 KiB, row-major, the 16-byte columns of row r
 // rotated by (r/4)%4), and one K tile is one k-step of the 32x32x64 MFMA (64 cycles each).
 //
-// Two shapes of the workgroup are compiled, and the launcher picks by K (where a 256 x 256 tile is the right
-// size at all: gemm_tile_shape in gemm_nt_tile_kernel.hip):
-//   short products: 8 waves (two per SIMD), a wave owns 128 (m) x 64 (n) = 8 accumulator blocks; ring of 4
+// These are the fixed configurations 1 to 4, for tests, sweeps and measurements (configuration 0 takes one of the kernels of
+// gemm_nt_tile_kernel.hip), in two shapes of the workgroup with and without paired copies:
+//   8 waves (two per SIMD), a wave owns 128 (m) x 64 (n) = 8 accumulator blocks; ring of 4
 //     stages, one stage copied per tile, three tiles ahead;
-//   K >= 2048: 4 waves (one per SIMD), a wave owns 128 x 128 = 16 accumulator blocks in the AGPRs; ring of 5
+//   4 waves (one per SIMD), a wave owns 128 x 128 = 16 accumulator blocks in the AGPRs; ring of 5
 //     stages with PAIRED copies: a 64-byte K tile asks the L2 for half a memory line, and what limits this
 //     kernel is the request path from the L2 into the CU, so two consecutive stages are copied together,
 //     piece by piece, at every second tile: the two halves of a line are requested back to back and the L1
@@ -49,7 +49,7 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 #ifndef GEMM8_COPY_PHASE
 #define GEMM8_COPY_PHASE 1
 #endif
-// Kernel configuration, fixed at compile time for the sweep harness or chosen per call by K (0):
+// Kernel configuration, fixed at compile time for the sweep harness or chosen per call (0, see gemm_fp8_launch):
 //   1: 8 waves (two per SIMD, 128 x 64 of C each), one stage copied per tile, three tiles ahead
 //   2: 8 waves, paired copies (see below)
 //   3: 4 waves (one per SIMD, 128 x 128 each, a third fewer LDS reads, accumulators in the AGPRs)
@@ -61,9 +61,6 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 #ifndef GEMM8_CONFIG
 #define GEMM8_CONFIG 0
 #endif
-// Smallest K for which configuration 0 takes the 4-wave paired kernel (below it: 8 waves, unpaired, whose
-// prologue and epilogue overlap better between the two waves of a SIMD).
-constexpr int H_LARGE_K = 2048;
 constexpr int H_BM = 256, H_BN = 256;   // tile of C per workgroup
 constexpr int H_BK = 64;                // K tile, elements = bytes per row
 #ifndef GEMM8_STAGES
@@ -354,12 +351,10 @@ int launch8(const GemmLaunchArgs& a)
     return e == hipSuccess ? 0 : -1;
 }
 
-int config_for(int K) { return GEMM8_CONFIG != 0 ? GEMM8_CONFIG : (K >= H_LARGE_K ? 4 : 1); }
-
 template <int OUT>
 int launch8_out(const GemmLaunchArgs& a)
 {
-    switch (a.config != 0 ? a.config : config_for(a.K)) {
+    switch (a.config != 0 ? a.config : GEMM8_CONFIG) {
         case 1: return launch8<OUT, 8, false>(a);
         case 2: return launch8<OUT, 8, true>(a);
         case 3: return launch8<OUT, 4, false>(a);
@@ -371,17 +366,18 @@ int launch8_out(const GemmLaunchArgs& a)
 
 int gemm_fp8_launch(const GemmLaunchArgs& a)
 {
-    if (GEMM8_CONFIG == 0 && a.config == 0) {
-        const int shape = gemm_tile_shape(a.M, a.N, a.K);
-        if (shape != 0) return gemm_tile_launch(a, 2, shape);
-    }
+    if (GEMM8_CONFIG == 0 && a.config == 0) return gemm_tile_launch(a, 2, gemm_tile_shape(a.M, a.N, a.K));
     return a.dtype == 0 ? launch8_out<0>(a) : launch8_out<1>(a);
 }
 
 // Reported for the configuration a large K takes.
 int gemm_fp8_launch_tile_param(int which)
 {
-    const int cfg = config_for(1 << 20);
+    if (GEMM8_CONFIG == 0) {                      // gemm_nt_wide_kernel: a ring of two and a half stages
+        constexpr int wide[] = {256, 256, 128, 2, 256};
+        return which >= 0 && which < 5 ? wide[which] : -1;
+    }
+    const int cfg = GEMM8_CONFIG;
     switch (which) {
         case 0: return H_BM;
         case 1: return H_BN;

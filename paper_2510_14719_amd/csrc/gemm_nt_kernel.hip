@@ -21,8 +21,8 @@
 //   the request path from the L2 into the CU; so even tiles issue the pieces of stages j+4 and j+5
 //   alternately and odd tiles none: the two halves of a line are requested back to back and the L1 merges
 //   them into one request to the L2 (+9-13 % at K >= 2048).
-// The launcher takes the 4-wave paired kernel from K = 2048 on and the 8-wave paired kernel below, where a
-// 256 x 256 tile is the right size at all (gemm_tile_shape in gemm_nt_tile_kernel.hip).
+// These are the fixed configurations 1 to 4, for tests, sweeps and measurements; configuration 0 takes one of the kernels of
+// gemm_nt_tile_kernel.hip, which copy whole lines per row and are faster at every size (the rule and the times are there).
 //
 // Measured on the device (M = N = 8192, K = 8192, fp16 N(0,1) operands, same box and session), 8 waves,
 // unpaired: 1.16 PFLOP/s; with the copies left out (wrong results, timing only) 1.40; with the
@@ -60,7 +60,7 @@ __device__ unsigned long long gemm_dbg[256 * 8 * 8];
 #ifndef GEMM_TAIL_READS
 #define GEMM_TAIL_READS 3
 #endif
-// Kernel configuration, fixed at compile time for the sweep harness or chosen per call by K (0):
+// Kernel configuration, fixed at compile time for the sweep harness or chosen per call (0, see gemm_launch):
 //   1: 8 waves (two per SIMD, 128 x 64 of C each), one stage copied per tile, three tiles ahead
 //   2: 8 waves, paired copies
 //   3: 4 waves (one per SIMD, 128 x 128 each, a third fewer LDS reads, accumulators in the AGPRs)
@@ -72,9 +72,6 @@ __device__ unsigned long long gemm_dbg[256 * 8 * 8];
 #ifndef GEMM_CONFIG
 #define GEMM_CONFIG 0
 #endif
-// Configuration 0: the 4-wave paired kernel from this K on, the 8-wave paired kernel below it (whose
-// prologue and epilogue overlap better between the two waves of a SIMD).
-constexpr int G_LARGE_K = 2048;
 constexpr int G_BM = 256, G_BN = 256;   // tile of C per workgroup
 constexpr int G_BK = 32;                // K tile
 #ifndef GEMM_STAGES
@@ -385,12 +382,10 @@ int launch(const GemmLaunchArgs& a)
     return e == hipSuccess ? 0 : -1;
 }
 
-int config_for(int K) { return GEMM_CONFIG != 0 ? GEMM_CONFIG : (K >= G_LARGE_K ? 4 : 2); }
-
 template <int DTYPE>
 int launch_dtype(const GemmLaunchArgs& a)
 {
-    switch (a.config != 0 ? a.config : config_for(a.K)) {
+    switch (a.config != 0 ? a.config : GEMM_CONFIG) {
         case 1: return launch<DTYPE, 8, false>(a);
         case 2: return launch<DTYPE, 8, true>(a);
         case 3: return launch<DTYPE, 4, false>(a);
@@ -409,17 +404,18 @@ extern "C" int gemm_dbg_read(unsigned long long* host, int n)
 
 int gemm_launch(const GemmLaunchArgs& a)
 {
-    if (GEMM_CONFIG == 0 && a.config == 0) {
-        const int shape = gemm_tile_shape(a.M, a.N, 2LL * a.K);
-        if (shape != 0) return gemm_tile_launch(a, a.dtype, shape);
-    }
+    if (GEMM_CONFIG == 0 && a.config == 0) return gemm_tile_launch(a, a.dtype, gemm_tile_shape(a.M, a.N, 2LL * a.K));
     return a.dtype == 0 ? launch_dtype<0>(a) : launch_dtype<1>(a);
 }
 
 // Reported for the configuration a large K takes.
 int gemm_launch_tile_param(int which)
 {
-    const int cfg = config_for(1 << 20);
+    if (GEMM_CONFIG == 0) {                      // gemm_nt_wide_kernel: a ring of two and a half stages
+        constexpr int wide[] = {256, 256, 64, 2, 256};
+        return which >= 0 && which < 5 ? wide[which] : -1;
+    }
+    const int cfg = GEMM_CONFIG;
     switch (which) {
         case 0: return G_BM;
         case 1: return G_BN;

@@ -20,14 +20,14 @@
 // fragment read touches cover all 64 banks.
 //
 // Epilogue: the product is computed transposed (a lane holds one row m of C and runs of four n).  The 16-bit results go
-// through the LDS and leave as whole row segments of the tile (16 bytes per lane, or single elements side by side
-// when N or the pointer does not allow wider stores): stored straight from the registers, an instruction would
+// through the LDS and leave as whole row segments of the tile (16 bytes per lane): stored straight from the registers, an instruction would
 // touch 32 rows with 16 bytes each.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
 
 #include "gemm_launch.h"
+#include "gemm_store.h"
 #include "gfx950_prims.h"
 #include "launch_once.h"
 #include "tile_schedule.h"
@@ -62,6 +62,17 @@ __device__ __forceinline__ f32x16 tile_mfma(const TileFrag<IN>& a, const TileFra
     }
 }
 
+// The workgroup's tile (tile row, tile column).
+__device__ __forceinline__ void raster_tile(int ntm, int ntn, int& tm, int& tn)
+{
+    const int t = __builtin_amdgcn_readfirstlane(tile_schedule(ntm * ntn, (int)gridDim.x, (int)blockIdx.x, 0));
+    const int per_group = T_GROUP_M * ntn;
+    const int group = t / per_group, in_group = t - group * per_group;
+    const int first = group * T_GROUP_M, rows = min(ntm - first, T_GROUP_M);
+    tm = __builtin_amdgcn_readfirstlane(first + in_group % rows);
+    tn = __builtin_amdgcn_readfirstlane(in_group / rows);
+}
+
 // IN: 0 fp16, 1 bf16, 2 E4M3.  OUT: 0 fp16, 1 bf16.  OCC: workgroups per CU the registers must allow.
 template <int IN, int OUT, int BM, int BN, int WM, int WN, int WK, int S, int OCC>
 __global__ __launch_bounds__(WM * WN * WK * 64, OCC * WM * WN * WK / 4)
@@ -89,14 +100,7 @@ void gemm_nt_tile_kernel(const char* __restrict__ A, const char* __restrict__ B,
     const int wm = wave % WM, wn = (wave / WM) % WN, wk = wave / (WM * WN);
 
     int tm, tn;
-    {
-        const int t = __builtin_amdgcn_readfirstlane(tile_schedule(ntm * ntn, (int)gridDim.x, (int)blockIdx.x, 0));
-        const int per_group = T_GROUP_M * ntn;
-        const int group = t / per_group, in_group = t - group * per_group;
-        const int first = group * T_GROUP_M, rows = min(ntm - first, T_GROUP_M);
-        tm = __builtin_amdgcn_readfirstlane(first + in_group % rows);
-        tn = __builtin_amdgcn_readfirstlane(in_group / rows);
-    }
+    raster_tile(ntm, ntn, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int nk = (row_bytes + 127) >> 7, nfull = row_bytes >> 7;   // stages, and those of them that are whole
 
@@ -272,23 +276,12 @@ void gemm_nt_tile_kernel(const char* __restrict__ A, const char* __restrict__ B,
             }
     __syncthreads();
     const int rows = min(BM, M - m0), cols = min(BN, N - n0);
-    if ((N & 7) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0) {
-        constexpr int CPR = BN / 8, RPI = NW * 64 / CPR;         // 16-byte chunks per row, rows per round
-        const int c = (threadIdx.x % CPR) * 8;
+    constexpr int CPR = BN / 8, RPI = NW * 64 / CPR;             // 16-byte chunks per row, rows per round
+    const int c = (threadIdx.x % CPR) * 8;
 #pragma unroll
-        for (int r0 = 0; r0 < BM; r0 += RPI) {
-            const int r = r0 + threadIdx.x / CPR;
-            if (r < rows && c < cols)
-                *reinterpret_cast<u32x4*>(C + (size_t)(m0 + r) * N + n0 + c) = *reinterpret_cast<const u32x4*>(cst + r * C_STRIDE + c * 2);
-        }
-    } else {
-        constexpr int RPI = NW * 64 / BN;
-        const int c = threadIdx.x % BN;
-#pragma unroll 4
-        for (int r0 = 0; r0 < BM; r0 += RPI) {
-            const int r = r0 + threadIdx.x / BN;
-            if (r < rows && c < cols) C[(size_t)(m0 + r) * N + n0 + c] = *reinterpret_cast<const uint16_t*>(cst + r * C_STRIDE + c * 2);
-        }
+    for (int r0 = 0; r0 < BM; r0 += RPI) {
+        const int r = r0 + threadIdx.x / CPR;
+        if (r < rows) store_chunk(C + (size_t)(m0 + r) * N + n0 + c, *reinterpret_cast<const u32x4*>(cst + r * C_STRIDE + c * 2), cols - c);
     }
 }
 
@@ -310,21 +303,197 @@ int launch_tile(const GemmLaunchArgs& a)
     return e == hipSuccess ? 0 : -1;
 }
 
+// ---- 256 x 256 of C per workgroup, for products that fill the chip with such tiles.  Four waves, one per SIMD, 128 x 128 each (the
+// split that reads least from the LDS: 128 KiB per 128-byte step along K, next to 64 KiB of copies written; the MFMAs of
+// a step take 2048 cycles), accumulators in the AGPRs.
+//
+// A step's rows are whole 128-byte lines (layout of the small-tile kernel), so one copy instruction asks the L2 for 8 lines
+// and copies can be spread evenly: one behind every fourth 32-cycle MFMA.  (Issued in bursts they fill the CU's
+// address path, 16 cycles per copy, and the waves that queue for it cannot issue their MFMAs.)
+//
+// Ring of five 32 KiB slots for the sequence A_0 B_0 A_1 B_1 A_2 ...: A_j and B_j are the operand tiles of step j.
+// Fragments are read one k-step ahead, so step j has been read completely when its last k-step starts.  There is the one
+// barrier of a step: behind it the slots of A_j and B_j are free and step j + 1 is complete; B_{j+2} and then A_{j+3} are
+// copied into the two slots until the next such point, which waits for B_{j+2} and leaves A_{j+3} in flight.
+template <int IN, int OUT>
+__global__ __launch_bounds__(256, 1)
+void gemm_nt_wide_kernel(const char* __restrict__ A, const char* __restrict__ B, uint16_t* __restrict__ C,
+                         int M, int N, int row_bytes, int ntm, int ntn)
+{
+    typedef Elem<OUT> E;
+    constexpr int KSTEPS = IN == 2 ? 2 : 4, HALVES = IN == 2 ? 2 : 1;
+    constexpr int SLOT = 256 * 128, SLOTS = 5;
+    constexpr int PPW = 8;                      // copies per wave and operand tile
+    constexpr int READS = 8 * HALVES;           // fragment reads per k-step: 4 blocks of each operand
+    constexpr int SPAN = 16 * KSTEPS;           // MFMAs between two barriers
+    constexpr int COPY_EVERY = SPAN / (2 * PPW);
+
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    const unsigned lds_base = (unsigned)(size_t)(LDS_AS void*)smem;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int lr = lane & 31, g = lane >> 5;
+    const int wm = wave & 1, wn = wave >> 1;
+
+    int tm, tn;
+    raster_tile(ntm, ntn, tm, tn);
+    const int m0 = tm * 256, n0 = tn * 256;
+    const int nk = (row_bytes + 127) >> 7, nfull = row_bytes >> 7;   // steps, and those of them that are whole
+
+    // ---- copies: lane L of piece p fetches row 8 p + L / 8 into slot L % 8 of the row (see gemm_nt_tile_kernel)
+    unsigned a_off[PPW], b_off[PPW];
+    auto piece_col = [&](int i) __attribute__((always_inline)) { return (lane & 7) ^ (((wave * PPW + i) * 4 + (lane >> 4)) & 7); };
+#pragma unroll
+    for (int i = 0; i < PPW; ++i) {
+        const int row = (wave * PPW + i) * 8 + (lane >> 3);
+        a_off[i] = (unsigned)min(m0 + row, M - 1) * (unsigned)row_bytes + piece_col(i) * 16;
+        b_off[i] = (unsigned)min(n0 + row, N - 1) * (unsigned)row_bytes + piece_col(i) * 16;
+    }
+    // piece i of the A (B) tile of step s < nk; `whole`: s < nfull is known (else a half step fetches its first half twice)
+    auto copy = [&](const char* mat, const unsigned (&off)[PPW], int s, int i, int slot, auto whole) __attribute__((always_inline)) {
+        const unsigned o = decltype(whole)::value || s < nfull ? off[i] : off[i] - (piece_col(i) & 4) * 16;
+        dma16(mat + (size_t)s * 128, o, lds_base + slot * SLOT + (wave * PPW + i) * 1024);
+    };
+
+    // ---- fragments of k-step k, in the order of use (MFMA q of a k-step multiplies block q / 4 of A with block q % 4 of B)
+    struct Frags { TileFrag<IN> am[4], bn[4]; };
+    auto read_one = [&](Frags& f, int k, int slot_a, int slot_b, int i) __attribute__((always_inline)) {
+        const int r = i / HALVES, h = i % HALVES;
+        const int col = IN == 2 ? k * 4 + g * 2 + h : k * 2 + g;
+        const int off = lr * 128 + ((col ^ ((lr >> 1) & 7)) * 16);
+        const bool is_a = r == 1 || r > 4;
+        const int blk = r == 0 || r == 1 ? 0 : (r <= 4 ? r - 1 : r - 4);
+        if (is_a) f.am[blk].h[h] = *reinterpret_cast<const i32x4*>(smem + slot_a * SLOT + wm * 16384 + off + blk * 4096);
+        else f.bn[blk].h[h] = *reinterpret_cast<const i32x4*>(smem + slot_b * SLOT + wn * 16384 + off + blk * 4096);
+    };
+
+    f32x16 acc[4][4];
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb) acc[nb][mb] = f32x16(0.f);
+
+    typedef std::integral_constant<bool, true> yes_t;
+    typedef std::integral_constant<bool, false> no_t;
+    auto next_slot = [](int s, int by) __attribute__((always_inline)) { s += by; return s >= SLOTS ? s - SLOTS : s; };
+
+    // ---- one k-step: 16 MFMAs on `cur` (unless `skip`: the missing half of a half step); between them the reads of the
+    // next k-step's fragments (while read_next) and whatever `behind(q)` issues
+    auto kstep = [&](const Frags& cur, Frags& nxt, int next_k, int slot_a, int slot_b, bool skip, bool read_next, auto behind) __attribute__((always_inline)) {
+        if (skip) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                if (q < READS && read_next) read_one(nxt, next_k, slot_a, slot_b, q);
+                behind(q);
+            }
+            return;
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int mb = q / 4, nb = q % 4;
+            acc[nb][mb] = tile_mfma<IN>(cur.bn[nb], cur.am[mb], acc[nb][mb]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (q < READS && read_next) read_one(nxt, next_k, slot_a, slot_b, q);
+            behind(q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto nothing = [](int) __attribute__((always_inline)) {};
+
+    // ---- prologue: the whole ring in flight; step 0 complete for everyone
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+        if (s < nk) {
+#pragma unroll
+            for (int i = 0; i < PPW; ++i) copy(A, a_off, s, i, 2 * s, no_t());
+            if (s < 2) {
+#pragma unroll
+                for (int i = 0; i < PPW; ++i) copy(B, b_off, s, i, 2 * s + 1, no_t());
+            }
+        }
+    if (nk > 2) wait_vmcnt<3 * PPW>(); else if (nk > 1) wait_vmcnt<2 * PPW>(); else wait_vmcnt<0>();
+    ring_barrier();
+    Frags X, Y;
+#pragma unroll
+    for (int i = 0; i < READS; ++i) read_one(X, 0, 0, 1, i);
+#pragma unroll
+    for (int k = 0; k < KSTEPS - 1; ++k)
+        kstep(k & 1 ? Y : X, k & 1 ? X : Y, k + 1, 0, 1, false, true, nothing);   // (the launcher keeps nfull >= 1)
+
+    // ---- from the barrier of step p to that of step p + 1: the last k-step of p, the others of p + 1.  STEADY: step p + 3
+    // exists and is whole.
+    int sa = 0;                                 // slot of A_p (B_p has the next one)
+    auto span = [&](int p, auto steady) __attribute__((always_inline)) {
+        constexpr bool STEADY = decltype(steady)::value;
+        if (STEADY || p + 2 < nk) wait_vmcnt<PPW>(); else wait_vmcnt<0>();   // own copies of step p + 1
+        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): this wave has read step p
+        ring_barrier();
+        const int free_a = sa, free_b = next_slot(sa, 1);
+        sa = next_slot(sa, 2);
+        const int sb = next_slot(sa, 1);
+        const bool half = !STEADY && p + 1 >= nfull;
+#pragma unroll
+        for (int k0 = 0; k0 < KSTEPS; ++k0) {   // k-step k0 of the span reads the fragments of k-step k0 of step p + 1
+            kstep(k0 & 1 ? X : Y, k0 & 1 ? Y : X, k0, sa, sb, half && k0 - 1 >= KSTEPS / 2, true, [&](int q) __attribute__((always_inline)) {
+                const int slot = k0 * 16 + q;
+                if (slot % COPY_EVERY != COPY_EVERY - 1) return;
+                const int i = slot / COPY_EVERY;
+                if (i < PPW) {
+                    if (STEADY || p + 2 < nk) copy(B, b_off, p + 2, i, free_a, steady);
+                } else {
+                    if (STEADY || p + 3 < nk) copy(A, a_off, p + 3, i - PPW, free_b, steady);
+                }
+            });
+        }
+    };
+    int p = 0;
+    if (p + 3 < nfull) {
+        do { span(p, yes_t()); } while (++p + 3 < nfull);
+    }
+    if (p + 1 < nk) {
+        do { span(p, no_t()); } while (++p + 1 < nk);
+    }
+    // ---- the last k-step.  Behind the barrier everything has been copied and read: the epilogue may use the ring.
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    ring_barrier();
+    kstep(Y, X, 0, 0, 0, nk > nfull, false, nothing);
+    store_wave_block<E, 4>(smem + wave * 8192, acc, C, M, N, m0 + wm * 128, n0 + wn * 128, lane);
+}
+
+template <int IN, int OUT>
+int launch_wide(const GemmLaunchArgs& a)
+{
+    constexpr int smem = 5 * 256 * 128;
+    if (a.K * (IN == 2 ? 1 : 2) < 128) return -1;   // the first step must be whole
+    auto kern = gemm_nt_wide_kernel<IN, OUT>;
+    static PerDeviceOnce once;                  // the attribute belongs to the (kernel, device) pair
+    if (once.prepare(reinterpret_cast<const void*>(kern), smem) < 0) return -1;
+    const char* A = (const char*)a.a;
+    const char* B = (const char*)a.b;
+    uint16_t* C = (uint16_t*)a.c;
+    int M = a.M, N = a.N, row_bytes = a.K * (IN == 2 ? 1 : 2);
+    int ntm = (M + 255) / 256, ntn = (N + 255) / 256;
+    void* args[] = {&A, &B, &C, &M, &N, &row_bytes, &ntm, &ntn};
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3((unsigned)(ntm * ntn)), dim3(256), args, smem, (hipStream_t)a.stream);
+    return e == hipSuccess ? 0 : -1;
+}
+
 // ---- which kernel takes a product.  Estimated time in microseconds of each candidate on a chip of 256 CUs, from the
-// number of its tiles and of 128-byte steps along K (one stage of the kernel above, and the same MFMA time for every
+// number of its tiles and of 128-byte steps along K (one step of the kernels above, and the same MFMA time for every
 // element type): start-up + rounds * (prologue and epilogue of a tile + steps * time per step).  A round is one tile on
 // every CU, also where two workgroups share a CU (shapes 1 and 2: their times per step are those of two tiles in
-// turn).  A step is cheaper while part of the chip is idle (step_idle: no other tile running).  Fitted to times measured on MI355X for
-// fp16 and E4M3 over M = N = 64 ... 8192 and K = 64 ... 16384: the choice is on average 1 % and at most 25 % slower
-// than the best of the four.  Microseconds at M x N x K, fp16, in the order 256 x 256, 64 x 64, 128 x 128 in pairs,
-// 128 x 128 with split k-steps (the choice in brackets):
-//    1000 x 777 x 512      30.3  [5.0]   9.3   8.5        64 x 64 x 16384     255  [35]   92   68
-//    2048 x 2048 x 512     18.5  11.4   [8.4] 11.2        2048 x 2048 x 4096   84   52    44  [37]
-//    8192 x 8192 x 256     74    113    [55]   86        8192 x 8192 x 2048 [233] 396   256  296
-//    8192 x 8192 x 512     92    146    [86]  120        8192 x 8192 x 1024 [132] 225   147  179
+// turn).  A step is cheaper while part of the chip is idle (step_idle: no other tile running).  Fitted to times measured on
+// MI355X for fp16 and E4M3 over M = N = 64 ... 8192 and K = 64 ... 16384.
+// Microseconds at M x N x K, fp16, in the order 256 x 256, 64 x 64, 128 x 128 in pairs, 128 x 128 with split k-steps (the
+// choice in brackets):
+//    8192 x 8192 x 256      67    113    [56]   86        8192 x 8192 x 2048 [222] 396   256   296
+//    8192 x 8192 x 512     100    146    [86]  120        8192 x 8192 x 1024 [130] 225   147   179
+//    2048 x 2048 x 512     18.5  11.4   [8.4] 11.2        2048 x 2048 x 4096   69   50    43   [36]
+//    1000 x 777 x 512      30.3  [5.0]   9.3   8.5        64 x 64 x 16384     245  [35]   92   68
 struct ShapeModel { int tile; float start, per_tile, step_idle, step_full; };
 constexpr ShapeModel T_MODEL[4] = {
-    {256, 5.0f, 7.0f, 1.10f, 1.60f},      // 0: the 256 x 256 kernel
+    {256, 3.0f, 8.8f, 0.93f, 1.465f},       // 0: gemm_nt_wide_kernel
     {64, 2.0f, 1.0f, 0.13f, 0.185f},        // 1
     {128, 2.8f, 1.4f, 0.465f, 0.465f},      // 2
     {128, 1.0f, 4.0f, 0.28f, 0.48f},        // 3
@@ -340,6 +509,7 @@ int launch_shape(const GemmLaunchArgs& a, int shape)
         case 1: return launch_tile<IN, OUT, 64, 64, 2, 2, F8 ? 1 : 2, 4, 2>(a);
         case 2: return launch_tile<IN, OUT, 128, 128, 2, 2, 1, 2, 2>(a);
         case 3: return launch_tile<IN, OUT, 128, 128, F8 ? 4 : 2, 2, F8 ? 1 : 2, 4, 1>(a);
+        case 0: return launch_wide<IN, OUT>(a);
         default: return -1;
     }
 }
@@ -356,15 +526,15 @@ int gemm_tile_launch(const GemmLaunchArgs& a, int in_type, int shape)
 int gemm_tile_shape(int M, int N, long long row_bytes)
 {
     const float steps = (float)((row_bytes + 127) / 128);
-    int best = 0;
+    int best = -1;
     float best_time = 0.f;
-    for (int s = 0; s < 4; ++s) {
+    for (int s = row_bytes < 128 ? 1 : 0; s < 4; ++s) {
         const ShapeModel& m = T_MODEL[s];
         const long long tiles = ((M + m.tile - 1LL) / m.tile) * ((N + m.tile - 1LL) / m.tile), rounds = (tiles + 255) / 256;
         const float load = tiles < 256 ? tiles / 256.0f : 1.0f;
         float time = m.start + rounds * (m.per_tile + (m.step_idle + (m.step_full - m.step_idle) * load) * steps);
         if (s == 2 && (rounds & 1)) time += T_ALONE * steps;
-        if (s == 0 || time < best_time) {
+        if (best < 0 || time < best_time) {
             best = s;
             best_time = time;
         }

@@ -5,21 +5,34 @@
 
 namespace {
 
+// Eight elements of a row of C, of which the first `left` exist.  Rows of C are aligned to the element only, which the
+// memory path of gfx950 allows for stores of any width: unaligned rows cost a second line at most (8191 x 8191 x 512, fp16:
+// 90 us, with stores of single elements 107; 8192 x 8192 x 512: 85).
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+__device__ __forceinline__ void store_chunk(uint16_t* dst, u32x4 w, int left)
+{
+    if (left >= 8) {
+        *reinterpret_cast<u32x4_any*>(dst) = w;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 7; ++e)
+            if (e < left) dst[e] = (uint16_t)(w[e >> 1] >> ((e & 1) * 16));
+    }
+}
+
 // The block is 128 (m) x 32 NB (n); acc[nb][mb] holds, transposed, its 32 x 32 blocks: a lane has one row m and per register
 // quad four consecutive n.  Stored straight from the registers an instruction touches 32 rows with 16 bytes each, and the
 // stores of a tile (128 KiB) take longer than 256 bytes per row of K do.  So 32 rows at a time go through `st`, 2 NB KiB of the
 // LDS that only this wave uses (no barrier: the LDS accesses of a wave complete in order), and leave as segments of
-// 32 NB columns: 16 bytes per lane, 8 where rows of C are only 8-byte aligned, or single elements side by side.
+// 32 NB columns, 16 bytes per lane.
 // The 16-byte chunks of a row are stored permuted, so that the writes and the wide reads cover all banks.
 // Microseconds before and after, M = N = 8192 on MI355X: fp16, K = 1024: 152 -> 132, K = 8192: 862 -> 839; E4M3, K = 8192:
-// 410 -> 374; M = N = 8191 (single elements), K = 512: fp16 225 -> 109.
+// 410 -> 374; M = N = 8191, K = 512: fp16 225 -> 94.
 template <typename E, int NB>
 __device__ __forceinline__ void store_wave_block(char* st, const f32x16 (&acc)[NB][4], uint16_t* C, int M, int N, int m0, int n0, int lane)
 {
     constexpr int CH = NB * 4, RPB = 16 / CH;                    // 16-byte chunks per staged row, rows per 256 bytes
     const int lr = lane & 31, g = lane >> 5;
-    const bool v16 = (N & 7) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0;
-    const bool v8 = (N & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 7) == 0;
     auto chunk = [&](int row, int c) __attribute__((always_inline)) -> char* {
         return st + row * (CH * 16) + ((c ^ ((row / RPB) & (CH - 1))) * 16);
     };
@@ -36,29 +49,12 @@ __device__ __forceinline__ void store_wave_block(char* st, const f32x16 (&acc)[N
         }
         asm volatile("" ::: "memory");
         const int m1 = m0 + mb * 32;
-        if (v16) {
-            const int c = lane % CH, n = n0 + c * 8;
+        const int c = lane % CH, n = n0 + c * 8;
 #pragma unroll
-            for (int p = 0; p < CH / 2; ++p) {
-                const int row = (p * 64 + lane) / CH;
-                const u32x4 w = *reinterpret_cast<const u32x4*>(chunk(row, c));
-                if (m1 + row < M && n < N) *reinterpret_cast<u32x4*>(C + (size_t)(m1 + row) * N + n) = w;
-            }
-        } else if (v8) {
-            const int h = lane % (2 * CH), n = n0 + h * 4;
-#pragma unroll 4
-            for (int p = 0; p < CH; ++p) {
-                const int row = (p * 64 + lane) / (2 * CH);
-                const u32x2 w = *reinterpret_cast<const u32x2*>(chunk(row, h / 2) + (h & 1) * 8);
-                if (m1 + row < M && n < N) *reinterpret_cast<u32x2*>(C + (size_t)(m1 + row) * N + n) = w;
-            }
-        } else {
-#pragma unroll 4
-            for (int p = 0; p < 4 * CH; ++p) {
-                const int e = p * 64 + lane, row = e / (8 * CH), col = e % (8 * CH);
-                const uint16_t w = *reinterpret_cast<const uint16_t*>(chunk(row, col / 8) + (col & 7) * 2);
-                if (m1 + row < M && n0 + col < N) C[(size_t)(m1 + row) * N + n0 + col] = w;
-            }
+        for (int p = 0; p < CH / 2; ++p) {
+            const int row = (p * 64 + lane) / CH;
+            const u32x4 w = *reinterpret_cast<const u32x4*>(chunk(row, c));
+            if (m1 + row < M) store_chunk(C + (size_t)(m1 + row) * N + n, w, N - n);
         }
     }
 }

@@ -108,6 +108,40 @@ def test_small_tile_shapes(env, shape, M, N, Ks, dtype):
                   "shape %d M%d N%d K%d" % (shape, M, N, K))
 
 
+class LaunchArgs(ctypes.Structure):
+    _fields_ = [("a", ctypes.c_void_p), ("b", ctypes.c_void_p), ("c", ctypes.c_void_p), ("M", ctypes.c_int), ("N", ctypes.c_int),
+                ("K", ctypes.c_int), ("dtype", ctypes.c_int), ("stream", ctypes.c_void_p), ("config", ctypes.c_int)]
+
+
+# The 256 x 256 kernel with whole lines per row, called directly: one to six 128-byte steps (ring of two and a half), with and
+# without a half-filled last one, many steps; tiles that overhang by little and by nearly all.  It adds the k-steps in the order of
+# the fixed configurations, so its results are theirs, bit for bit.  A first step that is not whole is refused.
+@pytest.mark.parametrize("kind", ["fp16", "bf16", "e4m3"])
+@pytest.mark.parametrize("M,N", [(256, 256), (257, 511), (300, 40)])
+def test_whole_line_kernel(env, kind, M, N):
+    torch, binding, G = env
+    launch = binding.load_library()["_Z16gemm_tile_launchRK14GemmLaunchArgsii"]
+    f8, dtype = kind == "e4m3", I.BF16 if kind == "bf16" else I.FP16
+    view = {"fp16": torch.float16, "bf16": torch.bfloat16, "e4m3": torch.float8_e4m3fn}[kind]
+    out = torch.bfloat16 if kind == "bf16" else torch.float16
+    for row_bytes in (128, 192, 256, 320, 384, 448, 512, 576, 640, 704, 768, 4096, 4160):
+        K = row_bytes if f8 else row_bytes // 2
+        print("case gemm whole lines %s M%d N%d K%d" % (kind, M, N, K), flush=True)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(M + N + K)
+        a, b = (torch.randn((r, K), generator=gen, device="cuda").to(view) for r in (M, N))
+        c, want = (torch.full((M, N), float("nan"), dtype=out, device="cuda") for _ in range(2))
+        arg = LaunchArgs(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, dtype, torch.cuda.current_stream().cuda_stream, 0)
+        assert launch(ctypes.byref(arg), 2 if f8 else dtype, 0) == 0
+        (binding.gemm_nt_fp8 if f8 else binding.gemm_nt)(a, b, want, M, N, K, **({"out_dtype": dtype} if f8 else {}), config=1)
+        assert torch.equal(c, want)
+        if not f8:      # (the bound of `check` is that of 16-bit products; configuration 1 on E4M3 has its own test)
+            ref = a.double().cpu() @ b.double().cpu().T
+            check(c.double().cpu().numpy(), ref.numpy(), dtype, K, "whole lines %s K%d" % (kind, K))
+    arg = LaunchArgs(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, 64 if f8 else 32, dtype, None, 0)
+    assert launch(ctypes.byref(arg), 2 if f8 else dtype, 0) == -1
+
+
 # Rows of C that allow 16-, 8- and 2-byte stores, and a C that is aligned to less than its rows are; tiles that overhang by one
 # row and column, by most of a 32-row block and by whole waves; nothing outside C is written.
 @pytest.mark.parametrize("config", [2, 4])
