@@ -487,13 +487,13 @@ int launch_wide(const GemmLaunchArgs& a)
 // MI355X for fp16 and E4M3 over M = N = 64 ... 8192 and K = 64 ... 16384.
 // Microseconds at M x N x K, fp16, in the order 256 x 256, 64 x 64, 128 x 128 in pairs, 128 x 128 with split k-steps (the
 // choice in brackets):
-//    8192 x 8192 x 256      67    113    [56]   86        8192 x 8192 x 2048 [222] 396   256   296
-//    8192 x 8192 x 512     100    146    [86]  120        8192 x 8192 x 1024 [130] 225   147   179
+//    8192 x 8192 x 256      58    113    [56]   83        8192 x 8192 x 2048 [222] 396   256   296
+//    8192 x 8192 x 512     [77]   146     83   103        8192 x 8192 x 1024 [119] 225   134   158
 //    2048 x 2048 x 512     18.5  11.4   [8.4] 11.2        2048 x 2048 x 4096   69   50    43   [36]
 //    1000 x 777 x 512      30.3  [5.0]   9.3   8.5        64 x 64 x 16384     245  [35]   92   68
 struct ShapeModel { int tile; float start, per_tile, step_idle, step_full; };
 constexpr ShapeModel T_MODEL[4] = {
-    {256, 3.0f, 8.8f, 0.93f, 1.465f},       // 0: gemm_nt_wide_kernel
+    {256, 3.0f, 7.8f, 0.93f, 1.465f},       // 0: gemm_nt_wide_kernel
     {64, 2.0f, 1.0f, 0.13f, 0.185f},        // 1
     {128, 2.8f, 1.4f, 0.465f, 0.465f},      // 2
     {128, 1.0f, 4.0f, 0.28f, 0.48f},        // 3

@@ -7,12 +7,16 @@ namespace {
 
 // Eight elements of a row of C, of which the first `left` exist.  Rows of C are aligned to the element only, which the
 // memory path of gfx950 allows for stores of any width: unaligned rows cost a second line at most (8191 x 8191 x 512, fp16:
-// 90 us, with stores of single elements 107; 8192 x 8192 x 512: 85).
+// 90 us, with stores of single elements 107; 8192 x 8192 x 512: 85).  The stores are non-temporal: C is written once and not
+// read here, and its dirty lines otherwise push the operands out of the L2 (8192 x 8192, bf16, three sets of buffers in
+// turn: K = 256 77 -> 56 us, K = 1024 126 -> 119; 4096 x 4096 x 512 with the consumer of C behind it: 36 -> 33.5).  What it
+// costs: a C of 128 MiB that is written again and again by short products no longer stays in the last-level cache (K = 256,
+// one C: 51 -> 56; with a consumer 87 -> 97).
 typedef u32x4 u32x4_any __attribute__((aligned(2)));
 __device__ __forceinline__ void store_chunk(uint16_t* dst, u32x4 w, int left)
 {
     if (left >= 8) {
-        *reinterpret_cast<u32x4_any*>(dst) = w;
+        __builtin_nontemporal_store(w, reinterpret_cast<u32x4_any*>(dst));
     } else {
 #pragma unroll
         for (int e = 0; e < 7; ++e)
