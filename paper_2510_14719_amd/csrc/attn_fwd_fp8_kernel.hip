@@ -587,7 +587,8 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     // a piece of the ring that is private to the wave and leave as whole segments (from the registers an instruction
     // would touch 32 rows with 16 bytes each).  The pieces lie in the slots of the stages nt and nt + 1, which no wave
     // reads and no copy targets any more (with KS = 2 above the exchange area).  A staged row's 16-byte chunks are permuted so that the 8-byte
-    // writes and the 16-byte reads cover all banks.
+    // writes and the 16-byte reads cover all banks.  Non-temporal stores: dirty lines of O would push K and V out of the L2
+    // (4 x 16 heads, N 1024, d 128, causal: 24.6 -> 23.1 us; N 4096: 277 -> 274).
     {
         constexpr int EPI_F = KS == 2 ? D / 2 : (STAGE_BYTES / 256 < D ? STAGE_BYTES / 256 : D);   // features staged at a time
         static_assert(KS == 1 || XBYTES + NW * 32 * EPI_F * 2 <= STAGES * STAGE_BYTES, "above the exchange area");
@@ -619,7 +620,7 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
             for (int p = 0; p < CH / 2; ++p) {  // (the LDS accesses of a wave complete in order)
                 const int row = (p * 64 + el) / CH, c = el % CH;
                 const u32x4 w = *reinterpret_cast<const u32x4*>(es + row * (CH * 16) + ((c ^ ((row / RPC) & (CH - 1))) * 16));
-                if (wq0 + row < N) *reinterpret_cast<u32x4*>(oh + (size_t)(wq0 + row) * D + part * EPI_F + c * 8) = w;
+                if (wq0 + row < N) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(oh + (size_t)(wq0 + row) * D + part * EPI_F + c * 8));
             }
         }
     }

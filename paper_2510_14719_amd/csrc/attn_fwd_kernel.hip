@@ -468,6 +468,8 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // wave (so no barrier), and leave as whole 64- to 256-byte segments.
     // `region`: LDS offset of the wave's piece, 32 rows x F features; a row's 16-byte chunks are stored permuted so that
     // the 8-byte writes and the 16-byte reads cover all banks.
+    // The stores are non-temporal: dirty lines of O would push K and V of the heads in work out of the L2 (16 x 16 heads,
+    // N 1024, d 64, fp16: 84.9 -> 83.0 us, causal 62.7 -> 61.8; long sequences: the same).
     constexpr int EPI_F = NW == 12 ? D / 4 : (PERSIST || KS == 2 ? D / 2 : D);   // features staged at a time
     constexpr int EPI_BYTES = 32 * EPI_F * 2;
     auto epilogue = [&](size_t ep_head_off, int ep_bh, int ep_wq0, unsigned region) __attribute__((always_inline)) {
@@ -498,7 +500,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             for (int p = 0; p < CH / 2; ++p) {                           // (the LDS accesses of a wave complete in order)
                 const int row = (p * 64 + lane) / CH, c = lane % CH;
                 const u32x4 w = *reinterpret_cast<const u32x4*>(st + row * (CH * 16) + ((c ^ ((row / RPB) & (CH - 1))) * 16));
-                if (row0 + row < N) *reinterpret_cast<u32x4*>(oh + (size_t)(row0 + row) * D + part * EPI_F + c * 8) = w;
+                if (row0 + row < N) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(oh + (size_t)(row0 + row) * D + part * EPI_F + c * 8));
             }
         }
     }
