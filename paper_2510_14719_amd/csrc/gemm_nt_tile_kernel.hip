@@ -36,7 +36,6 @@ namespace {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int T_GROUP_M = 8;                    // tile rows per raster group: see tile_coords in gemm_nt_kernel.hip
 
@@ -307,8 +306,13 @@ int launch_tile(const GemmLaunchArgs& a)
 // split that reads least from the LDS: 128 KiB per 128-byte step along K, next to 64 KiB of copies written; the MFMAs of
 // a step take 2048 cycles), accumulators in the AGPRs.
 //
+// What bounds a full chip here is power: on operands of zeros a 8192 x 8192 x 8192 product takes two thirds of the time.
+// 16-bit operands therefore take the 16 x 16 x 32 MFMA: per flop it reads its operands twice as often as the 32 x 32 x 16 one
+// but moves half as much of the fp32 accumulators (the same product, bf16: 761 -> 697 us, although zeros take longer, 503 ->
+// 535).  E4M3 operands keep 32 x 32 x 64, where both come out alike and 16 x 16 fragments would not fit the registers.
+//
 // A step's rows are whole 128-byte lines (layout of the small-tile kernel), so one copy instruction asks the L2 for 8 lines
-// and copies can be spread evenly: one behind every fourth 32-cycle MFMA.  (Issued in bursts they fill the CU's
+// and copies can be spread evenly: one per 128 cycles of MFMAs.  (Issued in bursts they fill the CU's
 // address path, 16 cycles per copy, and the waves that queue for it cannot issue their MFMAs.)
 //
 // Ring of five 32 KiB slots for the sequence A_0 B_0 A_1 B_1 A_2 ...: A_j and B_j are the operand tiles of step j.
@@ -321,18 +325,20 @@ void gemm_nt_wide_kernel(const char* __restrict__ A, const char* __restrict__ B,
                          int M, int N, int row_bytes, int ntm, int ntn)
 {
     typedef Elem<OUT> E;
-    constexpr int KSTEPS = IN == 2 ? 2 : 4, HALVES = IN == 2 ? 2 : 1;
+    constexpr bool B16 = IN != 2;               // 16 x 16 x 32 MFMAs; E4M3: 32 x 32 x 64
+    constexpr int KSTEPS = 2, HALVES = IN == 2 ? 2 : 1;          // a k-step is 64 bytes of every row
+    constexpr int BS = B16 ? 16 : 32, NB = 128 / BS;             // block size, blocks of each operand per wave
     constexpr int SLOT = 256 * 128, SLOTS = 5;
     constexpr int PPW = 8;                      // copies per wave and operand tile
-    constexpr int READS = 8 * HALVES;           // fragment reads per k-step: 4 blocks of each operand
-    constexpr int SPAN = 16 * KSTEPS;           // MFMAs between two barriers
+    constexpr int READS = 2 * NB * HALVES;      // fragment reads per k-step
+    constexpr int READ_EVERY = B16 ? 2 : 1;     // MFMAs per read
+    constexpr int SPAN = NB * NB * KSTEPS;      // MFMAs between two barriers
     constexpr int COPY_EVERY = SPAN / (2 * PPW);
 
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const unsigned lds_base = (unsigned)(size_t)(LDS_AS void*)smem;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    const int lr = lane & 31, g = lane >> 5;
     const int wm = wave & 1, wn = wave >> 1;
 
     int tm, tn;
@@ -355,46 +361,50 @@ void gemm_nt_wide_kernel(const char* __restrict__ A, const char* __restrict__ B,
         dma16(mat + (size_t)s * 128, o, lds_base + slot * SLOT + (wave * PPW + i) * 1024);
     };
 
-    // ---- fragments of k-step k, in the order of use (MFMA q of a k-step multiplies block q / 4 of A with block q % 4 of B)
-    struct Frags { TileFrag<IN> am[4], bn[4]; };
+    // ---- fragments of k-step k, in the order of use (MFMA q of a k-step multiplies block q / NB of A with block q % NB of B)
+    struct Frags { TileFrag<IN> am[NB], bn[NB]; };
     auto read_one = [&](Frags& f, int k, int slot_a, int slot_b, int i) __attribute__((always_inline)) {
         const int r = i / HALVES, h = i % HALVES;
-        const int col = IN == 2 ? k * 4 + g * 2 + h : k * 2 + g;
-        const int off = lr * 128 + ((col ^ ((lr >> 1) & 7)) * 16);
-        const bool is_a = r == 1 || r > 4;
-        const int blk = r == 0 || r == 1 ? 0 : (r <= 4 ? r - 1 : r - 4);
-        if (is_a) f.am[blk].h[h] = *reinterpret_cast<const i32x4*>(smem + slot_a * SLOT + wm * 16384 + off + blk * 4096);
-        else f.bn[blk].h[h] = *reinterpret_cast<const i32x4*>(smem + slot_b * SLOT + wn * 16384 + off + blk * 4096);
+        const int row = lane % BS, col = B16 ? k * 4 + (lane >> 4) : k * 4 + (lane >> 5) * 2 + h;
+        const int off = row * 128 + ((col ^ ((row >> 1) & 7)) * 16);
+        const bool is_a = r == 1 || r > NB;
+        const int blk = r == 0 || r == 1 ? 0 : (r <= NB ? r - 1 : r - NB);
+        if (is_a) f.am[blk].h[h] = *reinterpret_cast<const i32x4*>(smem + slot_a * SLOT + wm * 16384 + off + blk * (BS * 128));
+        else f.bn[blk].h[h] = *reinterpret_cast<const i32x4*>(smem + slot_b * SLOT + wn * 16384 + off + blk * (BS * 128));
     };
 
-    f32x16 acc[4][4];
+    typedef typename std::conditional<B16, f32x4, f32x16>::type block_t;
+    block_t acc[NB][NB];
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) acc[nb][mb] = f32x16(0.f);
+        for (int mb = 0; mb < NB; ++mb) acc[nb][mb] = block_t(0.f);
 
     typedef std::integral_constant<bool, true> yes_t;
     typedef std::integral_constant<bool, false> no_t;
     auto next_slot = [](int s, int by) __attribute__((always_inline)) { s += by; return s >= SLOTS ? s - SLOTS : s; };
 
-    // ---- one k-step: 16 MFMAs on `cur` (unless `skip`: the missing half of a half step); between them the reads of the
+    // ---- one k-step: the MFMAs on `cur` (unless `skip`: the missing half of a half step); between them the reads of the
     // next k-step's fragments (while read_next) and whatever `behind(q)` issues
     auto kstep = [&](const Frags& cur, Frags& nxt, int next_k, int slot_a, int slot_b, bool skip, bool read_next, auto behind) __attribute__((always_inline)) {
+        auto between = [&](int q) __attribute__((always_inline)) {
+            if (q % READ_EVERY == 0 && q / READ_EVERY < READS && read_next) read_one(nxt, next_k, slot_a, slot_b, q / READ_EVERY);
+            behind(q);
+        };
         if (skip) {
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                if (q < READS && read_next) read_one(nxt, next_k, slot_a, slot_b, q);
-                behind(q);
-            }
+            for (int q = 0; q < NB * NB; ++q) between(q);
             return;
         }
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int mb = q / 4, nb = q % 4;
-            acc[nb][mb] = tile_mfma<IN>(cur.bn[nb], cur.am[mb], acc[nb][mb]);
+        for (int q = 0; q < NB * NB; ++q) {
+            const int mb = q / NB, nb = q % NB;
+            if constexpr (B16)
+                acc[nb][mb] = Elem<IN>::mfma16(__builtin_bit_cast(s16x8, cur.bn[nb].h[0]), __builtin_bit_cast(s16x8, cur.am[mb].h[0]), acc[nb][mb]);
+            else
+                acc[nb][mb] = tile_mfma<IN>(cur.bn[nb], cur.am[mb], acc[nb][mb]);
             __builtin_amdgcn_sched_barrier(0);
-            if (q < READS && read_next) read_one(nxt, next_k, slot_a, slot_b, q);
-            behind(q);
+            between(q);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -435,7 +445,7 @@ void gemm_nt_wide_kernel(const char* __restrict__ A, const char* __restrict__ B,
 #pragma unroll
         for (int k0 = 0; k0 < KSTEPS; ++k0) {   // k-step k0 of the span reads the fragments of k-step k0 of step p + 1
             kstep(k0 & 1 ? X : Y, k0 & 1 ? Y : X, k0, sa, sb, half && k0 - 1 >= KSTEPS / 2, true, [&](int q) __attribute__((always_inline)) {
-                const int slot = k0 * 16 + q;
+                const int slot = k0 * NB * NB + q;
                 if (slot % COPY_EVERY != COPY_EVERY - 1) return;
                 const int i = slot / COPY_EVERY;
                 if (i < PPW) {
@@ -458,7 +468,8 @@ void gemm_nt_wide_kernel(const char* __restrict__ A, const char* __restrict__ B,
     __builtin_amdgcn_s_waitcnt(0xC07F);
     ring_barrier();
     kstep(Y, X, 0, 0, 0, nk > nfull, false, nothing);
-    store_wave_block<E, 4>(smem + wave * 8192, acc, C, M, N, m0 + wm * 128, n0 + wn * 128, lane);
+    if constexpr (B16) store_wave_block<E>(smem + wave * 8192, acc, C, M, N, m0 + wm * 128, n0 + wn * 128, lane);
+    else store_wave_block<E, 4>(smem + wave * 8192, acc, C, M, N, m0 + wm * 128, n0 + wn * 128, lane);
 }
 
 template <int IN, int OUT>
@@ -487,13 +498,13 @@ int launch_wide(const GemmLaunchArgs& a)
 // MI355X for fp16 and E4M3 over M = N = 64 ... 8192 and K = 64 ... 16384.
 // Microseconds at M x N x K, fp16, in the order 256 x 256, 64 x 64, 128 x 128 in pairs, 128 x 128 with split k-steps (the
 // choice in brackets):
-//    8192 x 8192 x 256      58    113    [56]   83        8192 x 8192 x 2048 [222] 396   256   296
+//    8192 x 8192 x 256      58    113    [56]   83        8192 x 8192 x 2048 [200] 396   256   296
 //    8192 x 8192 x 512     [77]   146     83   103        8192 x 8192 x 1024 [119] 225   134   158
 //    2048 x 2048 x 512     18.5  11.4   [8.4] 11.2        2048 x 2048 x 4096   69   50    43   [36]
 //    1000 x 777 x 512      30.3  [5.0]   9.3   8.5        64 x 64 x 16384     245  [35]   92   68
 struct ShapeModel { int tile; float start, per_tile, step_idle, step_full; };
 constexpr ShapeModel T_MODEL[4] = {
-    {256, 3.0f, 7.8f, 0.93f, 1.465f},       // 0: gemm_nt_wide_kernel
+    {256, 3.0f, 7.8f, 0.95f, 1.30f},       // 0: gemm_nt_wide_kernel
     {64, 2.0f, 1.0f, 0.13f, 0.185f},        // 1
     {128, 2.8f, 1.4f, 0.465f, 0.465f},      // 2
     {128, 1.0f, 4.0f, 0.28f, 0.48f},        // 3

@@ -32,34 +32,61 @@ __device__ __forceinline__ void store_chunk(uint16_t* dst, u32x4 w, int left)
 // The 16-byte chunks of a row are stored permuted, so that the writes and the wide reads cover all banks.
 // Microseconds before and after, M = N = 8192 on MI355X: fp16, K = 1024: 152 -> 132, K = 8192: 862 -> 839; E4M3, K = 8192:
 // 410 -> 374; M = N = 8191, K = 512: fp16 225 -> 94.
+template <int CH>       // 16-byte chunks per staged row
+__device__ __forceinline__ char* staged_chunk(char* st, int row, int c)
+{
+    constexpr int RPB = 16 / CH;                // rows per 256 bytes
+    return st + row * (CH * 16) + ((c ^ ((row / RPB) & (CH - 1))) * 16);
+}
+
+// The 32 staged rows from row m1 of C on, columns from n0 on.
+template <int CH>
+__device__ __forceinline__ void store_staged_rows(char* st, uint16_t* C, int M, int N, int m1, int n0, int lane)
+{
+    asm volatile("" ::: "memory");              // (another lane's elements are read: keep the order of the LDS accesses)
+    const int c = lane % CH, n = n0 + c * 8;
+#pragma unroll
+    for (int p = 0; p < CH / 2; ++p) {
+        const int row = (p * 64 + lane) / CH;
+        const u32x4 w = *reinterpret_cast<const u32x4*>(staged_chunk<CH>(st, row, c));
+        if (m1 + row < M) store_chunk(C + (size_t)(m1 + row) * N + n, w, N - n);
+    }
+    asm volatile("" ::: "memory");
+}
+
 template <typename E, int NB>
 __device__ __forceinline__ void store_wave_block(char* st, const f32x16 (&acc)[NB][4], uint16_t* C, int M, int N, int m0, int n0, int lane)
 {
-    constexpr int CH = NB * 4, RPB = 16 / CH;                    // 16-byte chunks per staged row, rows per 256 bytes
     const int lr = lane & 31, g = lane >> 5;
-    auto chunk = [&](int row, int c) __attribute__((always_inline)) -> char* {
-        return st + row * (CH * 16) + ((c ^ ((row / RPB) & (CH - 1))) * 16);
-    };
 #pragma unroll
     for (int mb = 0; mb < 4; ++mb) {
-        asm volatile("" ::: "memory");          // (another lane's elements are read: keep the order of the LDS accesses)
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
+        for (int c = 0; c < NB * 4; ++c) {
             const f32x16& x = acc[c / 4][mb];
             u32x2 w;
             w[0] = E::pack2(x[c % 4 * 4 + 0], x[c % 4 * 4 + 1]);
             w[1] = E::pack2(x[c % 4 * 4 + 2], x[c % 4 * 4 + 3]);
-            *reinterpret_cast<u32x2*>(chunk(lr, c) + g * 8) = w;
+            *reinterpret_cast<u32x2*>(staged_chunk<NB * 4>(st, lr, c) + g * 8) = w;
         }
-        asm volatile("" ::: "memory");
-        const int m1 = m0 + mb * 32;
-        const int c = lane % CH, n = n0 + c * 8;
+        store_staged_rows<NB * 4>(st, C, M, N, m0 + mb * 32, n0, lane);
+    }
+}
+
+// The same for a 128 x 128 block held as 16 x 16 blocks acc[nb][mb] (lane: row lane % 16, four n from 4 (lane / 16) on).
+template <typename E>
+__device__ __forceinline__ void store_wave_block(char* st, const f32x4 (&acc)[8][8], uint16_t* C, int M, int N, int m0, int n0, int lane)
+{
 #pragma unroll
-        for (int p = 0; p < CH / 2; ++p) {
-            const int row = (p * 64 + lane) / CH;
-            const u32x4 w = *reinterpret_cast<const u32x4*>(chunk(row, c));
-            if (m1 + row < M) store_chunk(C + (size_t)(m1 + row) * N + n, w, N - n);
+    for (int mb = 0; mb < 8; ++mb) {
+#pragma unroll
+        for (int nb = 0; nb < 8; ++nb) {
+            const f32x4& x = acc[nb][mb];
+            u32x2 w;
+            w[0] = E::pack2(x[0], x[1]);
+            w[1] = E::pack2(x[2], x[3]);
+            *reinterpret_cast<u32x2*>(staged_chunk<16>(st, (mb & 1) * 16 + (lane & 15), nb * 2 + (lane >> 5)) + ((lane >> 4) & 1) * 8) = w;
         }
+        if (mb & 1) store_staged_rows<16>(st, C, M, N, m0 + (mb - 1) * 16, n0, lane);
     }
 }
 

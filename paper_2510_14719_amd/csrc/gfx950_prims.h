@@ -8,6 +8,7 @@
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -23,6 +24,9 @@ template <> struct Elem<0> {  // IEEE binary16
     typedef _Float16 v2 __attribute__((ext_vector_type(2)));
     static __device__ __forceinline__ f32x16 mfma(s16x8 a, s16x8 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ f32x4 mfma16(s16x8 a, s16x8 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
     }
     static __device__ __forceinline__ unsigned pack2(float lo, float hi) {
         f32x2 x = {lo, hi};
@@ -47,6 +51,9 @@ template <> struct Elem<1> {  // bfloat16
     typedef __bf16 v2 __attribute__((ext_vector_type(2)));
     static __device__ __forceinline__ f32x16 mfma(s16x8 a, s16x8 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ f32x4 mfma16(s16x8 a, s16x8 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
     }
     static __device__ __forceinline__ unsigned pack2(float lo, float hi) {
         f32x2 x = {lo, hi};

@@ -114,8 +114,9 @@ class LaunchArgs(ctypes.Structure):
 
 
 # The 256 x 256 kernel with whole lines per row, called directly: one to six 128-byte steps (ring of two and a half), with and
-# without a half-filled last one, many steps; tiles that overhang by little and by nearly all.  It adds the k-steps in the order of
-# the fixed configurations, so its results are theirs, bit for bit.  A first step that is not whole is refused.
+# without a half-filled last one, many steps; tiles that overhang by little and by nearly all.  On E4M3 it
+# adds the k-steps in the order of the fixed configurations, so its results are theirs, bit for bit (16-bit operands take
+# MFMAs of another shape).  A first step that is not whole is refused.
 @pytest.mark.parametrize("kind", ["fp16", "bf16", "e4m3"])
 @pytest.mark.parametrize("M,N", [(256, 256), (257, 511), (300, 40)])
 def test_whole_line_kernel(env, kind, M, N):
@@ -133,9 +134,10 @@ def test_whole_line_kernel(env, kind, M, N):
         c, want = (torch.full((M, N), float("nan"), dtype=out, device="cuda") for _ in range(2))
         arg = LaunchArgs(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, dtype, torch.cuda.current_stream().cuda_stream, 0)
         assert launch(ctypes.byref(arg), 2 if f8 else dtype, 0) == 0
-        (binding.gemm_nt_fp8 if f8 else binding.gemm_nt)(a, b, want, M, N, K, **({"out_dtype": dtype} if f8 else {}), config=1)
-        assert torch.equal(c, want)
-        if not f8:      # (the bound of `check` is that of 16-bit products; configuration 1 on E4M3 has its own test)
+        if f8:
+            binding.gemm_nt_fp8(a, b, want, M, N, K, out_dtype=dtype, config=1)
+            assert torch.equal(c, want)
+        else:
             ref = a.double().cpu() @ b.double().cpu().T
             check(c.double().cpu().numpy(), ref.numpy(), dtype, K, "whole lines %s K%d" % (kind, K))
     arg = LaunchArgs(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, 64 if f8 else 32, dtype, None, 0)
