@@ -495,21 +495,22 @@ int launch_wide(const GemmLaunchArgs& a)
 // element type): start-up + rounds * (prologue and epilogue of a tile + steps * time per step).  A round is one tile on
 // every CU, also where two workgroups share a CU (shapes 1 and 2: their times per step are those of two tiles in
 // turn).  A step is cheaper while part of the chip is idle (step_idle: no other tile running).  Fitted to times measured on
-// MI355X for fp16 and E4M3 over M = N = 64 ... 8192 and K = 64 ... 16384.
-// Microseconds at M x N x K, fp16, in the order 256 x 256, 64 x 64, 128 x 128 in pairs, 128 x 128 with split k-steps (the
+// MI355X, three sets of buffers in turn, for bf16 and E4M3 over M, N = 64 ... 8192 and K = 64 ... 16384.
+// Microseconds at M x N x K, bf16, in the order 256 x 256, 64 x 64, 128 x 128 in pairs, 128 x 128 with split k-steps (the
 // choice in brackets):
-//    8192 x 8192 x 256      58    113    [56]   83        8192 x 8192 x 2048 [200] 396   256   296
-//    8192 x 8192 x 512     [77]   146     83   103        8192 x 8192 x 1024 [119] 225   134   158
-//    2048 x 2048 x 512     18.5  11.4   [8.4] 11.2        2048 x 2048 x 4096   69   50    43   [36]
-//    1000 x 777 x 512      30.3  [5.0]   9.3   8.5        64 x 64 x 16384     245  [35]   92   68
+//    8192 x 8192 x 256      60    105    [56]   83        8192 x 8192 x 2048 [198] 377   239   278
+//    8192 x 8192 x 512     [81]   137     83   107        4096 x 4096 x 256  [13.9] 28.3  16.5 22.6
+//    3000 x 3000 x 256     13.1  17.6  [13.4] 17.1        3000 x 3000 x 512  [17.0] 21.8  18.8 22.1
+//    2048 x 2048 x 256     11.2   8.6   [6.3]  7.1        2048 x 2048 x 4096   70    50    41  [32]
+//    1000 x 777 x 512      30    [5.0]   9.3   8.5        64 x 64 x 16384     245   [35]   92   68
 struct ShapeModel { int tile; float start, per_tile, step_idle, step_full; };
 constexpr ShapeModel T_MODEL[4] = {
-    {256, 3.0f, 7.8f, 0.95f, 1.30f},       // 0: gemm_nt_wide_kernel
+    {256, 1.5f, 8.5f, 0.95f, 1.30f},        // 0: gemm_nt_wide_kernel
     {64, 2.0f, 1.0f, 0.13f, 0.185f},        // 1
-    {128, 2.8f, 1.4f, 0.465f, 0.465f},      // 2
-    {128, 1.0f, 4.0f, 0.28f, 0.48f},        // 3
+    {128, 3.5f, 1.6f, 0.41f, 0.41f},        // 2
+    {128, 1.0f, 4.5f, 0.28f, 0.48f},        // 3
 };
-constexpr float T_ALONE = 0.09f;            // shape 2: what a step costs more in a round without a partner
+constexpr float T_ALONE = 0.13f;            // shape 2: what a step costs more in a round without a partner
 
 template <int IN, int OUT>
 int launch_shape(const GemmLaunchArgs& a, int shape)
