@@ -384,7 +384,7 @@ void gemm_nt_wide_kernel(const char* __restrict__ A, const char* __restrict__ B,
     typedef std::integral_constant<bool, false> no_t;
     auto next_slot = [](int s, int by) __attribute__((always_inline)) { s += by; return s >= SLOTS ? s - SLOTS : s; };
 
-    // ---- one k-step: the MFMAs on `cur` (unless `skip`: the missing half of a half step); between them the reads of the
+    // ---- one k-step: the MFMAs on `cur` (unless `skip`: the missing k-step of a half step, the very last one); between them the reads of the
     // next k-step's fragments (while read_next) and whatever `behind(q)` issues
     auto kstep = [&](const Frags& cur, Frags& nxt, int next_k, int slot_a, int slot_b, bool skip, bool read_next, auto behind) __attribute__((always_inline)) {
         auto between = [&](int q) __attribute__((always_inline)) {
@@ -441,10 +441,9 @@ void gemm_nt_wide_kernel(const char* __restrict__ A, const char* __restrict__ B,
         const int free_a = sa, free_b = next_slot(sa, 1);
         sa = next_slot(sa, 2);
         const int sb = next_slot(sa, 1);
-        const bool half = !STEADY && p + 1 >= nfull;
 #pragma unroll
         for (int k0 = 0; k0 < KSTEPS; ++k0) {   // k-step k0 of the span reads the fragments of k-step k0 of step p + 1
-            kstep(k0 & 1 ? X : Y, k0 & 1 ? Y : X, k0, sa, sb, half && k0 - 1 >= KSTEPS / 2, true, [&](int q) __attribute__((always_inline)) {
+            kstep(k0 & 1 ? X : Y, k0 & 1 ? Y : X, k0, sa, sb, false, true, [&](int q) __attribute__((always_inline)) {
                 const int slot = k0 * NB * NB + q;
                 if (slot % COPY_EVERY != COPY_EVERY - 1) return;
                 const int i = slot / COPY_EVERY;
