@@ -145,7 +145,7 @@ template <int DTYPE, int D, int NW, int MB, int BN, int STAGES, bool CAUSAL, boo
 __global__ __launch_bounds__(NW * 64, (D == 64 && ATTN_D64_TWO_WG) ? 4 : 1)
 void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                      uint16_t* __restrict__ o, float* __restrict__ lse, int N, int nqt, int total,
-                     float scale, float scale_log2e)
+                     float scale, float scale_log2e, float m_none)
 {
     typedef Elem<DTYPE> E;
     constexpr int BM = NW * MB * 32 / KS;       // query rows per workgroup
@@ -512,7 +512,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // slots that hold neither a stage still being read (nt - 1, or nt - 2) nor one being filled: slot 2 under the next
     // prologue (stages -1, 0, 1), else those of the stages nt and nt + 1, which no copy targets; with KS = 2 above the exchange area.
     // ---- KS = 2: O, row sum and reference of this wave become those of all keys, for the half of the features that it
-    // stores.  The reference of a wave without any visible key is -inf and weighs 0.
+    // stores.  The reference of a wave without any visible key is m_none, its sums are 0.
     auto merge_groups = [&](auto upper) __attribute__((always_inline)) {
         constexpr int SEND = decltype(upper)::value ? 0 : DB / 2, KEEP = DB / 2 - SEND;   // feature blocks
         constexpr int FLOATS = DB / 2 * 16 + 2;
@@ -597,7 +597,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     wait_vmcnt<0>();
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-        m_run[mb] = -__builtin_inff();
+        m_run[mb] = m_none;                     // (see launch)
         l_run[mb] = 0.f;
 #pragma unroll
         for (int db = 0; db < DB; ++db) O[mb][db] = f32x16(0.f);
@@ -775,7 +775,11 @@ int launch(const AttnLaunchArgs& a)
     float* lse = a.lse;
     int N = a.N, nqt_arg = nqt, total_arg = (int)total;
     float scale = a.scale, scale_log2e = a.scale * log2e;
-    void* args[] = {&q, &k, &v, &o, &lse, &N, &nqt_arg, &total_arg, &scale, &scale_log2e};
+    // The softmax reference before the first finite score.  Not -inf: where the first keys that a wave works on all score
+    // -inf, (-inf) - (-inf) would turn the row into NaN.  The most negative float whose scaled value is finite gives those
+    // keys the weight exp2(-inf) = 0 and moves to the first finite score.
+    float m_none = scale_log2e > 1.f ? -0x1.fffff0p127f / scale_log2e : -__FLT_MAX__;
+    void* args[] = {&q, &k, &v, &o, &lse, &N, &nqt_arg, &total_arg, &scale, &scale_log2e, &m_none};
     // the launch's own status, not hipGetLastError(): that one also reports stale errors of unrelated calls
     const hipError_t e = hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3((unsigned)grid), dim3(NW * 64),
                                          args, smem, (hipStream_t)a.stream);

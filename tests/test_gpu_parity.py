@@ -143,6 +143,30 @@ def test_zero_q_gives_running_mean(G, oracle, causal):
     G.check(o, l, o_ref, l_ref, "zero-q", tol_lse=1e-4)
 
 
+# Keys that score -inf for every query (an infinite element, or a product beyond the range of fp32) weigh nothing, wherever
+# they lie: the first keys of a row, the first or second half of its first tile (the shares of the two wave groups in the
+# form for few tiles), whole tiles.  Rows that see no other key have no defined result and are left out.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,N", [(2, 333), (300, 300)])
+@pytest.mark.parametrize("dtype,low", [(I.FP16, -np.inf), (I.BF16, -3e38)])
+def test_keys_that_score_minus_infinity(G, oracle, dtype, low, H, N, d, causal):
+    for first, last in ((0, 32), (32, 64), (0, 64), (0, 128), (64, 192)):
+        q, k, v = I.make_qkv(1, H, N, d, dtype, 2100 + first + last)
+        four, bad = I.to_bits(np.array([4.0, low], dtype=np.float32), dtype)
+        q[..., 0] = four
+        k[..., 0] = 0
+        k[:, :, first:last, 0] = bad
+        print("case -inf keys %d..%d H%d N%d d%d causal%d dtype%d" % (first, last, H, N, d, causal, dtype), flush=True)
+        o, l = G.run_gpu(q, k, v, dtype, 1.0 / math.sqrt(d), causal)
+        rows = np.arange(last if causal and first == 0 else 0, N)
+        for h in (0, H - 1):
+            sl = (slice(0, 1), slice(h, h + 1))
+            o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]),
+                                           dtype, 1.0 / math.sqrt(d), causal)
+            G.check(o[sl][:, :, rows], l[sl][:, :, rows], o_ref[:, :, rows], l_ref[:, :, rows], "-inf keys %d..%d head %d" % (first, last, h))
+
+
 @pytest.mark.parametrize("dtype", [I.FP16, I.BF16])
 def test_large_scores_exercise_rescaling(G, oracle, dtype):
     # scores with |s| up to ~60 and a maximum that keeps moving along the key axis
