@@ -590,8 +590,10 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     // a piece of the ring that is private to the wave and leave as whole segments (from the registers an instruction
     // would touch 32 rows with 16 bytes each).  The pieces lie in the slots of the stages nt and nt + 1, which no wave
     // reads and no copy targets any more (with KS = 2 above the exchange area).  A staged row's 16-byte chunks are permuted so that the 8-byte
-    // writes and the 16-byte reads cover all banks.  Non-temporal stores: dirty lines of O would push K and V out of the L2
-    // (4 x 16 heads, N 1024, d 128, causal: 24.6 -> 23.1 us; N 4096: 277 -> 274).
+    // writes and the 16-byte reads cover all banks.  O is written through the L2 unless it is small (store_through; ordinary stores /
+    // written through / past the caches, us: 4 x 16 heads, N 1024, d 128, causal 24.7 / 23.5 / 23.5, with an elementwise kernel that
+    // reads O behind it 32.1 / 31.0 / 31.7, with a product 37.9 / 37.0 / 37.4; 64 heads, N 1024, d 64 17.8 / 17.1 / 17.4, elementwise
+    // 22.4 / 21.7 / 22.3; 2048 heads, N 256, d 64 59.2 / 61.6 / 62.8; small: 8 heads, N 256, d 128, causal 10.7 / 11.3 / 10.7).
     // A wave whose rows all lie beyond the sequence has nothing to store and stays out of the LDS, which the others would
     // share with it (N 64, d 128, 200 heads: 5.85 -> 5.62 us, N 100, d 64, 300 heads, causal: 9.37 -> 9.03).
     if (wq0 < N) {
@@ -621,12 +623,19 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
                 *reinterpret_cast<u32x2*>(es + er * (CH * 16) + ((c ^ ((er / RPC) & (CH - 1))) * 16) + eg * 8) = w;
             }
             asm volatile("" ::: "memory");
+            auto rows_out = [&](auto through) __attribute__((always_inline)) {
 #pragma unroll
-            for (int p = 0; p < CH / 2; ++p) {  // (the LDS accesses of a wave complete in order)
-                const int row = (p * 64 + el) / CH, c = el % CH;
-                const u32x4 w = *reinterpret_cast<const u32x4*>(es + row * (CH * 16) + ((c ^ ((row / RPC) & (CH - 1))) * 16));
-                if (wq0 + row < N) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(oh + (size_t)(wq0 + row) * D + part * EPI_F + c * 8));
-            }
+                for (int p = 0; p < CH / 2; ++p) {  // (the LDS accesses of a wave complete in order)
+                    const int row = (p * 64 + el) / CH, c = el % CH;
+                    const u32x4 w = *reinterpret_cast<const u32x4*>(es + row * (CH * 16) + ((c ^ ((row / RPC) & (CH - 1))) * 16));
+                    uint16_t* dst = oh + (size_t)(wq0 + row) * D + part * EPI_F + c * 8;
+                    if (wq0 + row < N) {
+                        if (decltype(through)::value) store_through(dst, w);
+                        else *reinterpret_cast<u32x4*>(dst) = w;
+                    }
+                }
+            };
+            if (total > SMALL_RESULT / (BM * D * 2)) rows_out(std::true_type{}); else rows_out(std::false_type{});
         }
     }
     if (!PERSIST) break;

@@ -468,8 +468,10 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // wave (so no barrier), and leave as whole 64- to 256-byte segments.
     // `region`: LDS offset of the wave's piece, 32 rows x F features; a row's 16-byte chunks are stored permuted so that
     // the 8-byte writes and the 16-byte reads cover all banks.
-    // The stores are non-temporal: dirty lines of O would push K and V of the heads in work out of the L2 (16 x 16 heads,
-    // N 1024, d 64, fp16: 84.9 -> 83.0 us, causal 62.7 -> 61.8; long sequences: the same).
+    // O is written through the L2 unless it is small (store_through; with KS = 1 it never is).  Ordinary stores / written through / past the caches, several
+    // sets of buffers in turn, us: 512 heads, N 256, d 64 18.0 / 16.7 / 16.7, with an elementwise kernel that reads O behind
+    // it 25.7 / 24.2 / 24.9, with a product 39.9 / 38.5 / 39.6; 64 heads, N 512, d 128, causal 15.2 / 14.3 / 14.4, elementwise 19.8 / 18.8 / 19.2;
+    // 256 heads, N 1024, d 64 89.1 / 87.9 / 87.9, 98.6 / 97.5 / 98.3, 104.9 / 103.9 / 108.8.  Small: 8 heads, N 256, d 64 6.89 / 7.15 / 6.89.
     constexpr int EPI_F = NW == 12 ? D / 4 : (PERSIST || KS == 2 ? D / 2 : D);   // features staged at a time
     constexpr int EPI_BYTES = 32 * EPI_F * 2;
     auto epilogue = [&](size_t ep_head_off, int ep_bh, int ep_wq0, unsigned region) __attribute__((always_inline)) {
@@ -496,12 +498,19 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                 *reinterpret_cast<u32x2*>(st + lr * (CH * 16) + ((c ^ ((lr / RPB) & (CH - 1))) * 16) + g * 8) = w;
             }
             asm volatile("" ::: "memory");
+            auto rows_out = [&](auto through) __attribute__((always_inline)) {
 #pragma unroll
-            for (int p = 0; p < CH / 2; ++p) {                           // (the LDS accesses of a wave complete in order)
-                const int row = (p * 64 + lane) / CH, c = lane % CH;
-                const u32x4 w = *reinterpret_cast<const u32x4*>(st + row * (CH * 16) + ((c ^ ((row / RPB) & (CH - 1))) * 16));
-                if (row0 + row < N) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(oh + (size_t)(row0 + row) * D + part * EPI_F + c * 8));
-            }
+                for (int p = 0; p < CH / 2; ++p) {                       // (the LDS accesses of a wave complete in order)
+                    const int row = (p * 64 + lane) / CH, c = lane % CH;
+                    const u32x4 w = *reinterpret_cast<const u32x4*>(st + row * (CH * 16) + ((c ^ ((row / RPB) & (CH - 1))) * 16));
+                    uint16_t* dst = oh + (size_t)(row0 + row) * D + part * EPI_F + c * 8;
+                    if (row0 + row < N) {
+                        if (decltype(through)::value) store_through(dst, w);
+                        else *reinterpret_cast<u32x4*>(dst) = w;
+                    }
+                }
+            };
+            if (KS == 1 || total > SMALL_RESULT / (BM * D * 2)) rows_out(std::true_type{}); else rows_out(std::false_type{});
         }
     }
     };

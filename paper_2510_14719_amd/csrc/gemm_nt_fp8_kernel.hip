@@ -330,7 +330,7 @@ void gemm_nt_fp8_kernel(const uint8_t* __restrict__ A, const uint8_t* __restrict
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    store_wave_block<E, H_NB>(smem + wave * (H_NB * 2048), acc, C, M, N, m0 + wm * 128, n0 + wn * (H_NB * 32), lane);
+    store_wave_block_of<E>(smem + wave * (H_NB * 2048), acc, C, M, N, m0 + wm * 128, n0 + wn * (H_NB * 32), lane);
 }
 
 template <int OUT, int NW, bool PAIRED>

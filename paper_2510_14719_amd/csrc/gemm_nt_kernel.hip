@@ -361,7 +361,7 @@ void gemm_nt_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    store_wave_block<E, G_NB>(smem + wave * (G_NB * 2048), acc, C, M, N, m0 + wm * 128, n0 + wn * (G_NB * 32), lane);
+    store_wave_block_of<E>(smem + wave * (G_NB * 2048), acc, C, M, N, m0 + wm * 128, n0 + wn * (G_NB * 32), lane);
 }
 
 template <int DTYPE, int NW, bool PAIRED>

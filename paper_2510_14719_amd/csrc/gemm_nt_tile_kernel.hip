@@ -277,11 +277,14 @@ void gemm_nt_tile_kernel(const char* __restrict__ A, const char* __restrict__ B,
     const int rows = min(BM, M - m0), cols = min(BN, N - n0);
     constexpr int CPR = BN / 8, RPI = NW * 64 / CPR;             // 16-byte chunks per row, rows per round
     const int c = (threadIdx.x % CPR) * 8;
+    with_stores(stores_of(C, M, N), [&](auto how) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r0 = 0; r0 < BM; r0 += RPI) {
-        const int r = r0 + threadIdx.x / CPR;
-        if (r < rows) store_chunk(C + (size_t)(m0 + r) * N + n0 + c, *reinterpret_cast<const u32x4*>(cst + r * C_STRIDE + c * 2), cols - c);
-    }
+        for (int r0 = 0; r0 < BM; r0 += RPI) {
+            const int r = r0 + threadIdx.x / CPR;
+            if (r < rows)
+                store_chunk<decltype(how)::value>(C + (size_t)(m0 + r) * N + n0 + c, *reinterpret_cast<const u32x4*>(cst + r * C_STRIDE + c * 2), cols - c);
+        }
+    });
 }
 
 template <int IN, int OUT, int BM, int BN, int WM, int WN, int WK, int S, int OCC>
@@ -467,8 +470,7 @@ void gemm_nt_wide_kernel(const char* __restrict__ A, const char* __restrict__ B,
     __builtin_amdgcn_s_waitcnt(0xC07F);
     ring_barrier();
     kstep(Y, X, 0, 0, 0, nk > nfull, false, nothing);
-    if constexpr (B16) store_wave_block<E>(smem + wave * 8192, acc, C, M, N, m0 + wm * 128, n0 + wn * 128, lane);
-    else store_wave_block<E, 4>(smem + wave * 8192, acc, C, M, N, m0 + wm * 128, n0 + wn * 128, lane);
+    store_wave_block_of<E>(smem + wave * 8192, acc, C, M, N, m0 + wm * 128, n0 + wn * 128, lane);
 }
 
 template <int IN, int OUT>

@@ -89,6 +89,18 @@ __device__ __forceinline__ void dma16(const void* gbase, unsigned voff, unsigned
                  :: "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(voff), "s"(uniform_ptr(gbase)) : "memory", "m0");
 }
 
+// 16 bytes to global memory, written through: the line stays in the L2 and goes on to the last-level cache at once.  Left
+// dirty in the L2 (an ordinary store) the lines of a result push its operands out of there; stored past the caches
+// (non-temporal) they have to be fetched from HBM by whoever reads the result next.  Parts of a line (128 bytes) go on one
+// by one, so this is not for rows that begin and end inside a line.  dst need not be aligned.
+__device__ __forceinline__ void store_through(void* dst, u32x4 w) {
+    __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u32x4*)dst, w, "agent");
+}
+
+// Results up to this size are stored the ordinary way: they push little out of the L2, and a write that goes
+// on to the next cache lengthens the end of a short kernel (by 0.1 ... 0.4 us).
+constexpr long long SMALL_RESULT = 4ll << 20;
+
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }

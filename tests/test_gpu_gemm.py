@@ -161,6 +161,38 @@ def test_large_tile_stores(env, config, M, N, skew):
     assert bool((buf[:16 + skew] == 7.0).all()) and bool((buf[16 + skew + M * N:] == 7.0).all())
 
 
+# The ways C leaves: whole memory lines are written through the L2 from 4 MiB on, every other tile of them past the caches from 96 MiB
+# on and all above 128 MiB, anything else with ordinary stores.  The same product into a C that starts on a line and into one that does not (always ordinary) has the
+# same bits, in every kernel; rows and columns overhang the tiles; nothing outside C is written.
+@pytest.mark.parametrize("kind", ["bf16", "e4m3"])
+@pytest.mark.parametrize("M,N,K", [(2049, 1024, 64), (2101, 3008, 512), (4099, 4160, 256), (4099, 4160, 2048), (7001, 8256, 64), (7001, 8256, 1024), (16400, 8256, 64), (16400, 8256, 1024)])
+def test_ways_of_storing_c(env, kind, M, N, K):
+    torch, binding, _ = env
+    print("case gemm ways of storing %s M%d N%d K%d" % (kind, M, N, K), flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    a, b = (torch.randn((r, K), generator=gen, device="cuda").to(torch.bfloat16 if kind == "bf16" else torch.float8_e4m3fn) for r in (M, N))
+    out = []
+    for skew in (0, 1):
+        buf = torch.full((M * N + 128,), 7.0, dtype=torch.bfloat16, device="cuda")
+        c = buf[64 + skew:64 + skew + M * N]
+        assert (c.data_ptr() % 128 == 0) == (skew == 0)
+        if kind == "bf16":
+            binding.gemm_nt(a, b, c, M, N, K)
+        else:
+            binding.gemm_nt_fp8(a, b, c, M, N, K, out_dtype=I.BF16)
+        assert bool((buf[:64 + skew] == 7.0).all()) and bool((buf[64 + skew + M * N:] == 7.0).all())
+        out.append(c)
+    assert torch.equal(*out)
+    rows = torch.tensor([0, M // 2, M - 1], device="cuda")
+    ref = a[rows].double() @ b.double().T
+    err = (out[0].view(M, N)[rows].double() - ref).abs()
+    # half an ulp of the bf16 result, and 2e-6 K for fp32 sums (see the top) or, on E4M3, whose matrix instruction adds its 64
+    # products in a narrower frame, 2^-14 of the sum of their magnitudes
+    slack = 2e-6 * K if kind == "bf16" else 2.0 ** -14 * (a[rows].double().abs() @ b.double().abs().T)
+    assert bool((err <= 1.01 * U[I.BF16] * ref.abs() + slack).all())
+
+
 def test_odd_n_uses_scalar_stores(env):
     _, _, G = env
     M, N, K = 130, 37, 96                     # N % 4 != 0: rows of C are not 8-byte aligned
