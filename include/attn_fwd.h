@@ -88,8 +88,10 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o, float *lse,
  * asynchrony and the return codes are those of attn_fwd.
  *
  * Numeric contract of the rounding of P (what a caller, or a test, may rely on).  The probabilities are rounded
- * relative to a per-row reference r that the kernel keeps while it walks the keys: r is a score of the row
- * that has really occurred, never above the running maximum and at most 8 powers of two (a factor 2^8 in the
+ * relative to a per-row reference r that the kernel keeps while it walks the keys; where attn_fwd_fp8_call_rows is 128, one
+ * for the first 64 of every 128 keys and one for the others, each with sums of its own, which are brought to the larger
+ * reference and added in fp32 at the end.  r is a score of the row (of its share of the keys)
+ * that has really occurred, never above the running maximum of that share and at most 8 powers of two (a factor 2^8 in the
  * probabilities) below it; it only moves up, by taking the value of the running maximum, when that
  * maximum has grown by more than 2^8 since r was set.  Every weight exp(s - r) <= 2^8 is rounded to E4M3 with
  * round-to-nearest-even: relative error at most 2^-4 for values down to 2^-6 (the smallest normal number),
@@ -119,12 +121,19 @@ const char *attn_fwd_strerror(int code);
 int attn_fwd_version(void);
 
 /*
- * Name of a launch parameter of the kernel chosen for (d, causal) and its value,
- * for benchmark reports: which = 0 query rows per workgroup (BM), 1 keys per
- * step (BN), 2 LDS stages, 3 threads per workgroup.  Returns -1 for an unknown
- * `which` or unsupported d.
+ * Launch parameters of the kernel for (d, causal) that calls with enough work to fill the chip take, for benchmark
+ * reports: which = 0 query rows per workgroup (BM), 1 keys per step (BN), 2 LDS stages, 3 threads per
+ * workgroup.  Returns -1 for an unknown `which` or unsupported d.
  */
 int attn_fwd_tile_param(int d, int causal, int which);
+
+/*
+ * Query rows per workgroup of the kernel that a call with these sizes takes: those of attn_fwd_tile_param, or 128 where
+ * the two halves of a workgroup share out the keys of 128 rows (see attn_fwd_fp8 for what that means for the rounding).
+ * -1 for sizes that no call accepts.
+ */
+int attn_fwd_call_rows(int B, int H, int N, int d, int causal);
+int attn_fwd_fp8_call_rows(int B, int H, int N, int d, int causal);
 
 /*
  * The static tile schedule of the launch (host-side copy of what the kernel evaluates; the paper's

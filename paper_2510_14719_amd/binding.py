@@ -61,6 +61,9 @@ def load_library() -> ctypes.CDLL:
         lib.attn_fwd_version.argtypes = []
         lib.attn_fwd_tile_param.restype = ci
         lib.attn_fwd_tile_param.argtypes = [ci, ci, ci]
+        for rows in (lib.attn_fwd_call_rows, lib.attn_fwd_fp8_call_rows):
+            rows.restype = ci
+            rows.argtypes = [ci, ci, ci, ci, ci]
         lib.attn_fwd_tile_schedule.restype = ci
         lib.attn_fwd_tile_schedule.argtypes = [ci, ci, ci, ci]
         lib.attn_fwd_mfma_probe.restype = ci

@@ -123,6 +123,18 @@ int attn_fwd_version(void) { return 100; }
 
 int attn_fwd_tile_param(int d, int causal, int which) { return attn_launch_tile_param(d, causal, which); }
 
+int attn_fwd_call_rows(int B, int H, int N, int d, int causal)
+{
+    if (B < 1 || H < 1 || N < 1 || (d != 64 && d != 128)) return -1;
+    return attn_launch_call_rows(d, N, (long long)B * H, causal);
+}
+
+int attn_fwd_fp8_call_rows(int B, int H, int N, int d, int causal)
+{
+    if (B < 1 || H < 1 || N < 1 || (d != 64 && d != 128)) return -1;
+    return attn_fp8_launch_call_rows(d, N, (long long)B * H, causal);
+}
+
 int attn_fwd_tile_schedule(int total, int grid, int block, int round)
 {
     if (total < 1 || grid < 1 || grid > total || block < 0 || block >= grid || round < 0) return -2;

@@ -56,6 +56,7 @@
 
 #include "attn_launch.h"
 #include "gfx950_prims.h"
+#include "key_split.h"
 #include "launch_once.h"
 #include "tile_schedule.h"
 
@@ -88,7 +89,7 @@ constexpr float RESCALE_LOG2_FP8 = 8.0f;
 #define ATTN8_PERSISTENT 0
 #endif
 
-// 1: small grids take the form that splits the keys of a stage between the waves (see launch_fp8_d).
+// 1: small grids take the form that splits the keys of a stage between the waves (see key_split.h).
 #ifndef ATTN8_KEY_SPLIT
 #define ATTN8_KEY_SPLIT 1
 #endif
@@ -692,20 +693,16 @@ int launch_fp8(const AttnLaunchArgs& a)
     return e == hipSuccess ? 0 : -1;
 }
 
+// Whether this build has the form that splits keys.
+template <int D> constexpr bool HAS_SPLIT = ATTN8_KEY_SPLIT && (D == 128 ? ATTN8_CFG_BN_D128 : ATTN8_CFG_BN_D64) == 64 && ATTN8_STAGES == 4;
+
 template <int OUT, int D>
 int launch_fp8_d(const AttnLaunchArgs& a)
 {
     constexpr int BN = D == 128 ? ATTN8_CFG_BN_D128 : ATTN8_CFG_BN_D64;
-    // Few tiles: 128-row tiles with the keys of a 128-key stage shared out between the halves of the workgroup (KS = 2).
-    // A step then takes 0.91 us for 128 keys against 0.83 us for 64 (d = 128), at twice the tiles: it pays while the
-    // 128-row tiles fit the chip in one round, and with the mask and long rows (one 256-row tile per CU leaves most of them waiting
-    // for the longest) up to two rounds, at d = 64, whose registers do not spill, up to eight.  Up to 256 keys a tile
-    // has no steps to save.  Measured on MI355X, 256-row tiles against split ones (us): 1 head, N 16384, d 128: 218 -> 121;
-    // 32 heads, N 1024: 21 -> 17, d 64: 16.5 -> 11.4; beyond the line, 64 heads, N 1024, d 128: 24 against 33.  Causal: 8 heads,
-    // N 8192, d 128: 117 -> 87, 64 heads, N 4096, d 64: 156 -> 138; beyond the line, 64 heads, N 2048, d 128: 71 against 78.
-    if constexpr (ATTN8_KEY_SPLIT && BN == 64 && ATTN8_STAGES == 4) {
-        const long long tiles128 = (long long)((a.N + 127) / 128) * a.B * a.H;
-        if ((a.N > 256 && tiles128 <= 256) || (a.causal && a.N >= 2048 && tiles128 <= (D == 64 ? 2048 : 512)))
+    // (A step of split tiles takes 0.91 us for 128 keys, one of whole tiles 0.83 us for 64, at d = 128.)
+    if constexpr (HAS_SPLIT<D>) {
+        if (attn_splits_keys(D, a.N, (long long)a.B * a.H, a.causal != 0, true))
             return a.causal ? launch_fp8<OUT, D, BN, true, false, 2>(a) : launch_fp8<OUT, D, BN, false, false, 2>(a);
     }
     if (a.causal) return ATTN8_PERSISTENT ? launch_fp8<OUT, D, BN, true, true>(a) : launch_fp8<OUT, D, BN, true, false>(a);
@@ -719,6 +716,11 @@ int attn_fp8_launch(const AttnLaunchArgs& a)
 {
     if (a.dtype == 0) return a.d == 128 ? launch_fp8_d<0, 128>(a) : launch_fp8_d<0, 64>(a);
     return a.d == 128 ? launch_fp8_d<1, 128>(a) : launch_fp8_d<1, 64>(a);
+}
+
+int attn_fp8_launch_call_rows(int d, int N, long long heads, int causal)
+{
+    return (d == 128 ? HAS_SPLIT<128> : HAS_SPLIT<64>) && attn_splits_keys(d, N, heads, causal != 0, true) ? 128 : 256;
 }
 
 int attn_fp8_launch_tile_param(int d, int which)

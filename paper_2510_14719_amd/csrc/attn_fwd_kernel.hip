@@ -35,6 +35,7 @@
 
 #include "attn_launch.h"
 #include "gfx950_prims.h"
+#include "key_split.h"
 #include "launch_once.h"
 #include "tile_schedule.h"
 
@@ -75,7 +76,7 @@ constexpr float RESCALE_LOG2 = 8.0f;
 #define ATTN_D64_TWO_WG 0
 #endif
 
-// 1: small grids take the form that splits the keys of a tile between the wave groups (see launch_d).
+// 1: small grids take the form that splits the keys of a tile between the wave groups (see key_split.h).
 #ifndef ATTN_KEY_SPLIT
 #define ATTN_KEY_SPLIT 1
 #endif
@@ -795,21 +796,18 @@ int launch(const AttnLaunchArgs& a)
     return e == hipSuccess ? 0 : -1;
 }
 
+// The rule, where this build has the form.
+bool splits_keys(int d, int N, long long heads, bool causal)
+{
+    return ATTN_KEY_SPLIT && (d == 64 || ATTN_CFG_NW == 8) && ATTN_CFG_STAGES == 4 && attn_splits_keys(d, N, heads, causal, false);
+}
+
 template <int DTYPE, int D>
 int launch_d(const AttnLaunchArgs& a)
 {
     constexpr int NW = D == 128 ? ATTN_CFG_NW : 8, MB = D == 64 ? ATTN_CFG_MB_D64 : ATTN_CFG_MB, BN = ATTN_CFG_BN, STAGES = ATTN_CFG_STAGES;
-    // Few tiles: 128-row tiles with the keys shared out between the wave groups (KS = 2).  A step of 64 keys takes 0.75 us
-    // (d = 128) instead of 1.16, at twice the tiles, so it pays while the 128-row tiles still fit the chip in
-    // one round; with the mask and long rows up to two rounds (one 256-row tile per CU would leave most of them waiting for the
-    // longest).  Measured on MI355X, fp16, 256-row against split tiles: 1 head, N 16384, d 128: 296 -> 193 us; 8 heads,
-    // N 2309, d 64: 43 -> 29; 32 heads, N 1024, d 128: 30 -> 25; one step beyond the line, 64 heads, N 1024, d 128: 42
-    // against 50.  Causal: 8 heads, N 8192, d 128: 179 -> 152, d 64: 140 -> 110; 64 heads, N 1024, d 128: 31 against 41.
-    if (ATTN_KEY_SPLIT && NW == 8 && STAGES == 4) {
-        const long long tiles128 = (long long)((a.N + 127) / 128) * a.B * a.H;
-        if (tiles128 <= 256 || (a.causal && a.N >= 2048 && tiles128 <= 512))
-            return a.causal ? launch<DTYPE, D, 8, 1, BN, STAGES, true, false, 2>(a) : launch<DTYPE, D, 8, 1, BN, STAGES, false, false, 2>(a);
-    }
+    if (splits_keys(D, a.N, (long long)a.B * a.H, a.causal != 0))
+        return a.causal ? launch<DTYPE, D, 8, 1, BN, STAGES, true, false, 2>(a) : launch<DTYPE, D, 8, 1, BN, STAGES, false, false, 2>(a);
     // When the persistent form is used (d = 128 only: at d = 64 two workgroups share a CU and cover each
     // other's prologue and epilogue, and the next tile's Q fragments would cost the registers that let
     // them co-reside).  Causal: always; measured +2.5 % at N = 8192 (balanced tile lengths, next
@@ -839,6 +837,12 @@ extern "C" int attn_dbg_read(unsigned long long* host, int n)
     return (int)hipMemcpyFromSymbol(host, HIP_SYMBOL(attn_dbg), sizeof(unsigned long long) * n);
 }
 #endif
+
+int attn_launch_call_rows(int d, int N, long long heads, int causal)
+{
+    if (!(ATTN_CFG_PIPE && d == 128) && splits_keys(d, N, heads, causal != 0)) return 128;
+    return attn_launch_tile_param(d, causal, 0);
+}
 
 int attn_launch_tile_param(int d, int causal, int which)
 {

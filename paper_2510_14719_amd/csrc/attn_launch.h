@@ -61,6 +61,9 @@ int attn_launch(const AttnLaunchArgs& a);
 // Query rows per workgroup (0), keys per tile (1), LDS stages (2), threads per workgroup (3).
 int attn_launch_tile_param(int d, int causal, int which);
 
+// Query rows per workgroup of the kernel that a call takes.
+int attn_launch_call_rows(int d, int N, long long heads, int causal);
+
 // The in-wave pipelined kernel (attn_fwd_pipe_kernel.hip), d = 128 only; same contract as attn_launch.
 int attn_pipe_launch(const AttnLaunchArgs& a);
 
@@ -68,6 +71,7 @@ int attn_pipe_launch(const AttnLaunchArgs& a);
 int attn_fp8_launch(const AttnLaunchArgs& a);
 // Query rows per workgroup (0), keys per tile (1), LDS stages (2), threads per workgroup (3).
 int attn_fp8_launch_tile_param(int d, int which);
+int attn_fp8_launch_call_rows(int d, int N, long long heads, int causal);
 
 // Register-only MFMA stream (mfma_probe.hip): `workgroups` workgroups of mfma_probe_threads() threads,
 // every wave issuing iters * 8 MFMAs of the given element type; one float per thread is written to sink.
