@@ -58,6 +58,15 @@ int gemm_nt_config(const void *a, const void *b, void *c, int M, int N, int K, v
 int gemm_nt_f16(const void *a, const void *b, void *c, int M, int N, int K, void *stream);
 int gemm_nt_bf16(const void *a, const void *b, void *c, int M, int N, int K, void *stream);
 
+/*
+ * The kernels that gemm_nt chooses from, by the tile of C of a workgroup: 0 = 256 x 256, 1 = 64 x 64, 2 = 128 x 128 with
+ * two workgroups per compute unit, 3 = 128 x 128 with more waves.  gemm_nt_shape says which one a product takes (-1 for sizes that
+ * no call accepts), gemm_nt_by_shape takes the one the caller names (for tests and measurements): GEMM_NT_ERR_SHAPE for any
+ * other value, and for shape 0 with K < 64.
+ */
+int gemm_nt_shape(int M, int N, int K);
+int gemm_nt_by_shape(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int dtype, int shape);
+
 /* Host-only argument check: what gemm_nt would return before launching. */
 int gemm_nt_check_args(const void *a, const void *b, const void *c, int M, int N, int K, int dtype);
 
@@ -86,6 +95,10 @@ int gemm_nt_fp8(const void *a, const void *b, void *c, int M, int N, int K, void
  * 4 = the same with paired copies.  GEMM_NT_ERR_SHAPE for any other value.
  */
 int gemm_nt_fp8_config(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int out_dtype, int config);
+
+/* The same as gemm_nt_shape and gemm_nt_by_shape for gemm_nt_fp8 (shape 0 needs K >= 128). */
+int gemm_nt_fp8_shape(int M, int N, int K);
+int gemm_nt_fp8_by_shape(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int out_dtype, int shape);
 
 /* Host-only argument check: what gemm_nt_fp8 would return before launching. */
 int gemm_nt_fp8_check_args(const void *a, const void *b, const void *c, int M, int N, int K, int out_dtype);

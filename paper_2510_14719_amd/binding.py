@@ -78,6 +78,12 @@ def load_library() -> ctypes.CDLL:
         lib.gemm_nt.argtypes = [vp, vp, vp, ci, ci, ci, vp, ci]
         lib.gemm_nt_config.restype = ci
         lib.gemm_nt_config.argtypes = [vp, vp, vp, ci, ci, ci, vp, ci, ci]
+        for shape_of in (lib.gemm_nt_shape, lib.gemm_nt_fp8_shape):
+            shape_of.restype = ci
+            shape_of.argtypes = [ci, ci, ci]
+        for by_shape in (lib.gemm_nt_by_shape, lib.gemm_nt_fp8_by_shape):
+            by_shape.restype = ci
+            by_shape.argtypes = [vp, vp, vp, ci, ci, ci, vp, ci, ci]
         lib.gemm_nt_f16.restype = ci
         lib.gemm_nt_f16.argtypes = [vp, vp, vp, ci, ci, ci, vp]
         lib.gemm_nt_bf16.restype = ci

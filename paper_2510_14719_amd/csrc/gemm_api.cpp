@@ -48,6 +48,34 @@ int gemm_nt(const void* a, const void* b, void* c, int M, int N, int K, void* st
     return gemm_nt_config(a, b, c, M, N, K, stream, dtype, 0);
 }
 
+int gemm_nt_shape(int M, int N, int K)
+{
+    if (M < 1 || N < 1 || K < 32 || K % 32 != 0) return -1;
+    return gemm_tile_shape(M, N, 2LL * K);
+}
+
+int gemm_nt_by_shape(const void* a, const void* b, void* c, int M, int N, int K, void* stream, int dtype, int shape)
+{
+    const int rc = gemm_nt_check_args(a, b, c, M, N, K, dtype);
+    if (rc != GEMM_NT_OK) return rc;
+    if (shape < 0 || shape > 3 || (shape == 0 && K < 64)) return GEMM_NT_ERR_SHAPE;
+    return gemm_tile_launch({a, b, c, M, N, K, dtype, stream}, dtype, shape) == 0 ? GEMM_NT_OK : GEMM_NT_ERR_LAUNCH;
+}
+
+int gemm_nt_fp8_shape(int M, int N, int K)
+{
+    if (M < 1 || N < 1 || K < 64 || K % 64 != 0) return -1;
+    return gemm_tile_shape(M, N, K);
+}
+
+int gemm_nt_fp8_by_shape(const void* a, const void* b, void* c, int M, int N, int K, void* stream, int out_dtype, int shape)
+{
+    const int rc = gemm_nt_fp8_check_args(a, b, c, M, N, K, out_dtype);
+    if (rc != GEMM_NT_OK) return rc;
+    if (shape < 0 || shape > 3 || (shape == 0 && K < 128)) return GEMM_NT_ERR_SHAPE;
+    return gemm_tile_launch({a, b, c, M, N, K, out_dtype, stream}, 2, shape) == 0 ? GEMM_NT_OK : GEMM_NT_ERR_LAUNCH;
+}
+
 int gemm_nt_fp8_check_args(const void* a, const void* b, const void* c, int M, int N, int K, int out_dtype)
 {
     if (!a || !b || !c) return GEMM_NT_ERR_NULL;

@@ -152,6 +152,13 @@ def test_gemm_argument_validation_needs_no_gpu(lib):
     assert lib.gemm_nt_bf16(a, b, c, 8, 8, 64 + 8, None) == -2
     assert lib.gemm_nt_config(a, b, c, 8, 8, 64, None, 0, 5) == -2        # unknown configuration
     assert lib.gemm_nt_config(a, b, None, 8, 8, 64, None, 0, 2) == -1
+    for bad in (-1, 4):
+        assert lib.gemm_nt_by_shape(a, b, c, 8, 8, 64, None, 0, bad) == -2     # unknown kernel
+    assert lib.gemm_nt_by_shape(a, b, c, 8, 8, 32, None, 0, 0) == -2           # rows shorter than a line
+    assert lib.gemm_nt_by_shape(None, b, c, 8, 8, 64, None, 0, 1) == -1
+    assert lib.gemm_nt_shape(8, 8, 48) == -1 and lib.gemm_nt_shape(0, 8, 64) == -1
+    for M, N, K in ((1, 1, 32), (64, 64, 32), (8192, 8192, 32), (300, 4000, 1024), (8192, 8192, 8192)):
+        assert lib.gemm_nt_shape(M, N, K) in ((1, 2, 3) if K < 64 else (0, 1, 2, 3))
     for code in range(-8, 1):
         assert len(lib.gemm_nt_strerror(code)) > 3
     bm, bn, bk, st, th = (lib.gemm_nt_tile_param(w) for w in range(5))
@@ -180,5 +187,9 @@ def test_gemm_fp8_argument_validation_needs_no_gpu(lib):
     assert lib.gemm_nt_fp8_config(a, b, c, 8, 8, 64, None, 0, 5) == -2     # unknown configuration
     assert lib.gemm_nt_fp8_config(a, b, c, 8, 8, 64, None, 0, -1) == -2
     assert lib.gemm_nt_fp8_config(None, b, c, 8, 8, 64, None, 0, 1) == -1
+    assert lib.gemm_nt_fp8_by_shape(a, b, c, 8, 8, 128, None, 0, 4) == -2      # unknown kernel
+    assert lib.gemm_nt_fp8_by_shape(a, b, c, 8, 8, 64, None, 0, 0) == -2       # rows shorter than a line
+    assert lib.gemm_nt_fp8_by_shape(a, b, None, 8, 8, 64, None, 0, 1) == -1
+    assert lib.gemm_nt_fp8_shape(8, 8, 96) == -1 and lib.gemm_nt_fp8_shape(8192, 8192, 64) in (1, 2, 3)
     bm, bn, bk, st, th = (lib.gemm_nt_fp8_tile_param(w) for w in range(5))
     assert st * (bm + bn) * bk <= 160 * 1024 and th % 64 == 0 and lib.gemm_nt_fp8_tile_param(9) == -1

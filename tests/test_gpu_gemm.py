@@ -5,8 +5,6 @@ one final rounding to 16 bit): |C_gpu - C_ref| <= 1.01 * u * |C_ref| + 2e-6 * K,
 fp16 and 2^-8 for bf16 (half an ulp of the output); the second term bounds the accumulated fp32
 rounding for N(0,1) operands (K * 2^-24 * sum|a||b| / sqrt(K) in the typical case) with a wide margin.
 """
-import ctypes
-
 import numpy as np
 import pytest
 
@@ -83,10 +81,6 @@ def test_every_kernel_configuration_in_full(env, M, N, K, dtype, config):
     assert np.array_equal(c, c1)
 
 
-def shape_of(binding, M, N, row_bytes):
-    return binding.load_library()["_Z15gemm_tile_shapeiix"](ctypes.c_int(M), ctypes.c_int(N), ctypes.c_longlong(row_bytes))
-
-
 # One to eleven 128-byte steps along K around the ring depths (4, 2, 4) of the small-tile shapes, whole and with a half-filled
 # last step (K % 64 == 32), tiles that overhang by one row or column and by all but one, rows of C for both store widths.
 @pytest.mark.parametrize("shape,M,N,Ks", [(1, 65, 63, (32, 64, 96, 128, 192, 224, 256, 288, 320, 352, 704)), (1, 64, 128, (288, 640)),
@@ -96,7 +90,7 @@ def shape_of(binding, M, N, row_bytes):
 def test_small_tile_shapes(env, shape, M, N, Ks, dtype):
     _, binding, G = env
     for K in Ks:
-        assert shape_of(binding, M, N, 2 * K) == shape
+        assert binding.load_library().gemm_nt_shape(M, N, K) == shape
         a, b = I.make_ab(M, N, K, dtype, seed=1100 + M + N + K)
         print("case gemm shape%d M%d N%d K%d dtype%d" % (shape, M, N, K, dtype), flush=True)
         c = run_gpu(env, a, b, dtype)
@@ -108,11 +102,6 @@ def test_small_tile_shapes(env, shape, M, N, Ks, dtype):
                   "shape %d M%d N%d K%d" % (shape, M, N, K))
 
 
-class LaunchArgs(ctypes.Structure):
-    _fields_ = [("a", ctypes.c_void_p), ("b", ctypes.c_void_p), ("c", ctypes.c_void_p), ("M", ctypes.c_int), ("N", ctypes.c_int),
-                ("K", ctypes.c_int), ("dtype", ctypes.c_int), ("stream", ctypes.c_void_p), ("config", ctypes.c_int)]
-
-
 # The 256 x 256 kernel with whole lines per row, called directly: one to six 128-byte steps (ring of two and a half), with and
 # without a half-filled last one, many steps; tiles that overhang by little and by nearly all.  On E4M3 it
 # adds the k-steps in the order of the fixed configurations, so its results are theirs, bit for bit (16-bit operands take
@@ -121,7 +110,8 @@ class LaunchArgs(ctypes.Structure):
 @pytest.mark.parametrize("M,N", [(256, 256), (257, 511), (300, 40)])
 def test_whole_line_kernel(env, kind, M, N):
     torch, binding, G = env
-    launch = binding.load_library()["_Z16gemm_tile_launchRK14GemmLaunchArgsii"]
+    lib = binding.load_library()
+    launch = lib.gemm_nt_fp8_by_shape if kind == "e4m3" else lib.gemm_nt_by_shape
     f8, dtype = kind == "e4m3", I.BF16 if kind == "bf16" else I.FP16
     view = {"fp16": torch.float16, "bf16": torch.bfloat16, "e4m3": torch.float8_e4m3fn}[kind]
     out = torch.bfloat16 if kind == "bf16" else torch.float16
@@ -132,16 +122,14 @@ def test_whole_line_kernel(env, kind, M, N):
         gen.manual_seed(M + N + K)
         a, b = (torch.randn((r, K), generator=gen, device="cuda").to(view) for r in (M, N))
         c, want = (torch.full((M, N), float("nan"), dtype=out, device="cuda") for _ in range(2))
-        arg = LaunchArgs(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, dtype, torch.cuda.current_stream().cuda_stream, 0)
-        assert launch(ctypes.byref(arg), 2 if f8 else dtype, 0) == 0
+        assert launch(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, torch.cuda.current_stream().cuda_stream, dtype, 0) == 0
         if f8:
             binding.gemm_nt_fp8(a, b, want, M, N, K, out_dtype=dtype, config=1)
             assert torch.equal(c, want)
         else:
             ref = a.double().cpu() @ b.double().cpu().T
             check(c.double().cpu().numpy(), ref.numpy(), dtype, K, "whole lines %s K%d" % (kind, K))
-    arg = LaunchArgs(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, 64 if f8 else 32, dtype, None, 0)
-    assert launch(ctypes.byref(arg), 2 if f8 else dtype, 0) == -1
+    assert launch(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, 64 if f8 else 32, None, dtype, 0) == -2
 
 
 # Rows of C that allow 16-, 8- and 2-byte stores, and a C that is aligned to less than its rows are; tiles that overhang by one

@@ -12,7 +12,6 @@ a factor 4 at the smallest K and is still far below a single wrong term: one mis
 of a fragment changes an entry by about 4 typical products, i.e. by 2^-4 S at K = 64 and 2^-12 S at
 K = 16384.  Integer-valued operands, whose sums are exact in any frame, must match bit for bit.
 """
-import ctypes
 
 import numpy as np
 import pytest
@@ -102,7 +101,7 @@ def test_every_kernel_configuration_in_full(env, M, N, K, config):
 def test_small_tile_shapes(env, shape, M, N, Ks):
     _, binding, G = env
     for K in Ks:
-        assert binding.load_library()["_Z15gemm_tile_shapeiix"](ctypes.c_int(M), ctypes.c_int(N), ctypes.c_longlong(K)) == shape
+        assert binding.load_library().gemm_nt_fp8_shape(M, N, K) == shape
         a, b = I.make_ab(M, N, K, I.E4M3, seed=1100 + M + N + K)
         print("case gemm_fp8 shape%d M%d N%d K%d" % (shape, M, N, K), flush=True)
         c = run_gpu(env, a, b, I.FP16)
