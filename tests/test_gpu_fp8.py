@@ -70,6 +70,49 @@ def test_few_and_many_tiles(G, oracle, H, lengths, d, causal):
             G.check_fp8(o[sl], l[sl], o_ref, l_ref, bo, bl, "H%d N%d d%d head %d" % (H, N, d, h))
 
 
+# Enough heads for the 256-row kernel: its steady state followed by a ragged end, with ends that put the epilogue's pieces in each of the
+# ring's slots; keys whose norm grows, so that the reference keeps moving up to the end.  The first and the last head.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("growing", [False, True])
+def test_ragged_ends_with_many_heads(G, oracle, growing, d, causal):
+    from paper_2510_14719_amd import binding
+    for N in (700,) if growing else (577, 700, 800, 1000, 1531):
+        H = 300 if N <= 700 else 70
+        assert binding.load_library().attn_fwd_fp8_call_rows(1, H, N, d, causal) == 256
+        q, k, v = I.make_qkv(1, H, N, d, E4M3, 1600 + N + d)
+        if growing:
+            rng = np.random.Generator(np.random.Philox(1700 + d))
+            k = I.f32_to_e4m3_bits(rng.standard_normal((1, H, N, d), dtype=np.float32) * np.linspace(0.2, 6.0, N, dtype=np.float32)[None, None, :, None])
+        scale = 0.3 if growing else 1.0 / math.sqrt(d)
+        print("case fp8 ragged many heads H%d N%d d%d causal%d growing%d" % (H, N, d, causal, growing), flush=True)
+        o, l = G.run_gpu_fp8(q, k, v, I.FP16, scale, causal)
+        assert np.isfinite(o).all() and np.isfinite(l).all()
+        for h in (0, H - 1):
+            sl = (slice(0, 1), slice(h, h + 1))
+            qh, kh, vh = (np.ascontiguousarray(x[sl]) for x in (q, k, v))
+            o_ref, l_ref, p = oracle.attn_ref(qh, kh, vh, E4M3, scale, causal, return_p=True)
+            bo, bl = G.fp8_bounds(p, G.e4m3_to_f64(vh), o_ref, I.FP16)
+            G.check_fp8(o[sl], l[sl], o_ref, l_ref, bo, bl, "H%d N%d d%d head %d" % (H, N, d, h))
+
+
+# ... and for the epilogue of the split form above 4 MiB of O
+@pytest.mark.parametrize("causal", [False, True])
+def test_split_form_with_a_large_result(G, oracle, causal):
+    from paper_2510_14719_amd import binding
+    H, N, d = 8, 3900, 128
+    assert binding.load_library().attn_fwd_fp8_call_rows(1, H, N, d, causal) == 128
+    q, k, v = I.make_qkv(1, H, N, d, E4M3, 1800)
+    print("case fp8 split, large result causal%d" % causal, flush=True)
+    o, l = G.run_gpu_fp8(q, k, v, I.BF16, 1.0 / math.sqrt(d), causal)
+    assert np.isfinite(o).all() and np.isfinite(l).all()
+    sl = (slice(0, 1), slice(H - 1, H))
+    qh, kh, vh = (np.ascontiguousarray(x[sl]) for x in (q, k, v))
+    o_ref, l_ref, p = oracle.attn_ref(qh, kh, vh, E4M3, 1.0 / math.sqrt(d), causal, return_p=True)
+    bo, bl = G.fp8_bounds(p, G.e4m3_to_f64(vh), o_ref, I.BF16)
+    G.check_fp8(o[sl], l[sl], o_ref, l_ref, bo, bl, "split, large result")
+
+
 def test_config_f1(G, oracle):
     w = I.FP8_WORKLOADS["f1"]
     _full(G, oracle, w.B, w.H, w.N, w.d, w.causal, w.seed, what="f1")

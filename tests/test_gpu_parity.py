@@ -183,6 +183,60 @@ def test_large_scores_exercise_rescaling(G, oracle, dtype):
     G.check(o, l, o_ref, l_ref, "large-scores", tol_o_max=4e-2 if dtype == I.BF16 else 2e-2, tol_lse=2e-2)
 
 
+# Enough heads for the 256-row kernels (few heads take 128-row tiles, whatever the length): their steady state, more than eight key
+# tiles, followed by a ragged end, with row tiles that end at different places; ends that put the epilogue's pieces in each of the
+# ring's slots.  The first and the last head, and every element written.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,dtype", [(64, I.FP16), (64, I.BF16), (128, I.FP16)])
+def test_ragged_ends_with_many_heads(G, oracle, d, dtype, causal):
+    from paper_2510_14719_amd import binding
+    for N in (577, 700, 800, 1000, 1531):
+        H = 300 if N <= 700 else 70
+        assert binding.load_library().attn_fwd_call_rows(1, H, N, d, causal) == 256
+        q, k, v = I.make_qkv(1, H, N, d, dtype, 2200 + N + d)
+        print("case ragged many heads H%d N%d d%d causal%d dtype%d" % (H, N, d, causal, dtype), flush=True)
+        o, l = G.run_gpu(q, k, v, dtype, 1.0 / math.sqrt(d), causal)
+        assert np.isfinite(o).all() and np.isfinite(l).all()
+        for h in (0, H - 1):
+            sl = (slice(0, 1), slice(h, h + 1))
+            o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]),
+                                           dtype, 1.0 / math.sqrt(d), causal)
+            G.check(o[sl], l[sl], o_ref, l_ref, "H%d N%d d%d head %d" % (H, N, d, h))
+
+
+# The split form above 4 MiB of O (another way of storing it), one round and two
+@pytest.mark.parametrize("d,H,N,causal", [(128, 8, 3900, False), (128, 8, 3900, True), (64, 16, 2005, False), (64, 16, 2005, True), (128, 16, 2700, True)])
+def test_split_form_with_a_large_result(G, oracle, d, H, N, causal):
+    from paper_2510_14719_amd import binding
+    assert binding.load_library().attn_fwd_call_rows(1, H, N, d, causal) == 128
+    q, k, v = I.make_qkv(1, H, N, d, I.FP16, 2300 + N)
+    print("case split, large result H%d N%d d%d causal%d" % (H, N, d, causal), flush=True)
+    o, l = G.run_gpu(q, k, v, I.FP16, 1.0 / math.sqrt(d), causal)
+    assert np.isfinite(o).all() and np.isfinite(l).all()
+    sl = (slice(0, 1), slice(H - 1, H))
+    o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]), I.FP16, 1.0 / math.sqrt(d), causal)
+    G.check(o[sl], l[sl], o_ref, l_ref, "split, large result H%d N%d d%d" % (H, N, d))
+
+
+# The same growing keys as above over enough heads for the 256-row kernels; the first heads keep the tolerances.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+def test_large_scores_with_many_heads(G, oracle, causal, d):
+    H, N, dtype = 100, 700, I.BF16
+    scale = 1.0 / math.sqrt(d)
+    q = I.normal_bits((1, H, N, d), dtype, 192, std=2.0)
+    rng = np.random.Generator(np.random.Philox(193))
+    kf = rng.standard_normal((1, H, N, d), dtype=np.float32) * (0.5 + 2.5 * np.arange(N, dtype=np.float32)[None, None, :, None] / N)
+    k = I.to_bits(kf, dtype)
+    v = I.normal_bits((1, H, N, d), dtype, 194)
+    print("case large scores many heads d%d causal%d" % (d, causal), flush=True)
+    o, l = G.run_gpu(q, k, v, dtype, scale, causal)
+    for h in (0, H - 1):
+        sl = (slice(0, 1), slice(h, h + 1))
+        o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]), dtype, scale, causal)
+        G.check(o[sl], l[sl], o_ref, l_ref, "large-scores head %d" % h, tol_o_max=4e-2, tol_lse=2e-2)
+
+
 def test_score_shift_moves_lse_only(G):
     B, H, N, d = 1, 1, 512, 64
     scale, c = 0.125, 24.0

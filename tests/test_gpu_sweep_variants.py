@@ -75,6 +75,16 @@ def test_attention_variants_against_the_oracle(env, op, point):
         o_ref, l_ref = oracle.attn_ref(q, k, v, dtype, scale, causal)
         of, lf = _attn(torch, lib, q, k, v, dtype, scale, causal)
         _check(of, lf, o_ref, l_ref, "N%d dtype%d causal%d" % (N, dtype, causal))
+    # (those take 128-row tiles where the build has them; the kernels the knobs select, with a ragged end: many heads, the
+    # first and the last)
+    for (H, N, dtype, causal, seed) in [(90, 577, I.FP16, False, 307), (60, 1000, I.BF16, True, 308)]:
+        assert ((N + 127) // 128) * H > 256
+        q, k, v = I.make_qkv(1, H, N, 128, dtype, seed)
+        of, lf = _attn(torch, lib, q, k, v, dtype, 1.0 / math.sqrt(128), causal)
+        for h in (0, H - 1):
+            sl = (slice(0, 1), slice(h, h + 1))
+            o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]), dtype, 1.0 / math.sqrt(128), causal)
+            _check(of[sl], lf[sl], o_ref, l_ref, "H%d N%d dtype%d causal%d head %d" % (H, N, dtype, causal, h))
     # a workload long enough for the steady state of every loop, on sampled rows
     for name in (["c5"] if op == "attn_causal" else ["c3", "c5"]):
         w = I.WORKLOADS[name]
@@ -100,6 +110,14 @@ def test_fp8_attention_variants_against_the_oracle(env, op, point):
     o_ref, l_ref = oracle.attn_ref(q, k, v, I.E4M3, scale, True)
     of, lf = _attn(torch, lib, q, k, v, I.E4M3, scale, True, fp8=True)
     _check(of, lf, o_ref, l_ref, "fp8 N333 causal", tol=(1.5e-1, 8e-3, 7e-2))
+    # the 256-row kernel with a ragged end, its first and last head
+    H, N = 60, 1000
+    q, k, v = I.make_qkv(1, H, N, 128, I.E4M3, 309)
+    of, lf = _attn(torch, lib, q, k, v, I.E4M3, scale, True, fp8=True)
+    for h in (0, H - 1):
+        sl = (slice(0, 1), slice(h, h + 1))
+        o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]), I.E4M3, scale, True)
+        _check(of[sl], lf[sl], o_ref, l_ref, "fp8 H%d N%d causal head %d" % (H, N, h), tol=(1.5e-1, 8e-3, 7e-2))
     for name, tol in (("f3", (TOL_O_MAX, TOL_O_MEAN, TOL_LSE)), ("f5", (1.5e-1, 8e-3, 7e-2))):
         w = I.FP8_WORKLOADS[name]
         q, k, v = I.make_workload(w)
