@@ -152,15 +152,11 @@ void gemm_nt_tile_kernel(const char* __restrict__ A, const char* __restrict__ B,
 
     // own copies of every stage but the last `out` ones issued are complete
     auto wait_out = [&](int out) __attribute__((always_inline)) {
-        if (S > 7 && out >= 6) wait_vmcnt<(S > 7 ? 6 : 0) * PPW>();
-        else if (S > 6 && out == 5) wait_vmcnt<(S > 6 ? 5 : 0) * PPW>();
-        else if (S > 5 && out == 4) wait_vmcnt<(S > 5 ? 4 : 0) * PPW>();
-        else if (S > 4 && out == 3) wait_vmcnt<(S > 4 ? 3 : 0) * PPW>();
-        else if (S > 3 && out == 2) wait_vmcnt<(S > 3 ? 2 : 0) * PPW>();
+        if (S > 3 && out == 2) wait_vmcnt<(S > 3 ? 2 : 0) * PPW>();
         else if (S > 2 && out == 1) wait_vmcnt<(S > 2 ? 1 : 0) * PPW>();
         else wait_vmcnt<0>();
     };
-    static_assert(S >= 2 && S <= 8, "wait_out lists the counts");
+    static_assert(S >= 2 && S <= 4, "wait_out lists the counts");
 
     // ---- prologue: the whole ring in flight, stage 0 complete for everyone, its fragments requested
 #pragma unroll
