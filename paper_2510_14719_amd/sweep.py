@@ -39,16 +39,14 @@ What the axes stand for on gfx950:
                                 in-wave software pipeline of the paper's Algorithm 1) or after them as one block (0)
              ATTN8_STAGES       depth of the LDS ring (the paper's D): copies run STAGES - 2 tiles ahead
              ATTN8_COPIES_IN_PASS copies issued one by one behind MFMAs of the pass (1) or all right after the barrier (0)
-  gemm       GEMM_STAGES        depth of the LDS ring (the paper's D): 4 or 5
-             GEMM_CONFIG        0: chosen by K; 1: 8 waves x (128 x 64); 2: the same with paired copies (two stages
+  gemm       GEMM_CONFIG        0: the kernels of gemm_nt_tile_kernel.hip, chosen by M, N and K (the default; they have none of
+                                the knobs below); 1: 8 waves x (128 x 64); 2: the same with paired copies (two stages
                                 issued together so that both halves of a memory line are requested back to back);
                                 3: 4 waves x (128 x 128); 4: the same with paired copies
-             GEMM_TAIL_READS    LDS requests allowed in flight across the tile boundary
-  gemm_fp8   GEMM8_STAGES, GEMM8_TAIL_READS, GEMM8_CONFIG   the same for the 8-bit-float kernel
+             GEMM_STAGES        (configurations 1 to 4) depth of the LDS ring (the paper's D): 4 or 5
+             GEMM_TAIL_READS    (configurations 1 to 4) LDS requests allowed in flight across the tile boundary
+  gemm_fp8   GEMM8_CONFIG, GEMM8_STAGES, GEMM8_TAIL_READS   the same for 8-bit floats
              GEMM8_COPY_PHASE   copies behind the odd (1) or the even (0) MFMAs of a K tile
-             GEMM8_CONFIG       0: chosen by K; 1: 8 waves x (128 x 64); 2: the same with paired copies (two stages
-                                issued together so that both halves of a memory line are requested back to back);
-                                3: 4 waves x (128 x 128); 4: the same with paired copies
 """
 from __future__ import annotations
 
@@ -92,8 +90,8 @@ TEST_VARIANTS = {
 
 
 def grid_points(op: str):
-    """All combinations of the grid of ``op`` as dicts, the default point first.  (For attn_schedule the pipe-only
-    knobs only vary with ATTN_CFG_PIPE = 1.)"""
+    """All combinations of the grid of ``op`` as dicts, the default point first.  (Knobs of a kernel only vary where it is
+    selected: the in-wave kernel's with ATTN_CFG_PIPE = 1, those of the fixed product kernels with a configuration of 1 to 4.)"""
     g = GRIDS[op]
     keys = list(g)
     pts = [dict(zip(keys, vals)) for vals in itertools.product(*(g[k] for k in keys))]
@@ -102,6 +100,9 @@ def grid_points(op: str):
         # generated assembly loop, which has its own fragment window and is interleaved by construction
         pts = [p for p in pts if (p["ATTN_CFG_PIPE"] == 1 or all(p[k] == DEFAULTS[k] for k in keys if k != "ATTN_CFG_PIPE"))
                and (p["ATTNP_CFG_NW"] == 8 or (p["ATTNP_INTERLEAVE"] == 1 and p["ATTNP_FWIN"] == 3))]
+    if op in ("gemm", "gemm_fp8"):
+        config = keys[0]
+        pts = [p for p in pts if p[config] != 0 or all(p[k] == DEFAULTS[k] for k in keys)]
     pts.sort(key=lambda p: (not all(p[k] == DEFAULTS[k] for k in keys), [p[k] for k in keys]))
     return pts
 

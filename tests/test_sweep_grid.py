@@ -17,6 +17,8 @@ def test_default_point_first_and_names_unique():
             n *= len(vals)
         if op == "attn_schedule":       # the knobs of the in-wave kernel only vary where that kernel is selected
             n = 1 + 4 + 1               # the default, eight waves x (interleave, window), four waves
+        if op in ("gemm", "gemm_fp8"):  # configuration 0 has no further knobs
+            n = 1 + 4 * 2 * 2
         assert len(pts) == n
         assert all(pts[0][k] == sweep.DEFAULTS[k] for k in grid)
         names = [sweep.variant_name(op, p) for p in pts]
