@@ -138,7 +138,7 @@ int attn_fwd_fp8_call_rows(int B, int H, int N, int d, int causal);
 /*
  * The static tile schedule of the launch (host-side copy of what the kernel evaluates; the paper's
  * Section 4.2 describes persistent kernels that walk a tile queue).  A launch covers `total` logical
- * tiles (logical tile t = (batch*head t / nqt, query tile t % nqt), nqt = ceil(N / BM); under the
+ * tiles (logical tile t = (batch*head t / nqt, query tile t % nqt), nqt = ceil(N / attn_fwd_call_rows); under the
  * causal mask the query tiles of a head are numbered from the longest to the shortest) with `grid`
  * workgroups, 1 <= grid <= total.  Returns the logical tile workgroup `block` processes in round
  * `round` (0, 1, ...), -1 when it has none in that round or any later one, -2 for arguments out of

@@ -17,10 +17,15 @@
  *   stream  a hipStream_t passed as void* (NULL = the default stream).
  *   dtype   GEMM_NT_FP16 (IEEE binary16) or GEMM_NT_BF16 (bfloat16).
  *
- * a and b must be 16-byte aligned, c 2-byte aligned (8-byte alignment and N % 4 == 0 give the fast
- * stores).  The caller owns every buffer; the library allocates nothing, retains nothing and never
- * synchronises: a call validates its arguments on the host, enqueues one kernel on `stream` on the
- * current device and returns.  Calls are thread safe.
+ * a and b must be 16-byte aligned, c 2-byte aligned (c on a 128-byte line and N % 64 == 0 give the
+ * fastest stores: every store then fills whole lines).  The caller owns every buffer; the library
+ * allocates nothing, retains nothing and never synchronises: a call validates its arguments on the
+ * host, enqueues one kernel on `stream` on the current device and returns.  Calls are thread safe.
+ *
+ * The fp32 sums are the same from call to call, but the order in which gemm_nt adds the products depends
+ * on M, N and K (they choose the kernel): an entry of C may differ in its last bits from the one that
+ * a product with other M or N, or a fixed configuration below, computes from the same rows.
+ * gemm_nt_fp8 adds in one order whatever the sizes.
  *
  * Return value: GEMM_NT_OK or a negative error code (gemm_nt_strerror gives its text).  Validation
  * happens before any HIP call; nothing is enqueued when an error is returned.
@@ -48,7 +53,7 @@ int gemm_nt(const void *a, const void *b, void *c, int M, int N, int K, void *st
 
 /*
  * The same call with the kernel configuration chosen by the caller instead of by M, N and K (for tests and
- * measurements; every configuration computes the same product): 0 = as gemm_nt, 1 = 8 waves of 128 x 64,
+ * measurements; every configuration computes the same product, 1 ... 4 bit for bit): 0 = as gemm_nt, 1 = 8 waves of 128 x 64,
  * 2 = the same with the copies of two consecutive K tiles issued together, 3 = 4 waves of 128 x 128,
  * 4 = the same with paired copies.  GEMM_NT_ERR_SHAPE for any other value.
  */
@@ -90,7 +95,7 @@ int gemm_nt_fp8(const void *a, const void *b, void *c, int M, int N, int K, void
 
 /*
  * The same call with the kernel configuration chosen by the caller instead of by M, N and K (for tests and
- * measurements; every configuration computes the same product): 0 = as gemm_nt_fp8, 1 = 8 waves of 128 x 64,
+ * measurements; all compute the same product bit for bit): 0 = as gemm_nt_fp8, 1 = 8 waves of 128 x 64,
  * 2 = the same with the copies of two consecutive K tiles issued together, 3 = 4 waves of 128 x 128,
  * 4 = the same with paired copies.  GEMM_NT_ERR_SHAPE for any other value.
  */
@@ -107,12 +112,13 @@ int gemm_nt_fp8_check_args(const void *a, const void *b, const void *c, int M, i
 const char *gemm_nt_strerror(int code);
 
 /*
- * Launch parameters of the kernel, for benchmark reports: which = 0 rows of C per workgroup, 1 columns,
+ * Launch parameters of the kernel with fixed tiles (configurations 1 ... 4), for benchmark reports; gemm_nt_shape says what
+ * a call takes: which = 0 rows of C per workgroup, 1 columns,
  * 2 K tile, 3 LDS stages, 4 threads per workgroup.  Returns -1 for an unknown `which`.
  */
 int gemm_nt_tile_param(int which);
 
-/* The same for the kernel behind gemm_nt_fp8 (the configuration a large K takes). */
+/* The same for the E4M3 kernel with fixed tiles (configurations 3 and 4). */
 int gemm_nt_fp8_tile_param(int which);
 
 #ifdef __cplusplus

@@ -19,7 +19,7 @@
 //            18 heads, N 3584 56 / 67; 5 heads, N 10325 141 / 118; d 64: 64 heads, N 4096 156 / 138; 64 heads, N 2048 57 / 52
 #pragma once
 
-constexpr int CHIP_CUS = 256;                   // compute units of the whole chip: what the lines below were measured on
+#include "tile_schedule.h"                      // CHIP_CUS
 
 // heads = batch size x heads.
 inline bool attn_splits_keys(int d, int N, long long heads, bool causal, bool fp8)

@@ -22,6 +22,8 @@
 #define TILE_SCHEDULE_HD
 #endif
 
+constexpr int CHIP_CUS = 256;                   // compute units of the whole chip: the rules of the dispatch were measured on it
+
 TILE_SCHEDULE_HD inline int tile_schedule(int total, int grid, int block, int round)
 {
     const int XCDS = 8;
