@@ -27,6 +27,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_TFLOPS = {0: 2500.0, 1: 2500.0, 2: 5000.0}   # MI355X dense MFMA peak: fp16, bf16, fp8
+GEMM_SHAPES = ((256, 256), (64, 64), (128, 128), (128, 128))   # rows and columns of C per workgroup of gemm_nt_shape's kernels
 DTYPE_NAME = {0: "fp16", 1: "bf16", 2: "fp8-e4m3"}
 
 # HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (two runs, each scaled by what the
@@ -35,6 +36,7 @@ DTYPE_NAME = {0: "fp16", 1: "bf16", 2: "fp8-e4m3"}
 PROFILE_OF = {"c4": "profiles/attn_fwd_c4_fp16_noncausal.md", "c3": "profiles/attn_fwd_c3_bf16_noncausal.md", "c5": "profiles/attn_fwd_c5_bf16_causal.md",
               "c2": "profiles/attn_fwd_c2_fp16_d64_noncausal.md", "c2_causal": "profiles/attn_fwd_c2_fp16_d64_causal.md",
               "f4": "profiles/attn_fwd_fp8_f4_e4m3_noncausal.md",
+              ("gemm", 256): "profiles/gemm_nt_m8192_n8192_k256_fp16.md",
               ("gemm", 16384): "profiles/gemm_nt_m8192_n8192_k16384_fp16.md",
               ("gemm_fp8", 16384): "profiles/gemm_nt_fp8_m8192_n8192_k16384_e4m3.md"}
 
@@ -55,7 +57,7 @@ def describe(w) -> str:
         "causal" if w.causal else "non-causal", " peaky-K" if w.peaky else "")
 
 
-# The benchmark spec's tolerances for N(0,1) inputs (O max-abs, O mean-abs, LSE max-abs); the 8-bit-float workloads
+# The tolerances for N(0,1) inputs (O max-abs, O mean-abs, LSE max-abs); the 8-bit-float workloads
 # of these shapes stay inside them as well.
 TOL = {"o_max_abs": 2e-2, "o_mean_abs": 2e-3, "lse_max_abs": 1e-2}
 
@@ -162,6 +164,8 @@ def main_gemm(args) -> int:
     c = torch.empty((M, N), dtype=torch.int16, device="cuda")
     stream = torch.cuda.current_stream()
     flops = 2.0 * M * N * K
+    lib = binding.load_library()
+    shape = lib.gemm_nt_fp8_shape(M, N, K) if fp8 else lib.gemm_nt_shape(M, N, K)
 
     def step():
         if fp8:
@@ -189,7 +193,7 @@ def main_gemm(args) -> int:
         "unit": "TFLOP/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": ms_per_step,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f8e4m3" if fp8 else "f16", "data": "synthetic",
         "config": {"workload": "gemm_nt: M=8192 N=8192 K=%d %s" % (K, "E4M3 operands, fp16 result" if fp8 else "fp16"),
-                   "tile": binding.gemm_fp8_tile_params() if fp8 else binding.gemm_tile_params(),
+                   "tile": dict(zip(("BM", "BN"), GEMM_SHAPES[shape]), shape=shape),
                    "flops_per_step": flops, "wall_s_timed_region": wall},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_TFLOPS[dtype], "unit": "TFLOP/s",
                      "frac": achieved / PEAK_TFLOPS[dtype],
@@ -318,7 +322,7 @@ def main() -> int:
     peak = PEAK_TFLOPS[w.dtype]
 
     # ---- the timed variant's output against the oracle: the whole heads that the CPU baseline computes anyway,
-    # element by element, within the benchmark spec's tolerances.  A violation fails the run (exit code 4).
+    # element by element, within the tolerances above.  A violation fails the run (exit code 4).
     parity, base = None, None
     if not args.no_cpu_baseline:
         import numpy as np
@@ -332,6 +336,10 @@ def main() -> int:
                   "all_outputs_finite": bool(torch.isfinite(whole_o).all()) and bool(torch.isfinite(lse).all()),
                   "tolerance": TOL}
         parity["ok"] = bool(parity["all_outputs_finite"] and all(parity[k_] <= TOL[k_] for k_ in TOL))
+
+    lib = binding.load_library()
+    tile = binding.fp8_tile_params(w.d) if fp8 else binding.tile_params(w.d, w.causal)
+    tile["BM"] = (lib.attn_fwd_fp8_call_rows if fp8 else lib.attn_fwd_call_rows)(w.B, w.H, w.N, w.d, int(w.causal))
 
     out = {
         "metric": "attention fwd TFLOP/s (4*B*H*N^2*d, halved causal), 1 GPU",
@@ -347,7 +355,7 @@ def main() -> int:
         "dtype": {0: "f16", 1: "bf16", 2: "f8e4m3"}[w.dtype],
         "data": "synthetic",
         "config": {"workload": describe(w), "scale": w.scale,
-                   "tile": binding.fp8_tile_params(w.d) if fp8 else binding.tile_params(w.d, w.causal),
+                   "tile": tile,
                    "flops_per_step": w.flops, "wall_s_timed_region": wall},
         "frac_of_mfma_peak": tflops / peak,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
