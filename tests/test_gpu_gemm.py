@@ -68,8 +68,8 @@ def test_full_compare(env, M, N, K, dtype):
 @pytest.mark.parametrize("M,N,K,dtype", [(1, 1, 32, I.FP16), (257, 255, 64, I.BF16), (300, 520, 160, I.FP16), (640, 513, 1056, I.FP16),
                                            (256, 256, 2048, I.BF16)])
 def test_every_kernel_configuration_in_full(env, M, N, K, dtype, config):
-    # gemm_nt picks the configuration by K; each of the four kernels must handle every shape: one and two
-    # K tiles, odd and even tile counts, overhanging tiles
+    # the four kernels with fixed tiles: each must handle every shape, one and two K tiles, odd and even tile
+    # counts, overhanging tiles
     _, _, G = env
     a, b = I.make_ab(M, N, K, dtype, seed=600 + M + N + K)
     print("case gemm config%d M%d N%d K%d dtype%d" % (config, M, N, K, dtype), flush=True)
@@ -82,7 +82,7 @@ def test_every_kernel_configuration_in_full(env, M, N, K, dtype, config):
 
 
 # One to eleven 128-byte steps along K around the ring depths (4, 2, 4) of the small-tile shapes, whole and with a half-filled
-# last step (K % 64 == 32), tiles that overhang by one row or column and by all but one, rows of C for both store widths.
+# last step (K % 64 == 32), tiles that overhang by one row or column and by all but one, rows of C on and off 16-byte boundaries.
 @pytest.mark.parametrize("shape,M,N,Ks", [(1, 65, 63, (32, 64, 96, 128, 192, 224, 256, 288, 320, 352, 704)), (1, 64, 128, (288, 640)),
                                           (1, 127, 136, (32, 320)), (2, 1937, 1936, (32, 64, 96, 128, 192)), (2, 1921, 2047, (160, 256)),
                                           (3, 1025, 1929, (4096,)), (3, 1793, 1793, (4000,))])
@@ -181,9 +181,9 @@ def test_ways_of_storing_c(env, kind, M, N, K):
     assert bool((err <= 1.01 * U[I.BF16] * ref.abs() + slack).all())
 
 
-def test_odd_n_uses_scalar_stores(env):
+def test_odd_n(env):
     _, _, G = env
-    M, N, K = 130, 37, 96                     # N % 4 != 0: rows of C are not 8-byte aligned
+    M, N, K = 130, 37, 96                     # rows of C are not aligned to more than an element
     a, b = I.make_ab(M, N, K, I.FP16, seed=7)
     c = run_gpu(env, a, b, I.FP16).double().cpu().numpy()
     check(c, G.gemm_nt(a, b, I.FP16), I.FP16, K, "odd N")

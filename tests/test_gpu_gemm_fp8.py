@@ -79,8 +79,8 @@ def test_full_compare(env, M, N, K, out_dtype):
 @pytest.mark.parametrize("config", [1, 2, 3, 4])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 64), (257, 255, 128), (300, 520, 320), (640, 513, 2112), (256, 256, 2048)])
 def test_every_kernel_configuration_in_full(env, M, N, K, config):
-    # gemm_nt_fp8 picks the configuration by K (1 below 2048, 4 from there on); each of the four kernels
-    # must handle every shape: one and two K tiles, odd and even tile counts, overhanging tiles
+    # the four kernels with fixed tiles: each must handle every shape, one and two K tiles, odd and even tile
+    # counts, overhanging tiles
     _, _, G = env
     a, b = I.make_ab(M, N, K, I.E4M3, seed=500 + M + N + K)
     print("case gemm_fp8 config%d M%d N%d K%d" % (config, M, N, K), flush=True)
@@ -95,7 +95,7 @@ def test_every_kernel_configuration_in_full(env, M, N, K, config):
 
 
 # One to six 128-byte steps along K around the ring depths (4, 2, 4) of the small-tile shapes, whole and with a half-filled
-# last step (K % 128 == 64), overhanging tiles, rows of C for both store widths.
+# last step (K % 128 == 64), overhanging tiles, rows of C on and off 16-byte boundaries.
 @pytest.mark.parametrize("shape,M,N,Ks", [(1, 65, 63, (64, 128, 192, 320, 448, 512, 576, 640, 768)), (1, 127, 136, (64, 704)),
                                           (2, 1937, 1936, (64, 128, 192, 384)), (3, 1025, 1929, (8192,))])
 def test_small_tile_shapes(env, shape, M, N, Ks):
@@ -113,9 +113,9 @@ def test_small_tile_shapes(env, shape, M, N, Ks):
               "shape %d M%d N%d K%d" % (shape, M, N, K))
 
 
-def test_odd_n_uses_scalar_stores(env):
+def test_odd_n(env):
     _, _, G = env
-    M, N, K = 130, 37, 192                    # N % 4 != 0: rows of C are not 8-byte aligned
+    M, N, K = 130, 37, 192                    # rows of C are not aligned to more than an element
     a, b = I.make_ab(M, N, K, I.E4M3, seed=7)
     c = run_gpu(env, a, b, I.FP16).double().cpu().numpy()
     check(c, G.gemm_nt(a, b, I.E4M3), magnitudes(env, a) @ magnitudes(env, b).T, I.FP16, "odd N")

@@ -1,6 +1,6 @@
 """Parity of the HIP path (through the C ABI) with the fp64 CPU oracle.
 
-Tolerances are the benchmark spec's: O max-abs 2e-2, mean-abs 2e-3; LSE max-abs 1e-2.
+Tolerances for N(0,1) inputs: O max-abs 2e-2, mean-abs 2e-3; LSE max-abs 1e-2.
 """
 import math
 

@@ -14,7 +14,7 @@ from paper_2510_14719_amd import inputs as I, sweep
 
 pytestmark = pytest.mark.gpu
 
-TOL_O_MAX, TOL_O_MEAN, TOL_LSE = 2e-2, 2e-3, 1e-2      # the benchmark spec's tolerances for N(0,1) inputs
+TOL_O_MAX, TOL_O_MEAN, TOL_LSE = 2e-2, 2e-3, 1e-2      # the tolerances for N(0,1) inputs
 
 
 @pytest.fixture(scope="module")
