@@ -17,6 +17,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import statistics
 import sys
@@ -58,8 +59,17 @@ def describe(w) -> str:
 
 
 # The tolerances for N(0,1) inputs (O max-abs, O mean-abs, LSE max-abs); the 8-bit-float workloads
-# of these shapes stay inside them as well.
+# of these shapes stay inside them as well, but for the mean of the short ones (see tolerances()).
 TOL = {"o_max_abs": 2e-2, "o_mean_abs": 2e-3, "lse_max_abs": 1e-2}
+
+
+def tolerances(w, fp8):
+    """TOL, with E4M3 probabilities also the mean error that their rounding gives: relative to its weight p_j each has an
+    error of at most 2^-4, an rms below 2^-4 / sqrt(3), independent of the others; O is off by sum_j p_j e_j (v_j - O), and with
+    N(0,1) scores and values sum_j p_j^2 is e / N on the average: rms 2^-4 sqrt(e / 3 N), mean magnitude sqrt(2 / pi) of that."""
+    if not fp8:
+        return TOL
+    return dict(TOL, o_mean_abs=max(TOL["o_mean_abs"], (2.0 / math.pi) ** 0.5 * 2.0 ** -4 * (math.e / (3.0 * w.N)) ** 0.5))
 
 
 def cpu_baseline(w, qn, kn, vn, budget_heads: int = 2):
@@ -331,11 +341,12 @@ def main() -> int:
         of = o.view(torch.float16 if out_dtype == 0 else torch.bfloat16).reshape(w.B * w.H, w.N, w.d)[sel].double().cpu().numpy()
         lf = lse.reshape(w.B * w.H, w.N)[sel].double().cpu().numpy()
         whole_o = o.view(torch.float16 if out_dtype == 0 else torch.bfloat16)
+        tol = tolerances(w, fp8)
         parity = {"heads": len(sel), "elements": int(of.size), "o_max_abs": float(np.abs(of - o_ref).max()),
                   "o_mean_abs": float(np.abs(of - o_ref).mean()), "lse_max_abs": float(np.abs(lf - l_ref).max()),
                   "all_outputs_finite": bool(torch.isfinite(whole_o).all()) and bool(torch.isfinite(lse).all()),
-                  "tolerance": TOL}
-        parity["ok"] = bool(parity["all_outputs_finite"] and all(parity[k_] <= TOL[k_] for k_ in TOL))
+                  "tolerance": tol}
+        parity["ok"] = bool(parity["all_outputs_finite"] and all(parity[k_] <= tol[k_] for k_ in tol))
 
     lib = binding.load_library()
     tile = binding.fp8_tile_params(w.d) if fp8 else binding.tile_params(w.d, w.causal)
