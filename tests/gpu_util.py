@@ -5,7 +5,7 @@ import torch
 
 from paper_2510_14719_amd import binding, inputs as I
 
-# spec tolerances for N(0,1) inputs
+# Tolerances for N(0,1) inputs
 TOL_O_MAX = 2e-2
 TOL_O_MEAN = 2e-3
 TOL_LSE_MAX = 1e-2
