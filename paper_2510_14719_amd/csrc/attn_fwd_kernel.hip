@@ -11,22 +11,30 @@
 //    STAGES tiles, the counterpart of an aref ring of depth D (Section 3.3.2); one s_waitcnt plus one
 //    s_barrier per tile play the role of the full/empty credits: a stage is overwritten only after
 //    every wave has passed the barrier that follows its last read of it.
-//  * A gfx950 wave issues in order and cannot run its own vector instructions under its own MFMA
-//    (measured: one wave alternating 1 MFMA + n FMAs takes 41 + 4n cycles per pair), so the overlap of
-//    Algorithm 1 cannot live inside one instruction stream.  It is realised BETWEEN the two waves that
-//    share a SIMD: the eight waves of a workgroup form two groups of four (one wave of each group per
-//    SIMD) that run the same pipeline half a period apart,
+//  * The overlap of Algorithm 1 is realised BETWEEN the two waves that share a SIMD: the eight waves of a workgroup
+//    form two groups of four (one wave of each group per SIMD) that run the same pipeline half a period apart,
 //        group A after barrier j:  [U_{j-1}, T_j] on the matrix cores, then C_j on the vector ALU
 //        group B after barrier j:  C_j on the vector ALU, then [U_j, T_{j+1}] on the matrix cores
-//    so while one wave of a SIMD streams 32 MFMAs the other one does its softmax.  The workgroup
+//    so while one wave of a SIMD streams its MFMAs the other one does its softmax.  The workgroup
 //    barrier re-locks the two groups into opposite phases every tile.
 //
-// Register layout.  The scores are computed transposed, S^T = K Q^T, with the 32x32x16 MFMA: the
-// K tile is the A operand (32 keys x 16 features), Q^T the B operand.  A lane then owns ONE query
-// (column lane%32 of the result) and 16 of the 32 keys of a block; the other 16 keys of that query
-// sit in lane^32.  Row maximum and row sum are in-lane operations plus one lane<->lane+32
-// exchange, and the probabilities are already laid out as the B operand of the second contraction
-// O^T = V^T P^T.  V^T fragments come from the LDS through the transposing 64-bit read of gfx950.
+// Register layout.  The scores are computed transposed, S^T = K Q^T, with the 16x16x32 MFMA: the
+// K tile is the A operand (16 keys x 32 features), Q^T the B operand.  A lane then owns ONE query
+// (column lane%16 of the result) of each of its wave's 16-query blocks, and four of the 16 keys of a block; the other
+// keys of that query sit in the lanes 16, 32 and 48 further on.  The probabilities of two key blocks are already laid out as the
+// B operand of the second contraction O^T = V^T P^T (which key stands at which step of a contraction is free, as
+// long as V^T follows).  V^T fragments come from the LDS through the transposing 64-bit read of gfx950.
+//
+// What bounds it at d = 128: the power the matrix cores draw.  On operands of zeros N = 16384, 16 heads, fp16, takes 1200 us
+// with either MFMA size, on N(0,1) operands 1845 us with 32x32x16 and 1670 with 16x16x32, which moves half as much of the
+// fp32 accumulators per flop (one session; 4 x 16 heads, N = 4096, bf16: 457 / 420; causal, 2 x 32 heads, N = 8192: 918 / 855).
+// At d = 64 it is the issue of vector instructions: the softmax of a wave and tile takes 800 cycles by itself (of them 32
+// exponentials 10 each, 16 conversions 8 each) and each MFMA of the other waves holds up the vector ALU for 6 to 7, whatever its
+// size (256 heads, N = 1024: 81 us / 75).
+//
+// The row sums are a further row of the second contraction, a block of ones next to V^T (one MFMA per 32 keys and 16 queries):
+// the packed dot products that did it on the vector side go through the matrix pipe as well and cost it more (N = 16384 as above:
+// 1727 us with them, 1667 without).
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -49,31 +57,14 @@ constexpr float RESCALE_LOG2 = 8.0f;
 #define ATTN_FWIN 2
 #endif
 
-// Independent accumulation chains of the row sum (see softmax_tile).
-#ifndef ATTN_SUMCHAINS
-#define ATTN_SUMCHAINS 4
-#endif
-
 // 1: launch one workgroup per resident slot and let each walk several tiles; 0: one workgroup per tile.
 #ifndef ATTN_PERSISTENT
 #define ATTN_PERSISTENT 1
-#endif
-// Longest sequence for which the non-causal d = 128 launch is persistent too (see launch_d).
-#ifndef ATTN_PERSIST_NC_MAX_N
-#define ATTN_PERSIST_NC_MAX_N 1024
 #endif
 
 // 1: the causal d = 64 launch is persistent as well (measured on MI355X: see launch_d).
 #ifndef ATTN_PERSISTENT_D64
 #define ATTN_PERSISTENT_D64 1
-#endif
-
-// 1: the d = 64 kernels are compiled for two resident workgroups per CU (128 registers per lane).  The one-tile-per-
-// workgroup kernels need 113 registers and are resident in pairs anyway; the persistent causal one needs 168 (the next
-// tile's Q fragments are loaded under the epilogue), and forced down to 128 it spills and gains nothing (measured on
-// MI355X, c2 causal: 552 vs 548-558 TFLOP/s), so the knob is off.
-#ifndef ATTN_D64_TWO_WG
-#define ATTN_D64_TWO_WG 0
 #endif
 
 // 1: small grids take the form that splits the keys of a tile between the wave groups (see key_split.h).
@@ -129,34 +120,39 @@ __device__ __forceinline__ float xor32_max(float x) {
     swap32(a, b);
     return __builtin_fmaxf(a, b);
 }
-__device__ __forceinline__ float xor32_sum(float x) {
+// The same with lane^16 (v_permlane16_swap: odd rows of 16 lanes of the first operand against even rows of the second).
+__device__ __forceinline__ float xor16_max(float x) {
     float a = x, b = x;
-    swap32(a, b);
-    return a + b;
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    return __builtin_fmaxf(a, b);
 }
 
 // (d = 64: the LDS ring is 64 KiB, two workgroups fit a CU; the second launch bound, waves per SIMD, asks the
-// compiler for the 128 registers per lane that let their 16 waves be resident together)
+// compiler for the 128 registers per lane that let their 16 waves be resident together: 256 heads, N = 1024, 88 us without
+// it, 75 with it.  The persistent kernel loads the next tile's Q under the epilogue and needs 170; held to 128 it spills and is slower, causal
+// 58 -> 61 us, and without its persistence 67.)
 // KS = 2 (small grids): the two wave groups of a workgroup work on the SAME NW / 2 * 32 query rows and share out the keys of
 // every tile, group A the first half and group B the second, each with a softmax state of its own; at the end
 // partner waves (w and w + 4) exchange halves of O and their maxima and sums through the LDS and each stores half of
 // the features.  A workgroup then covers 128 rows in about half the time of 256, twice as many of them are there to
 // fill the chip, and both groups keep their phases (one on the matrix cores while the other does its softmax).
 template <int DTYPE, int D, int NW, int MB, int BN, int STAGES, bool CAUSAL, bool PERSIST, int KS = 1>
-__global__ __launch_bounds__(NW * 64, (D == 64 && ATTN_D64_TWO_WG) ? 4 : 1)
+__global__ __launch_bounds__(NW * 64, (D == 64 && MB == 1 && !PERSIST) ? 4 : 1)
 void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                      uint16_t* __restrict__ o, float* __restrict__ lse, int N, int nqt, int total,
                      float scale, float scale_log2e, float m_none)
 {
     typedef Elem<DTYPE> E;
     constexpr int BM = NW * MB * 32 / KS;       // query rows per workgroup
-    constexpr int KB = BN / 32 / KS;            // 32-key blocks of a K/V tile that a wave computes on
-    constexpr int KK = D / 16;                  // contraction steps of Q K^T
-    constexpr int DB = D / 32;                  // 32-wide feature blocks of O
+    constexpr int KB = BN / 16 / KS;            // 16-key blocks of a K/V tile that a wave computes on
+    constexpr int QB = MB * 2;                  // 16-query blocks of a wave
+    constexpr int KK = D / 32;                  // contraction steps of Q K^T
+    constexpr int FB = D / 16;                  // 16-wide feature blocks of O
+    constexpr bool AHEAD = KS == 2;             // see fetch_ahead
     constexpr int ROW_BYTES = D * 2;
     constexpr int TILE_BYTES = BN * ROW_BYTES;  // one K or one V tile
     constexpr int STAGE_BYTES = 2 * TILE_BYTES;
-    constexpr int RB = BN / 16;                 // 16-row blocks per tile
+    constexpr int RB = BN / 8;                  // 8-row blocks per tile
     constexpr int CHUNKS = TILE_BYTES / 1024;   // 1 KiB wave-transfers per tile
     // Which waves issue the copies: 0 = all eight, 1 = group B only, 2 = group A only.
     constexpr int NG = NW / 4;                  // wave groups: one wave of each group per SIMD
@@ -165,7 +161,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     constexpr int LPG = 2 * CPW;                // copies such a wave issues per stage (K part + V part)
     static_assert(CHUNKS % COPY_WAVES == 0, "tile must split evenly over the copying waves");
     static_assert(STAGES == 4, "the ring protocol below keeps four stages");
-    static_assert(KS == 1 || (KS == 2 && NW == 8 && !PERSIST && D / 32 % 2 == 0), "the key split pairs the two wave groups");
+    static_assert(KS == 1 || (KS == 2 && NW == 8 && !PERSIST), "the key split pairs the two wave groups");
     static_assert(NW == 8 || NW == 12, "two or three groups of four waves, one wave of each group per SIMD");
 
 #ifdef ATTN_TIMING
@@ -176,10 +172,10 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept in an SGPR
     const int lane = threadIdx.x & 63;
-    const int lr = lane & 31, g = lane >> 5;
+    const int lc = lane & 15, lg = lane >> 4;   // column of a 16 x 16 block (query), and which four of its rows
     const int group = __builtin_amdgcn_readfirstlane(wave >> 2);   // waves w, w + 4 (, w + 8) share a SIMD
     const bool group_b = group == NG - 1;       // the group that does its softmax first
-    const int kb0 = KS == 2 ? group * KB : 0;   // first 32-key block of a tile that this wave computes on
+    const int kb0 = KS == 2 ? group * KB : 0;   // first 16-key block of a tile that this wave computes on
 
     // ---- which (batch*head, query tile) the workgroup works on: set per round of the tile schedule
     int round = 0;
@@ -207,7 +203,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         nt_w = nt;
         if (CAUSAL) nt_w = min(nt, (wq0 + MB * 32 - 1) / BN + 1);   // later tiles are wholly hidden from this wave's rows
         if (KS == 2) {                          // the same for this wave's share of the keys (may be 0 for group B)
-            const int last_key = (CAUSAL ? min(wq0 + MB * 32, N) : N) - 1 - kb0 * 32;
+            const int last_key = (CAUSAL ? min(wq0 + MB * 32, N) : N) - 1 - kb0 * 16;
             nt_w = last_key < 0 ? 0 : min(nt, last_key / BN + 1);
         }
         // All of these are wave-uniform; say so, or values that cross the tile loop end up in vector registers.
@@ -221,14 +217,17 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 
     // ---- global -> LDS copies.  Stage s of the ring holds K tile s+1 and V tile s: the pair that one
     // MFMA burst reads (U_s needs V_s, T_{s+1} needs K_{s+1}).  A wave moves CPW 1 KiB pieces of each.
-    // K tile in LDS: [feature group of 32][16-row block][16-byte column of the group (4)][row (16)][16 B]
-    // V tile in LDS: [feature group of 32][row (BN)][64 B]
-    // Lane L of a K piece fetches row L%16, column L/16 of the piece's (16 rows x 64 B) source block; of
-    // a V piece row L/4, column L%4.  Inside the sequence the per-lane offset is a constant and the
-    // tile/piece offset is added to the scalar base; the clamped form serves tiles that overrun the
+    // K and V tile in LDS: [feature group of 64][row (BN)][128 B], the 16-byte columns of a row permuted.  A piece is 8 rows
+    // x 128 bytes, whole memory lines (16 rows x 64 bytes, whose lanes ask for 64 or 16 bytes at a time, cost up to 5 % on calls
+    // of few tiles: 4 x 16 heads, N = 1024, d 128, causal 28.5 -> 27.8 us; 2 heads, N = 128, d 64 5.4 -> 5.1): lane L fetches row L/8.  K: column c of row r sits at c ^ (r / 2) % 8, so that the 16 rows
+    // that a fragment read takes one column of cover all banks; V: the 32-byte pairs of columns at p ^ (r / 2) % 4, for the 8
+    // rows x 32 bytes that half a wave of the transposing read covers.  Inside the sequence the per-lane offset is a constant
+    // and the tile/piece offset is added to the scalar base; the clamped form serves tiles that overrun the
     // sequence (their surplus rows are masked or never read).
-    const unsigned k_lane_off = (lane & 15) * ROW_BYTES + (lane >> 4) * 16;
-    const unsigned v_lane_off = (lane >> 2) * ROW_BYTES + (lane & 3) * 16;
+    const unsigned k_lane_col = ((lane & 7) ^ (lane >> 4)) * 16;                 // of an even piece; odd ones: ^ 64
+    const unsigned v_lane_col = ((lane & 7) ^ ((lane >> 4) * 2)) * 16;
+    const unsigned k_lane_off = (lane >> 3) * ROW_BYTES + k_lane_col;
+    const unsigned v_lane_off = (lane >> 3) * ROW_BYTES + v_lane_col;
     // does this wave issue copies, and its index among the copying waves (three groups: the first eight waves)
     const bool copies = NG == 3 ? wave < 8 : (ATTN_COPY_GROUP == 0 || (ATTN_COPY_GROUP == 1) == group_b);
     const int cwave = (NG == 3 || ATTN_COPY_GROUP == 0) ? wave : (wave & (NW / 2 - 1));
@@ -236,7 +235,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 #pragma unroll
     for (int i = 0; i < CPW; ++i) {
         const int wc = cwave * CPW + i, fg = wc / RB, rb = wc % RB;
-        piece_src[i] = rb * 16 * ROW_BYTES + fg * 64;
+        piece_src[i] = rb * 8 * ROW_BYTES + fg * 128;
         piece_dst[i] = wc * 1024;
     }
     auto issue_stage = [&](int s) __attribute__((always_inline)) {             // s = -1 is the stage that only brings K tile 0
@@ -246,21 +245,21 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             const char* kt = kh + (size_t)(s + 1) * TILE_BYTES;
             const char* vt = vh + (size_t)s * TILE_BYTES;
 #pragma unroll
-            for (int i = 0; i < CPW; ++i) dma16(kt + piece_src[i], k_lane_off, sbase + piece_dst[i]);
+            for (int i = 0; i < CPW; ++i) dma16(kt + piece_src[i], k_lane_off ^ (((cwave * CPW + i) & 1) * 64), sbase + piece_dst[i]);
 #pragma unroll
             for (int i = 0; i < CPW; ++i) dma16(vt + piece_src[i], v_lane_off, sbase + TILE_BYTES + piece_dst[i]);
         } else {
 #pragma unroll
             for (int i = 0; i < CPW; ++i) {
                 const int wc = cwave * CPW + i, fg = wc / RB, rb = wc % RB;
-                const int row = min(max((s + 1) * BN + rb * 16 + (lane & 15), 0), N - 1);
-                dma16(kh, (unsigned)(row * ROW_BYTES + fg * 64 + (lane >> 4) * 16), sbase + piece_dst[i]);
+                const int row = min(max((s + 1) * BN + rb * 8 + (lane >> 3), 0), N - 1);
+                dma16(kh, (unsigned)(row * ROW_BYTES + fg * 128) + (k_lane_col ^ ((wc & 1) * 64)), sbase + piece_dst[i]);
             }
 #pragma unroll
             for (int i = 0; i < CPW; ++i) {
                 const int wc = cwave * CPW + i, fg = wc / RB, rb = wc % RB;
-                const int row = min(max(s * BN + rb * 16 + (lane >> 2), 0), N - 1);
-                dma16(vh, (unsigned)(row * ROW_BYTES + fg * 64 + (lane & 3) * 16), sbase + TILE_BYTES + piece_dst[i]);
+                const int row = min(max(s * BN + rb * 8 + (lane >> 3), 0), N - 1);
+                dma16(vh, (unsigned)(row * ROW_BYTES + fg * 128 + v_lane_col), sbase + TILE_BYTES + piece_dst[i]);
             }
         }
     };
@@ -268,83 +267,104 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // One copy of a stage that lies wholly inside the sequence: K piece i < CPW, else V piece i - CPW.
     auto issue_piece_inside = [&](int s, int i) __attribute__((always_inline)) {
         const unsigned sbase = lds_base + ((s + STAGES) % STAGES) * STAGE_BYTES;
-        if (i < CPW) dma16(kh + (size_t)(s + 1) * TILE_BYTES + piece_src[i], k_lane_off, sbase + piece_dst[i]);
+        if (i < CPW) dma16(kh + (size_t)(s + 1) * TILE_BYTES + piece_src[i], k_lane_off ^ (((cwave * CPW + i) & 1) * 64), sbase + piece_dst[i]);
         else dma16(vh + (size_t)s * TILE_BYTES + piece_src[i - CPW], v_lane_off, sbase + TILE_BYTES + piece_dst[i - CPW]);
     };
 
     // ---- prologue of a tile: three stages in flight, Q fragments into registers
-    s16x8 Qf[MB][KK];
+    s16x8 Qf[QB][KK];
     auto prologue = [&]() __attribute__((always_inline)) {
         issue_stage(-1);
         issue_stage(0);
         issue_stage(1);
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const int row = min(wq0 + mb * 32 + lr, N - 1);
+        for (int qb = 0; qb < QB; ++qb) {
+            const int row = min(wq0 + qb * 16 + lc, N - 1);
             const uint16_t* qr = qh + (size_t)row * D;
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk)
-                Qf[mb][kk] = *reinterpret_cast<const s16x8*>(qr + (kk * 2 + g) * 8);
+                Qf[qb][kk] = *reinterpret_cast<const s16x8*>(qr + (kk * 4 + lg) * 8);
         }
     };
     prologue();
 
-    f32x16 O[MB][DB], S[MB][KB];
-    unsigned pw[MB][KB * 8];                    // P of the current tile as packed 16-bit pairs
-    float m_run[MB], l_run[MB];
+    f32x4 O[FB][QB], S[KB][QB];
+    u32x4 pw[KB / 2][QB];                       // P of the current tile as packed 16-bit pairs: the B operands of U
+    // reference of a row and what it adds to every exponent (-reference * scale * log2 e); both the same in the four lanes of a query
+    float m_run[QB], neg_mc[QB];
+    f32x4 L[QB];                                // row sums of P (all elements alike)
+    s16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = E::ONE;
 
     // per-lane LDS read offsets (the rest of every address is an immediate)
-    const int k_lane = kb0 * 2048 + (lr >> 4) * 1024 + g * 256 + (lr & 15) * 16;
-    const int v_lane = TILE_BYTES + kb0 * 32 * 64 + (4 * g + ((lane & 15) >> 2)) * 64 + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    const int k_lane = (kb0 * 16 + lc) * 128 + ((lg ^ (lc >> 1)) * 16);
+    const int v_lane = TILE_BYTES + (kb0 * 16 + 4 * lg + (lc >> 2)) * 128 + ((2 * lg + (lc >> 3)) & 3) * 32 + (lane & 3) * 8;
 
-    // K fragment (A operand of T): keys kb*32 + lane%32, features (kk*2 + lane/32)*8 .. +7
-    auto read_kf = [&](const char* sk, int kb, int kk) __attribute__((always_inline)) -> s16x8 {
-        return *reinterpret_cast<const s16x8*>(sk + ((kk >> 1) * RB + kb * 2) * 1024 + (kk & 1) * 512);
+    // K fragment (A operand of T): keys kb*16 + lane%16, features (kk*4 + lane/16)*8 .. +7
+    auto read_kf = [&](const char* const (&sk)[2], int kb, int kk) __attribute__((always_inline)) -> s16x8 {
+        return *reinterpret_cast<const s16x8*>(sk[kk & 1] + (kk >> 1) * (BN * 128) + kb * 16 * 128);
     };
-    // V^T fragment (A operand of U): features db*32 + lane%32, the 8 keys of block kb that the P
-    // operand of MFMA ks holds in this lane group, fetched with the transposing LDS read
-    auto read_vf = [&](const char* sv, int kb, int ks, int db) __attribute__((always_inline)) -> s16x8 {
-        const char* a = sv + db * (BN * 64) + (kb * 32 + ks * 16) * 64;
+    // V^T fragment (A operand of U): features fb*16 + lane%16, the 8 keys of blocks 2t and 2t + 1 that the P
+    // operand of the MFMA holds in this lane group, fetched with the transposing LDS read
+    auto read_vf = [&](const char* const (&sv)[4], int t, int fb) __attribute__((always_inline)) -> s16x8 {
+        const char* a = sv[fb & 3] + (fb >> 2) * (BN * 128) + t * 32 * 128;
         const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(a));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(a + 8 * 64));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LDS_AS s16x4*)(a + 16 * 128));
         return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
     };
 
     // ---- MFMA burst on one stage: U (O^T += V^T P^T with the P in pw) and/or T (S^T = K Q^T), as one
     // stream of MFMAs whose LDS fragments are requested FWIN MFMAs ahead.  The scheduling barriers
     // keep that order: left alone the compiler requests each fragment right before its MFMA.
+    // KS = 2: the first fragments of U are requested as soon as their stage is complete, a softmax before the burst that uses them.
+    // A split tile is a serial chain of latencies rather than a queue for the matrix cores (8 heads, N = 2309, causal: 33.5 -> 32.0 us;
+    // with 256-row tiles no difference).
+    s16x8 ahead[ATTN_FWIN];
+    auto fetch_ahead = [&](const char* stage_ptr) __attribute__((always_inline)) {
+        if (!AHEAD) return;
+        const char* const sv[4] = {stage_ptr + v_lane, stage_ptr + (v_lane ^ 32), stage_ptr + (v_lane ^ 64), stage_ptr + (v_lane ^ 96)};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < ATTN_FWIN; ++f) ahead[f] = read_vf(sv, f / FB, f % FB);
+        __builtin_amdgcn_sched_barrier(0);
+    };
     auto mfma_burst = [&](auto do_u, auto do_t, const char* stage_ptr) __attribute__((always_inline)) {
-        constexpr int NU = decltype(do_u)::value ? KB * 2 * DB : 0;
+        constexpr int NU = decltype(do_u)::value ? KB / 2 * FB : 0;
         constexpr int NT = decltype(do_t)::value ? KB * KK : 0;
         constexpr int NF = NU + NT;
         constexpr int FWIN = ATTN_FWIN < NF ? ATTN_FWIN : NF;
-        const char* sk = stage_ptr + k_lane;
-        const char* sv = stage_ptr + v_lane;
+        const char* const sk[2] = {stage_ptr + k_lane, stage_ptr + (k_lane ^ 64)};
+        const char* const sv[4] = {stage_ptr + v_lane, stage_ptr + (v_lane ^ 32), stage_ptr + (v_lane ^ 64), stage_ptr + (v_lane ^ 96)};
         s16x8 fr[NF];
+        constexpr bool HAVE = AHEAD && NU > 0;
+        if (HAVE) {
+#pragma unroll
+            for (int f = 0; f < FWIN; ++f) fr[f] = ahead[f];
+        }
         auto fetch = [&](int f) __attribute__((always_inline)) {
-            if (f < NU) fr[f] = read_vf(sv, f / (2 * DB), (f / DB) % 2, f % DB);
+            if (f < NU) fr[f] = read_vf(sv, f / FB, f % FB);
             else fr[f] = read_kf(sk, (f - NU) % KB, (f - NU) / KB);
         };
         auto run_mfma = [&](int f) __attribute__((always_inline)) {
             if (f < NU) {
-                const int kb = f / (2 * DB), ks = (f / DB) % 2, db = f % DB;
+                const int t = f / FB, fb = f % FB;
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    u32x4 w;
+                for (int qb = 0; qb < QB; ++qb) O[fb][qb] = E::mfma16(fr[f], __builtin_bit_cast(s16x8, pw[t][qb]), O[fb][qb]);
+                if (fb == FB - 1) {
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) w[t] = pw[mb][kb * 8 + ks * 4 + t];
-                    O[mb][db] = E::mfma(fr[f], __builtin_bit_cast(s16x8, w), O[mb][db]);
+                    for (int qb = 0; qb < QB; ++qb) L[qb] = E::mfma16(ones, __builtin_bit_cast(s16x8, pw[t][qb]), L[qb]);
                 }
             } else {
                 const int kb = (f - NU) % KB, kk = (f - NU) / KB;
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    S[mb][kb] = E::mfma(fr[f], Qf[mb][kk], kk == 0 ? f32x16(0.f) : S[mb][kb]);
-                }
+                for (int qb = 0; qb < QB; ++qb) S[kb][qb] = E::mfma16(fr[f], Qf[qb][kk], kk == 0 ? f32x4(0.f) : S[kb][qb]);
             }
         };
+        if (!HAVE) {
 #pragma unroll
-        for (int f = 0; f < FWIN; ++f) fetch(f);
+            for (int f = 0; f < FWIN; ++f) fetch(f);
+        }
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             if (f + FWIN < NF) fetch(f + FWIN);
@@ -353,101 +373,88 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         }
     };
 
-    // ---- C of tile j: mask, streaming softmax of S into pw, running maximum / sum, rescaling of O.
+    // ---- C of tile j: mask, streaming softmax of S into pw, running reference, rescaling of O and the row sums.
     // Base-2 exponentials with the scale folded into the exponent.  The running reference m only
     // moves when a row maximum grew by more than 2^RESCALE_LOG2 (the probabilities then stay below
-    // that factor), so the rescaling of O is rare after the first tiles.
+    // that factor), so everything about it is behind a rarely taken branch; `first`: the wave's first tile, where it is set.
     // With `spread` the wave's copies of stage j + 2 (known to lie inside the sequence) go out between the
     // exponentials, evenly spaced.
-    // `part`: 0 = the whole tile; 1 = mask, maximum, reference, rescaling and the first half of the score pairs;
-    // 2 = the second half of the pairs and the row sum (the middle group of three splits its softmax around its burst).
-    float part_negmc[MB], part_sum[MB][ATTN_SUMCHAINS];
-    auto softmax_tile = [&](int j, auto spread, auto part) __attribute__((always_inline)) {
+    // `part`: 0 = the whole tile; 1 = mask, maximum, reference, rescaling and the first half of the keys;
+    // 2 = the second half (the middle group of three splits its softmax around its burst).
+    auto softmax_tile = [&](int j, auto spread, auto part, auto first) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first)::value;
         constexpr bool SPREAD = decltype(spread)::value;
         constexpr int PART = decltype(part)::value;
-        constexpr int NPAIR = KB * 8, NCOPY = 2 * CPW, PER = NPAIR / NCOPY;
+        constexpr int NPAIR = KB * QB * 2, NCOPY = 2 * CPW, PER = NPAIR / NCOPY;
         static_assert(!SPREAD || (PER >= 1 && PER * NCOPY == NPAIR), "copies spread evenly over the exponentials");
         const int kv0 = j * BN;                 // first key of the tile; the wave's own start at block kb0
         if (PART != 2 && ((kv0 + BN > N) || (CAUSAL && kv0 + BN - 1 > wq0))) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-                const int qi = wq0 + mb * 32 + lr;
+            for (int qb = 0; qb < QB; ++qb) {
+                const int qi = wq0 + qb * 16 + lc;
                 const int lim = CAUSAL ? min(qi, N - 1) : N - 1;   // last visible key
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int key = kv0 + (kb0 + kb) * 32 + (i >> 2) * 8 + g * 4 + (i & 3);
-                        if (key > lim) S[mb][kb][i] = -__builtin_inff();
+                    for (int i = 0; i < 4; ++i) {
+                        const int key = kv0 + (kb0 + kb) * 16 + lg * 4 + i;
+                        if (key > lim) S[kb][qb][i] = -__builtin_inff();
                     }
             }
         }
-        float alpha[MB];
-        bool upd_any = false;
+        if (PART != 2) {
+            // A lane looks at its own part of the keys only: some lane of a row exceeds the limit exactly when the row does.
+            float mx[QB];
+            bool over = false;
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            // independent chains: a dot2 accumulate has a dependent latency of about four issue slots
-            constexpr int NCH = ATTN_SUMCHAINS;
-            float sum[NCH];
-            float neg_mc;
-            alpha[mb] = 1.0f;
-            if (PART != 2) {
-                float mx = S[mb][0][0];
+            for (int qb = 0; qb < QB; ++qb) {
+                mx[qb] = S[0][qb][0];
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) mx = __builtin_fmaxf(mx, S[mb][kb][i]);
-                mx = xor32_max(mx);
-                const float m_old = m_run[mb];
-                const float m_new = __builtin_fmaxf(m_old, mx);
-                const bool upd = (m_new - m_old) * scale_log2e > RESCALE_LOG2;
-                const float m_use = upd ? m_new : m_old;
-                upd_any |= upd;
-                alpha[mb] = __builtin_amdgcn_exp2f((m_old - m_use) * scale_log2e);
-                neg_mc = -m_use * scale_log2e;
-                m_run[mb] = m_use;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) sum[c] = 0.f;
-            } else {
-                neg_mc = part_negmc[mb];
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) sum[c] = part_sum[mb][c];
+                    for (int i = 0; i < 4; ++i) mx[qb] = __builtin_fmaxf(mx[qb], S[kb][qb][i]);
+                if (!FIRST) over |= __builtin_fmaf(mx[qb], scale_log2e, neg_mc[qb]) > RESCALE_LOG2;
             }
+            if (FIRST) {
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
+                for (int qb = 0; qb < QB; ++qb) {
+                    m_run[qb] = __builtin_fmaxf(m_none, xor32_max(xor16_max(mx[qb])));
+                    neg_mc[qb] = -m_run[qb] * scale_log2e;
+                }
+            } else if (__builtin_amdgcn_ballot_w64(over) != 0) {
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    if ((PART == 1 && kb * 8 + t >= NPAIR / 2) || (PART == 2 && kb * 8 + t < NPAIR / 2)) continue;
-                    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[mb][kb][2 * t], scale_log2e, neg_mc));
-                    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[mb][kb][2 * t + 1], scale_log2e, neg_mc));
+                for (int qb = 0; qb < QB; ++qb) {
+                    const float row_max = xor32_max(xor16_max(mx[qb]));
+                    const bool upd = __builtin_fmaf(row_max, scale_log2e, neg_mc[qb]) > RESCALE_LOG2;
+                    const float m_use = upd ? row_max : m_run[qb];
+                    const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_use) * scale_log2e);
+                    if (__builtin_amdgcn_ballot_w64(upd) == 0) continue;
+                    m_run[qb] = m_use;
+                    neg_mc[qb] = -m_use * scale_log2e;
+                    L[qb] = L[qb] * alpha;
+#pragma unroll
+                    for (int fb = 0; fb < FB; ++fb) O[fb][qb] = O[fb][qb] * alpha;
+                }
+            }
+        }
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            if ((PART == 1 && kb >= KB / 2) || (PART == 2 && kb < KB / 2)) continue;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[kb][qb][2 * t], scale_log2e, neg_mc[qb]));
+                    const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(S[kb][qb][2 * t + 1], scale_log2e, neg_mc[qb]));
                     const unsigned w = E::pack2(p0, p1);
-                    pw[mb][kb * 8 + t] = w;
-                    sum[t % NCH] = E::add_pair(w, sum[t % NCH]);
-                    if (SPREAD && mb == 0 && (kb * 8 + t) % PER == PER / 2) {
+                    pw[kb / 2][qb][kb % 2 * 2 + t] = w;
+                    const int n = (kb * QB + qb) * 2 + t;
+                    if (SPREAD && n % PER == PER / 2) {
                         __builtin_amdgcn_sched_barrier(0);
-                        if (copies) issue_piece_inside(j + 2, (kb * 8 + t) / PER);
+                        if (copies) issue_piece_inside(j + 2, n / PER);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
-            if (PART == 1) {                    // the second half continues these sums with this reference
-                part_negmc[mb] = neg_mc;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) part_sum[mb][c] = sum[c];
-                l_run[mb] = l_run[mb] * alpha[mb];
-            } else {
-                float tile_sum = sum[0];
-#pragma unroll
-                for (int c = 1; c < NCH; ++c) tile_sum += sum[c];
-                l_run[mb] = l_run[mb] * alpha[mb] + tile_sum;
-            }
-        }
-        if (PART != 2 && __builtin_amdgcn_ballot_w64(upd_any) != 0) {
-            // whole-vector multiplies: element-wise updates would make the compiler split the
-            // accumulator tuples into scalars and re-assemble them around every MFMA
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                for (int db = 0; db < DB; ++db) O[mb][db] = O[mb][db] * alpha[mb];
         }
     };
 
@@ -482,22 +489,23 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     char* const st = smem + region;
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-        const float l_tot = xor32_sum(l_run[mb]);
-        const float inv = 1.0f / l_tot;
         const int row0 = ep_wq0 + mb * 32;
-        if (g == 0 && row0 + lr < N && !(KS == 2 && group_b)) lh[row0 + lr] = m_run[mb] * scale + __builtin_logf(l_tot);
+        const float l_row = lg ? L[mb * 2 + 1][0] : L[mb * 2][0], m_row = lg ? m_run[mb * 2 + 1] : m_run[mb * 2];
+        if (lane < 32 && row0 + lane < N && !(KS == 2 && group_b)) lh[row0 + lane] = m_row * scale + __builtin_logf(l_row);
+        const float inv[2] = {1.0f / L[mb * 2][0], 1.0f / L[mb * 2 + 1][0]};
 #pragma unroll
         for (int part = 0; part < D / EPI_F; ++part) {
             if (KS == 2 && (part != 0) != group_b) continue;
             asm volatile("" ::: "memory");      // (order of the LDS accesses: another lane's row is read)
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int db = (part * CH + c) / 4, i4 = c % 4;
-                u32x2 w;
-                w[0] = E::pack2(O[mb][db][i4 * 4 + 0] * inv, O[mb][db][i4 * 4 + 1] * inv);
-                w[1] = E::pack2(O[mb][db][i4 * 4 + 2] * inv, O[mb][db][i4 * 4 + 3] * inv);
-                *reinterpret_cast<u32x2*>(st + lr * (CH * 16) + ((c ^ ((lr / RPB) & (CH - 1))) * 16) + g * 8) = w;
-            }
+            for (int f = 0; f < CH / 2; ++f)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 x = O[part * (CH / 2) + f][mb * 2 + h] * inv[h];
+                    const u32x2 w = {E::pack2(x[0], x[1]), E::pack2(x[2], x[3])};
+                    const int row = h * 16 + lc, c = f * 2 + (lg >> 1);
+                    *reinterpret_cast<u32x2*>(st + row * (CH * 16) + ((c ^ ((row / RPB) & (CH - 1))) * 16) + (lg & 1) * 8) = w;
+                }
             asm volatile("" ::: "memory");
             auto rows_out = [&](auto through) __attribute__((always_inline)) {
 #pragma unroll
@@ -523,40 +531,33 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // prologue (stages -1, 0, 1), else those of the stages nt and nt + 1, which no copy targets; with KS = 2 above the exchange area.
     // ---- KS = 2: O, row sum and reference of this wave become those of all keys, for the half of the features that it
     // stores.  The reference of a wave without any visible key is m_none, its sums are 0.
+    constexpr int XCHG_FLOATS = QB * (FB / 2 * 4 + 2);                   // floats per lane
     auto merge_groups = [&](auto upper) __attribute__((always_inline)) {
-        constexpr int SEND = decltype(upper)::value ? 0 : DB / 2, KEEP = DB / 2 - SEND;   // feature blocks
-        constexpr int FLOATS = DB / 2 * 16 + 2;
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        static_assert(NW * MB * FLOATS * 256 <= STAGES * STAGE_BYTES, "the exchange reuses the ring");
-        char* const mine = smem + wave * (MB * FLOATS * 256);
-        const char* const other = smem + (wave ^ 4) * (MB * FLOATS * 256);
+        constexpr int SEND = decltype(upper)::value ? 0 : FB / 2, KEEP = FB / 2 - SEND;   // feature blocks
+        constexpr int FLOATS = XCHG_FLOATS;
+        static_assert(NW * FLOATS * 256 <= STAGES * STAGE_BYTES, "the exchange reuses the ring");
+        char* const mine = smem + wave * (FLOATS * 256);
+        const char* const other = smem + (wave ^ 4) * (FLOATS * 256);
         __syncthreads();                        // nobody reads the ring any more
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
+        for (int qb = 0; qb < QB; ++qb) {
 #pragma unroll
-            for (int t = 0; t < DB / 2 * 4; ++t) {
-                f32x4 x;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[e] = O[mb][SEND + t / 4][t % 4 * 4 + e];
-                *reinterpret_cast<f32x4*>(mine + (mb * FLOATS * 4 + t * 16) * 64 + lane * 16) = x;
-            }
-            *reinterpret_cast<f32x2*>(mine + (mb * FLOATS + DB / 2 * 16) * 256 + lane * 8) = f32x2{m_run[mb], l_run[mb]};
+            for (int t = 0; t < FB / 2; ++t)
+                *reinterpret_cast<f32x4*>(mine + (qb * (FB / 2) + t) * 1024 + lane * 16) = O[SEND + t][qb];
+            *reinterpret_cast<f32x2*>(mine + QB * (FB / 2) * 1024 + qb * 512 + lane * 8) = f32x2{m_run[qb], L[qb][0]};
         }
         __syncthreads();
 #pragma unroll
-        for (int mb = 0; mb < MB; ++mb) {
-            const f32x2 ml = *reinterpret_cast<const f32x2*>(other + (mb * FLOATS + DB / 2 * 16) * 256 + lane * 8);
-            const float m = __builtin_fmaxf(m_run[mb], ml[0]);
-            const float w0 = __builtin_amdgcn_exp2f((m_run[mb] - m) * scale_log2e), w1 = __builtin_amdgcn_exp2f((ml[0] - m) * scale_log2e);
-            l_run[mb] = l_run[mb] * w0 + ml[1] * w1;
-            m_run[mb] = m;
+        for (int qb = 0; qb < QB; ++qb) {
+            const f32x2 ml = *reinterpret_cast<const f32x2*>(other + QB * (FB / 2) * 1024 + qb * 512 + lane * 8);
+            const float m = __builtin_fmaxf(m_run[qb], ml[0]);
+            const float w0 = __builtin_amdgcn_exp2f((m_run[qb] - m) * scale_log2e), w1 = __builtin_amdgcn_exp2f((ml[0] - m) * scale_log2e);
+            L[qb][0] = L[qb][0] * w0 + ml[1] * w1;
+            m_run[qb] = m;
 #pragma unroll
-            for (int t = 0; t < DB / 2 * 4; ++t) {
-                const f32x4 x = *reinterpret_cast<const f32x4*>(other + (mb * FLOATS * 4 + t * 16) * 64 + lane * 16);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    O[mb][KEEP + t / 4][t % 4 * 4 + e] = O[mb][KEEP + t / 4][t % 4 * 4 + e] * w0 + x[e] * w1;
-                }
+            for (int t = 0; t < FB / 2; ++t) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(other + (qb * (FB / 2) + t) * 1024 + lane * 16);
+                O[KEEP + t][qb] = O[KEEP + t][qb] * w0 + x * w1;
             }
         }
     };
@@ -572,7 +573,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             static_assert(!PERSIST || NW * EPI_BYTES <= STAGE_BYTES, "one free slot");
             region = 2 * STAGE_BYTES + wave * EPI_BYTES;
         } else if (KS == 2) {
-            constexpr int ABOVE = NW * MB * (D / 4 + 2) * 256;        // what merge_groups used
+            constexpr int ABOVE = NW * XCHG_FLOATS * 256;        // what merge_groups used
             static_assert(PERSIST || KS != 2 || ABOVE + NW * EPI_BYTES <= STAGES * STAGE_BYTES, "above the exchange area");
             region = ABOVE + wave * EPI_BYTES;
         } else {
@@ -601,16 +602,17 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // of inside it, where its vmcnt(0) would also wait for the K/V copies issued a moment earlier.
     // (The Q loads were issued after the copies of the prologue, so this wait also covers stages -1, 0, 1.)
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb)
+    for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) asm volatile("" :: "v"(Qf[mb][kk]));
+        for (int kk = 0; kk < KK; ++kk) asm volatile("" :: "v"(Qf[qb][kk]));
     wait_vmcnt<0>();
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-        m_run[mb] = m_none;                     // (see launch)
-        l_run[mb] = 0.f;
+    for (int qb = 0; qb < QB; ++qb) {
+        m_run[qb] = m_none;                     // (see launch)
+        neg_mc[qb] = -m_none * scale_log2e;
+        L[qb] = f32x4(0.f);
 #pragma unroll
-        for (int db = 0; db < DB; ++db) O[mb][db] = f32x16(0.f);
+        for (int fb = 0; fb < FB; ++fb) O[fb][qb] = f32x4(0.f);
     }
     __builtin_amdgcn_s_barrier();               // stages -1, 0, 1 are complete for every wave
 #ifdef ATTN_TIMING
@@ -626,20 +628,20 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         // C_{j+1}; both contractions read stage j.  Its burst falls between those of the first group (right after
         // the barrier) and of the last (after its whole softmax): three bursts per SIMD and tile, back to back.
         mfma_burst(std::false_type{}, std::true_type{}, stage_ptr(-1));                  // T_0
-        softmax_tile(0, std::false_type{}, FIRST_HALF);
+        softmax_tile(0, std::false_type{}, FIRST_HALF, std::true_type{});
         int j = 0;
         if (j + 1 < nt_w) {
             do {                                // bottom-tested: see group A
                 wait_stage(j);
                 if (j + 2 < nt) issue_stage(j + 2);
-                softmax_tile(j, std::false_type{}, SECOND_HALF);
+                softmax_tile(j, std::false_type{}, SECOND_HALF, std::false_type{});
                 mfma_burst(std::true_type{}, std::true_type{}, stage_ptr(j));
-                softmax_tile(j + 1, std::false_type{}, FIRST_HALF);
+                softmax_tile(j + 1, std::false_type{}, FIRST_HALF, std::false_type{});
             } while (++j + 1 < nt_w);
         }
         wait_stage(j);                                                                   // j == nt_w - 1
         if (j + 2 < nt) issue_stage(j + 2);
-        softmax_tile(j, std::false_type{}, SECOND_HALF);
+        softmax_tile(j, std::false_type{}, SECOND_HALF, std::false_type{});
         mfma_burst(std::true_type{}, std::false_type{}, stage_ptr(j));                   // U of the last tile
         for (++j; j < nt; ++j) {                                                         // idle tail of a causal wave
             wait_stage(j);
@@ -650,17 +652,19 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         // group A, iteration j: [U_{j-1}, T_j] then C_j; both contractions read stage j-1
         wait_stage(0);
         mfma_burst(std::false_type{}, std::true_type{}, stage_ptr(-1));                  // T_0
+        fetch_ahead(stage_ptr(0));
         if (2 < nt) issue_stage(2);
-        softmax_tile(0, std::false_type{}, WHOLE);
+        softmax_tile(0, std::false_type{}, WHOLE, std::true_type{});
         auto iter_a = [&](int j, auto spread) __attribute__((always_inline)) {
             TSTAMP(t0);
             wait_stage(j);
             TSTAMP(t1);
             mfma_burst(std::true_type{}, std::true_type{}, stage_ptr(j - 1));
+            fetch_ahead(stage_ptr(j));
             TSTAMP(t2);
             if (!decltype(spread)::value && j + 2 < nt) issue_stage(j + 2);
             TSTAMP(t3);
-            softmax_tile(j, spread, WHOLE);
+            softmax_tile(j, spread, WHOLE, std::false_type{});
             TSTAMP(t4);
             TACC(0, t0, t1); TACC(1, t1, t2); TACC(2, t2, t3); TACC(3, t3, t4);
         };
@@ -703,10 +707,11 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         auto iter_b = [&](int j, auto spread) __attribute__((always_inline)) {
             TSTAMP(t0);
             wait_stage(j);
+            fetch_ahead(stage_ptr(j));
             TSTAMP(t1);
             if (!decltype(spread)::value && j + 2 < nt) issue_stage(j + 2);
             TSTAMP(t2);
-            softmax_tile(j, spread, WHOLE);
+            softmax_tile(j, spread, WHOLE, std::false_type{});
             TSTAMP(t3);
             mfma_burst(std::true_type{}, std::true_type{}, stage_ptr(j));
             TSTAMP(t4);
@@ -725,8 +730,9 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             } while (++j + 1 < nt_w);
         }
         wait_stage(j);                                                                   // j == nt_w - 1
+        fetch_ahead(stage_ptr(j));
         if (j + 2 < nt) issue_stage(j + 2);
-        softmax_tile(j, std::false_type{}, WHOLE);
+        softmax_tile(j, std::false_type{}, WHOLE, std::false_type{});
         mfma_burst(std::true_type{}, std::false_type{}, stage_ptr(j));                   // U of the last tile
         for (++j; j < nt; ++j) {                                                         // idle tail of a causal wave
             wait_stage(j);
@@ -808,16 +814,13 @@ int launch_d(const AttnLaunchArgs& a)
     constexpr int NW = D == 128 ? ATTN_CFG_NW : 8, MB = D == 64 ? ATTN_CFG_MB_D64 : ATTN_CFG_MB, BN = ATTN_CFG_BN, STAGES = ATTN_CFG_STAGES;
     if (splits_keys(D, a.N, (long long)a.B * a.H, a.causal != 0))
         return a.causal ? launch<DTYPE, D, 8, 1, BN, STAGES, true, false, 2>(a) : launch<DTYPE, D, 8, 1, BN, STAGES, false, false, 2>(a);
-    // When the persistent form is used (d = 128 only: at d = 64 two workgroups share a CU and cover each
-    // other's prologue and epilogue, and the next tile's Q fragments would cost the registers that let
-    // them co-reside).  Causal: always; measured +2.5 % at N = 8192 (balanced tile lengths, next
-    // prologue under the epilogue).  Without the mask all tiles are equally long and the hardware's own
-    // dispatch balances as well; the persistent form only pays while a tile is short enough for its
-    // prologue and epilogue to matter, and its main loop compiles slightly looser (-0.3 % at N = 16384).
-    if (D == 128 && ATTN_PERSISTENT) {
-        if (a.causal) return launch<DTYPE, D, NW, MB, BN, STAGES, true, true>(a);
-        if (a.N <= ATTN_PERSIST_NC_MAX_N) return launch<DTYPE, D, NW, MB, BN, STAGES, false, true>(a);
-    }
+    // When the persistent form is used.  d = 128: always; with the mask it balances the tile lengths, and the next prologue
+    // goes on under the epilogue (4 x 16 heads, N = 4096, no mask, bf16: 447.7 -> 445.6 us, N = 16384, 16 heads, fp16 1773 -> 1767;
+    // 16 x 16 heads, N = 512, 43.3 -> 43.4).  d = 64: with the mask (61 -> 58 us at 256 heads, N = 1024); without it two workgroups
+    // share a CU and cover each other's prologue and epilogue, and the next tile's Q fragments would cost the registers that
+    // let them co-reside.
+    if (D == 128 && ATTN_PERSISTENT)
+        return a.causal ? launch<DTYPE, D, NW, MB, BN, STAGES, true, true>(a) : launch<DTYPE, D, NW, MB, BN, STAGES, false, true>(a);
     if (D == 64 && ATTN_PERSISTENT_D64 && a.causal) return launch<DTYPE, D, NW, MB, BN, STAGES, true, true>(a);
     return a.causal ? launch<DTYPE, D, NW, MB, BN, STAGES, true, false>(a) : launch<DTYPE, D, NW, MB, BN, STAGES, false, false>(a);
 }

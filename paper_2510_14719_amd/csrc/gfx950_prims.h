@@ -22,6 +22,7 @@ template <int DTYPE> struct Elem;
 template <> struct Elem<0> {  // IEEE binary16
     typedef _Float16 v8 __attribute__((ext_vector_type(8)));
     typedef _Float16 v2 __attribute__((ext_vector_type(2)));
+    static constexpr short ONE = 0x3c00;        // 1.0
     static __device__ __forceinline__ f32x16 mfma(s16x8 a, s16x8 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
     }
@@ -32,14 +33,9 @@ template <> struct Elem<0> {  // IEEE binary16
         f32x2 x = {lo, hi};
         return __builtin_bit_cast(unsigned, __builtin_convertvector(x, v2));
     }
-    // acc + lo + hi of a packed pair (the rounded values, as the second contraction sees them)
-    static __device__ __forceinline__ float add_pair(unsigned w, float acc) {
-        const v2 one = {(_Float16)1.0f, (_Float16)1.0f};
-        return __builtin_amdgcn_fdot2(__builtin_bit_cast(v2, w), one, acc, false);
-    }
-    // The same update for code that sits between MFMAs of its own wave (the dot instructions go through the matrix
-    // pipe: measured on MI355X, every v_dot2c there stalls the wave's MFMA stream by a dozen cycles).  fp16: the two
-    // unrounded values are added instead; their rounding to fp16 (2^-12 relative, zero mean) is far below what
+    // acc + lo + hi of a packed pair, for code that sits between MFMAs of its own wave (not with v_dot2c: the dot instructions
+    // go through the matrix pipe, measured on MI355X every one there stalls the wave's MFMA stream by a dozen cycles).  fp16: the two
+    // unrounded values are added; their rounding to fp16 (2^-12 relative, zero mean) is far below what
     // the sum is used for.
     static __device__ __forceinline__ float add_pair_valu(unsigned w, float p0, float p1, float acc) {
         (void)w;
@@ -49,6 +45,7 @@ template <> struct Elem<0> {  // IEEE binary16
 template <> struct Elem<1> {  // bfloat16
     typedef __bf16 v8 __attribute__((ext_vector_type(8)));
     typedef __bf16 v2 __attribute__((ext_vector_type(2)));
+    static constexpr short ONE = 0x3f80;        // 1.0
     static __device__ __forceinline__ f32x16 mfma(s16x8 a, s16x8 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8, a), __builtin_bit_cast(v8, b), c, 0, 0, 0);
     }
@@ -58,10 +55,6 @@ template <> struct Elem<1> {  // bfloat16
     static __device__ __forceinline__ unsigned pack2(float lo, float hi) {
         f32x2 x = {lo, hi};
         return __builtin_bit_cast(unsigned, __builtin_convertvector(x, v2));
-    }
-    static __device__ __forceinline__ float add_pair(unsigned w, float acc) {
-        const v2 one = {(__bf16)1.0f, (__bf16)1.0f};
-        return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(v2, w), one, acc, false);
     }
     // bf16: the ROUNDED values are added (a bf16 is the upper half of its fp32: one shift, one mask).  With 8
     // significant bits the rounding matters: normalising by the sum of the rounded probabilities lets the

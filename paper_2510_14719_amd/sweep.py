@@ -32,7 +32,6 @@ What the axes stand for on gfx950:
                                 tile back to back)
   attention  ATTN_FWIN          LDS fragments requested ahead of their MFMA inside a burst (the paper's P)
              ATTN_COPY_GROUP    which waves produce (issue the global -> LDS copies): 0 all, 2 group A, 1 group B
-             ATTN_SUMCHAINS     independent row-sum chains of the softmax
              ATTN_PERSISTENT    persistent launch with the static tile schedule (causal d = 128)
   attn_fp8   ATTN8_FWIN         the same for the 8-bit-float kernel
              ATTN8_INTERLEAVE   softmax of tile j issued in slices between the MFMAs of U_{j-1} and T_{j+1} (1: the
@@ -63,13 +62,13 @@ VARIANT_DIR = os.path.join(HERE, "sweep_variants")
 GRIDS = {
     "attn_schedule": {"ATTN_CFG_PIPE": [0, 1], "ATTNP_CFG_NW": [8, 4], "ATTNP_INTERLEAVE": [1, 0], "ATTNP_FWIN": [3, 2]},
     "attn_waves": {"ATTN_CFG_NW": [8, 12]},
-    "attn": {"ATTN_FWIN": [1, 2, 4, 8], "ATTN_COPY_GROUP": [0, 2, 1], "ATTN_SUMCHAINS": [2, 4]},
+    "attn": {"ATTN_FWIN": [1, 2, 4, 8], "ATTN_COPY_GROUP": [0, 2, 1]},
     "attn_causal": {"ATTN_PERSISTENT": [0, 1], "ATTN_FWIN": [2, 4]},
     "attn_fp8": {"ATTN8_FWIN": [1, 2, 3], "ATTN8_INTERLEAVE": [1, 0], "ATTN8_STAGES": [4, 8], "ATTN8_COPIES_IN_PASS": [1, 0]},
     "gemm": {"GEMM_CONFIG": [0, 1, 2, 3, 4], "GEMM_STAGES": [4, 5], "GEMM_TAIL_READS": [3, 0]},
     "gemm_fp8": {"GEMM8_CONFIG": [0, 1, 2, 3, 4], "GEMM8_STAGES": [4, 5], "GEMM8_TAIL_READS": [3, 0]},
 }
-DEFAULTS = {"ATTN_CFG_NW": 8, "ATTN_CFG_PIPE": 0, "ATTNP_CFG_NW": 8, "ATTNP_INTERLEAVE": 1, "ATTNP_FWIN": 3, "ATTN8_FWIN": 2, "ATTN8_INTERLEAVE": 1, "ATTN8_STAGES": 4, "ATTN8_COPIES_IN_PASS": 1, "ATTN_FWIN": 2, "ATTN_COPY_GROUP": 0, "ATTN_SUMCHAINS": 4, "ATTN_PERSISTENT": 1,
+DEFAULTS = {"ATTN_CFG_NW": 8, "ATTN_CFG_PIPE": 0, "ATTNP_CFG_NW": 8, "ATTNP_INTERLEAVE": 1, "ATTNP_FWIN": 3, "ATTN8_FWIN": 2, "ATTN8_INTERLEAVE": 1, "ATTN8_STAGES": 4, "ATTN8_COPIES_IN_PASS": 1, "ATTN_FWIN": 2, "ATTN_COPY_GROUP": 0, "ATTN_PERSISTENT": 1,
             "GEMM_STAGES": 4, "GEMM_CONFIG": 0, "GEMM_TAIL_READS": 3,
             "GEMM8_STAGES": 4, "GEMM8_TAIL_READS": 3, "GEMM8_COPY_PHASE": 1, "GEMM8_CONFIG": 0}
 
@@ -80,7 +79,7 @@ TEST_VARIANTS = {
                       {"ATTN_CFG_PIPE": 1, "ATTNP_CFG_NW": 8, "ATTNP_INTERLEAVE": 0, "ATTNP_FWIN": 2},
                       {"ATTN_CFG_PIPE": 1, "ATTNP_CFG_NW": 4, "ATTNP_INTERLEAVE": 1, "ATTNP_FWIN": 3}],
     "attn_waves": [{"ATTN_CFG_NW": 12}],
-    "attn": [{"ATTN_FWIN": 4, "ATTN_COPY_GROUP": 2, "ATTN_SUMCHAINS": 2}, {"ATTN_FWIN": 1, "ATTN_COPY_GROUP": 1, "ATTN_SUMCHAINS": 4}],
+    "attn": [{"ATTN_FWIN": 4, "ATTN_COPY_GROUP": 2}, {"ATTN_FWIN": 1, "ATTN_COPY_GROUP": 1}],
     "attn_causal": [{"ATTN_PERSISTENT": 0, "ATTN_FWIN": 2}, {"ATTN_PERSISTENT": 1, "ATTN_FWIN": 4}],
     "attn_fp8": [{"ATTN8_FWIN": 3, "ATTN8_INTERLEAVE": 0, "ATTN8_STAGES": 4, "ATTN8_COPIES_IN_PASS": 1},
                  {"ATTN8_FWIN": 1, "ATTN8_INTERLEAVE": 1, "ATTN8_STAGES": 8, "ATTN8_COPIES_IN_PASS": 0}],

@@ -167,6 +167,35 @@ def test_keys_that_score_minus_infinity(G, oracle, dtype, low, H, N, d, causal):
             G.check(o[sl][:, :, rows], l[sl][:, :, rows], o_ref[:, :, rows], l_ref[:, :, rows], "-inf keys %d..%d head %d" % (first, last, h))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("H", [1, 130])
+def test_a_dominating_key_at_every_place_of_a_tile(G, H, causal, d):
+    # Query i looks at key 64 + i % 64 (its features are a scaled copy of that key's, the key rows being nearly orthogonal sign
+    # patterns): the reference moves in the second tile, through whichever lane holds that key, and O is that key's row of V.
+    # H = 130: 256-row tiles, H = 1: split ones.  Bounds: the score gap is d * gain / sqrt(d) against cross terms
+    # of at most gain * sqrt(d) * 5.5 / sqrt(d) (5.5 standard deviations over the 64 x 447 pairs), so the other keys weigh less than
+    # 512 exp(-gain (sqrt(d) - 5.5)) < 1e-12 and O is V[key] rounded to 16 bits, which it is already: equal.
+    import torch
+    N, gain = 512, 16.0
+    gen = torch.Generator().manual_seed(5)
+    k = torch.where(torch.rand((1, H, N, d), generator=gen) < 0.5, -1.0, 1.0)
+    v = torch.randn((1, H, N, d), generator=gen).to(torch.float16)
+    place = 64 + torch.arange(N) % 64
+    q = k[:, :, place] * gain
+    q, k, v = (x.to(torch.float16).cuda() for x in (q, k, v))
+    print("dominating key H%d d%d causal%d rows%d" % (H, d, causal, G.binding.load_library().attn_fwd_call_rows(1, H, N, d, int(causal))), flush=True)
+    o = torch.full_like(v, float("nan"))
+    lse = torch.full((1, H, N), float("nan"), device="cuda")
+    G.binding.attn_fwd(q, k, v, o, lse, 1, H, N, d, 1.0 / math.sqrt(d), causal)
+    torch.cuda.synchronize()
+    seen = slice(128, N) if causal else slice(0, N)     # rows that see the key in either mask
+    place = place.cuda()
+    assert torch.equal(o[:, :, seen], v[:, :, place][:, :, seen])
+    want = gain * math.sqrt(d)
+    assert (lse[:, :, seen] - want).abs().max().item() <= 1e-5 * want
+
+
 @pytest.mark.parametrize("dtype", [I.FP16, I.BF16])
 def test_large_scores_exercise_rescaling(G, oracle, dtype):
     # scores with |s| up to ~60 and a maximum that keeps moving along the key axis
