@@ -33,7 +33,9 @@
 //  * The row sum comes from the matrix cores as well: next to the D/32 feature blocks of V^T the
 //    second contraction multiplies a block of ones with the same P operand, which yields the sum
 //    of the ROUNDED probabilities of every query row (O is then an exact convex combination of the
-//    V rows) and takes the additions off the vector ALU.
+//    V rows) and takes the additions off the vector ALU.  It is one 16x16x128 MFMA; us with a 32x32x64 one and with this:
+//    4 x 16 heads, N 1024, d 128, causal 22.2 / 20.1, N 4096 277 / 271; 2 x 32 heads, N 8192, causal 591 / 570;
+//    30 heads, N 1023 16.6 / 14.7; d 64 the same (62).
 //  * LDS layouts.  A key row is D bytes, at most one 128-byte memory line, so every copy
 //    instruction fetches whole rows (8 or 16 per instruction, fully coalesced) and both tiles are
 //    row-major in the LDS; only the order of the 16-byte columns inside a row is permuted (which
@@ -263,16 +265,25 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
         }
     }
 
-    // A operand of the ones block: 1.0 in every byte, kept in registers for the whole kernel
+    // A operand of the ones block, 16 x 128 for the 16x16x128 MFMA.  That MFMA takes the P of the 32x32x64 ones as it lies in the
+    // registers: its column c of contraction quarter h (lanes 16 h + c) is query 16 (h & 1) + c, so each column mixes two
+    // queries, told apart by the quarter.  A row therefore holds ones in the even quarters and zeros in the odd ones, or the other way
+    // round, by turns of four rows: a lane's four elements of the result are all the sum of its own query.  (A 32x32x64 block of
+    // ones takes twice the cycles and 16 accumulators instead of 4, which the kernels at d = 128 spilled.)
     i32x8 ones;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        int w = 0x38383838;
+    {
+        int w = ((lane >> 2) & 1) == ((lane >> 4) & 1) ? 0x38383838 : 0;
         asm volatile("" : "+v"(w));
-        ones[t] = w;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            int x = w;
+            asm volatile("" : "+v"(x));
+            ones[t] = x;
+        }
     }
 
-    f32x16 O[DB], L, S[2][KB];                  // L: the ones block of the second contraction = row sums
+    f32x16 O[DB], S[2][KB];
+    f32x4 L;                                    // the ones block of the second contraction: the row sum, four times
     int pw[2][KB * 4] = {};                     // P of two consecutive tiles, four E4M3 values per word
     float m_run;
 
@@ -312,11 +323,11 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     };
 
     // ---- softmax state shared by the slices of one tile
-    float sm_alpha = 1.f, sm_negmc = __builtin_inff();                  // (m_run = -inf: the first tile moves the reference)
+    float sm_alpha = 1.f, sm_negmc = 0.f;
     bool sm_upd = false;                        // some row's reference moved in this tile
     // first slice: (mask,) maximum, and where the reference moves its update and the rescaling factor.  (Exchange and update on every
     // tile took, us: 4 x 16 heads, N 4096, d 128 281 -> 279; N 16384, 16 heads 1025 -> 1010; 256 heads, N 1024, d 64 63.6 -> 61.3,
-    // causal 63.8 -> 61.9.  One chain: 280, 1017, 61.7; four: 285, 1020, 61.6.)
+    // causal 63.8 -> 61.9; one chain instead of two: 280, 1017, 61.7; four: 285, 1020, 61.6.)
     auto softmax_head = [&](auto par, auto masked, int j) __attribute__((always_inline)) {
         constexpr int P = decltype(par)::value;
         if (decltype(masked)::value) {
@@ -339,6 +350,8 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
 #pragma unroll
             for (int i = 0; i < 16; ++i) mc[i / 8] = __builtin_fmaxf(mc[i / 8], S[P][kb][i]);
         const float mx = __builtin_fmaxf(mc[0], mc[1]);
+        sm_negmc = -m_run * scale_log2e;        // (afresh: kept across tiles it costs a register, and so does an old alpha)
+        sm_alpha = __builtin_nondeterministic_value(sm_alpha);
         sm_upd = __builtin_amdgcn_ballot_w64(__builtin_fmaf(mx, scale_log2e, sm_negmc) > RESCALE_LOG2_FP8) != 0;
         if (sm_upd) {
             const float row_max = xor32_max_fp8(mx);
@@ -400,7 +413,6 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
             if (f < NU) {
                 const int kc = f / UB, db = (f % UB) == DB ? -1 : f % UB;
                 if (db >= 0) fr[f] = read_vf(st, kc, db);
-                else fr[f] = ones;
             } else {
                 fr[f] = read_kf(st, (f - NU) % KB, (f - NU) / KB);
             }
@@ -412,7 +424,7 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
 #pragma unroll
                 for (int t = 0; t < 8; ++t) p[t] = pw[P ^ 1][kc * 8 + t];
                 if (db >= 0) O[db] = mfma_fp8(fr[f], p, O[db]);
-                else L = mfma_fp8(fr[f], p, L);
+                else L = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ones, p, L, 0, 0, 0, 0, 0, 0);
             } else {
                 const int kb = (f - NU) % KB, fk = (f - NU) / KB;
                 S[P ^ 1][kb] = mfma_fp8(fr[f], Qf[fk], fk == 0 ? f32x16(0.f) : S[P ^ 1][kb]);
@@ -482,8 +494,8 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
 #pragma unroll
         for (int t = 0; t < 8; ++t) asm volatile("" :: "v"(Qf[fk][t]));
     wait_vmcnt<0>();
-    m_run = -__builtin_inff();
-    L = f32x16(0.f);
+    m_run = -__builtin_inff();                  // (the first tile moves it)
+    L = f32x4(0.f);
 #pragma unroll
     for (int db = 0; db < DB; ++db) O[db] = f32x16(0.f);
     __builtin_amdgcn_s_barrier();               // stages -2 .. 0 are complete for every wave
@@ -613,7 +625,7 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
         const int er = el & 31, eg = el >> 5;
         uint16_t* oh = o + head_off;
         float* lh = lse + (size_t)bh * N;
-        const float l_tot = L[0];               // every element of the ones block holds the row sum
+        const float l_tot = L[0];
         const float inv = 1.0f / l_tot;
         if (eg == 0 && wq0 + er < N && !upper) lh[wq0 + er] = m_run * scale + __builtin_logf(l_tot);
         char* const es = smem + (KS == 2 ? XBYTES + wave * (32 * EPI_F * 2) : ((nt + (wave >> 2)) % STAGES) * STAGE_BYTES + (wave & 3) * (32 * EPI_F * 2));
