@@ -13,11 +13,13 @@ import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libattn_fwd.so")
+FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
 
 FP16 = 0
 BF16 = 1
 
 _lib = None
+_fast = None        # the extension of csrc/fastcall.cpp, once loaded
 
 
 class AttnFwdError(RuntimeError):
@@ -106,6 +108,21 @@ def load_library() -> ctypes.CDLL:
     return _lib
 
 
+def _load_fast():
+    """The extension that makes the plain calls without the interpreter's share (csrc/fastcall.cpp); like the library it has
+    to have been built.  Whatever it does not take (NotImplemented) goes through the general code below."""
+    global _fast
+    if _fast is None:
+        lib = load_library()
+        if not os.path.exists(FASTCALL_PATH):
+            raise ImportError("%s is missing: build it with `python -m paper_2510_14719_amd.build`" % FASTCALL_PATH)
+        from . import _fastcall
+        _fastcall.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.attn_fwd, lib.attn_fwd_fp8, lib.gemm_nt, lib.gemm_nt_fp8)))
+        os.register_at_fork(after_in_child=_fastcall.disable)
+        _fast = _fastcall
+    return _fast
+
+
 def strerror(code: int) -> str:
     return load_library().attn_fwd_strerror(int(code)).decode()
 
@@ -143,15 +160,17 @@ def attn_fwd(q, k, v, o, lse, B, H, N, d, scale, causal, stream=None, dtype=None
     a 16-bit integer view needs an explicit ``dtype``).  Asynchronous: the kernel
     is enqueued on ``stream`` (default: torch's current stream) and the call returns.
     """
-    if dtype is None:
-        import torch
-        if q.dtype == torch.float16:
-            dtype = FP16
-        elif q.dtype == torch.bfloat16:
-            dtype = BF16
-        else:
-            raise ValueError("pass dtype=FP16/BF16 for tensors of type %s" % q.dtype)
-    rc = attn_fwd_raw(q, k, v, o, lse, B, H, N, d, scale, causal, stream, dtype)
+    rc = (_fast or _load_fast()).attn_fwd(q, k, v, o, lse, B, H, N, d, scale, causal, stream, dtype)
+    if rc is NotImplemented:
+        if dtype is None:
+            import torch
+            if q.dtype == torch.float16:
+                dtype = FP16
+            elif q.dtype == torch.bfloat16:
+                dtype = BF16
+            else:
+                raise ValueError("pass dtype=FP16/BF16 for tensors of type %s" % q.dtype)
+        rc = attn_fwd_raw(q, k, v, o, lse, B, H, N, d, scale, causal, stream, dtype)
     if rc != 0:
         raise AttnFwdError(rc, strerror(rc))
 
@@ -181,15 +200,17 @@ def attn_fwd_fp8(q, k, v, o, lse, B, H, N, d, scale, causal, stream=None, out_dt
 
     ``out_dtype`` defaults to the element type of ``o``.  Asynchronous, like ``attn_fwd``.
     """
-    if out_dtype is None:
-        import torch
-        if o.dtype == torch.float16:
-            out_dtype = FP16
-        elif o.dtype == torch.bfloat16:
-            out_dtype = BF16
-        else:
-            raise ValueError("pass out_dtype=FP16/BF16 for an output tensor of type %s" % o.dtype)
-    rc = attn_fwd_fp8_raw(q, k, v, o, lse, B, H, N, d, scale, causal, stream, out_dtype)
+    rc = (_fast or _load_fast()).attn_fwd_fp8(q, k, v, o, lse, B, H, N, d, scale, causal, stream, out_dtype)
+    if rc is NotImplemented:
+        if out_dtype is None:
+            import torch
+            if o.dtype == torch.float16:
+                out_dtype = FP16
+            elif o.dtype == torch.bfloat16:
+                out_dtype = BF16
+            else:
+                raise ValueError("pass out_dtype=FP16/BF16 for an output tensor of type %s" % o.dtype)
+        rc = attn_fwd_fp8_raw(q, k, v, o, lse, B, H, N, d, scale, causal, stream, out_dtype)
     if rc != 0:
         raise AttnFwdError(rc, strerror(rc))
 
@@ -240,15 +261,17 @@ def gemm_nt(a, b, c, M, N, K, stream=None, dtype=None, config=None) -> None:
     ``dtype`` defaults to the element type of ``a``.  Asynchronous: the kernel is enqueued on
     ``stream`` (default: torch's current stream) and the call returns.
     """
-    if dtype is None:
-        import torch
-        if a.dtype == torch.float16:
-            dtype = FP16
-        elif a.dtype == torch.bfloat16:
-            dtype = BF16
-        else:
-            raise ValueError("pass dtype=FP16/BF16 for tensors of type %s" % a.dtype)
-    rc = gemm_nt_raw(a, b, c, M, N, K, stream, dtype, config)
+    rc = (_fast or _load_fast()).gemm_nt(a, b, c, M, N, K, stream, dtype) if config is None else NotImplemented
+    if rc is NotImplemented:
+        if dtype is None:
+            import torch
+            if a.dtype == torch.float16:
+                dtype = FP16
+            elif a.dtype == torch.bfloat16:
+                dtype = BF16
+            else:
+                raise ValueError("pass dtype=FP16/BF16 for tensors of type %s" % a.dtype)
+        rc = gemm_nt_raw(a, b, c, M, N, K, stream, dtype, config)
     if rc != 0:
         raise GemmNtError(rc, load_library().gemm_nt_strerror(rc).decode())
 
@@ -272,7 +295,9 @@ def gemm_nt_fp8(a, b, c, M, N, K, stream=None, out_dtype=FP16, config=None) -> N
     """``gemm_nt_fp8(a, b, c, M, N, K, stream, out_dtype)`` of the C ABI: ``C = A B^T`` for E4M3 bytes
     ``a`` [M,K], ``b`` [N,K] and a 16-bit ``c`` [M,N] of type ``out_dtype``.  Asynchronous.  With ``config``
     the call goes to ``gemm_nt_fp8_config``."""
-    rc = gemm_nt_fp8_raw(a, b, c, M, N, K, stream, out_dtype, config)
+    rc = (_fast or _load_fast()).gemm_nt_fp8(a, b, c, M, N, K, stream, out_dtype) if config is None else NotImplemented
+    if rc is NotImplemented:
+        rc = gemm_nt_fp8_raw(a, b, c, M, N, K, stream, out_dtype, config)
     if rc != 0:
         raise GemmNtError(rc, load_library().gemm_nt_strerror(rc).decode())
 

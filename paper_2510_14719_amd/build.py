@@ -15,12 +15,14 @@ import os
 import re
 import subprocess
 import sys
+import threading
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libattn_fwd.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["attn_fwd_kernel.hip", "attn_fwd_pipe_kernel.hip", "attn_fwd_fp8_kernel.hip", "mfma_probe.hip", "attn_api.cpp",
@@ -58,6 +60,25 @@ def _text_with_includes(path: str, seen=None) -> str:
     return text
 
 
+def build_fastcall(verbose: bool = False, force: bool = False) -> str:
+    """The Python extension of csrc/fastcall.cpp (host code; it reads torch's tensors through torch's C++ headers)."""
+    src = os.path.join(CSRC, "fastcall.cpp")
+    if not force and os.path.exists(FASTCALL) and os.path.getmtime(FASTCALL) > os.path.getmtime(src):
+        return FASTCALL
+    import sysconfig
+    import torch
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    base = os.path.dirname(torch.__file__)
+    tmp = FASTCALL + ".tmp.%d.%d" % (os.getpid(), threading.get_ident())
+    # (the HIP runtime is the one torch has loaded, through libc10_hip)
+    _run([hipcc, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-no-hip-rt", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-x", "c++", src,
+          "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+          "-isystem", os.path.join(os.path.dirname(os.path.dirname(hipcc)), "include"), "-isystem", sysconfig.get_paths()["include"],
+          "-L", os.path.join(base, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-o", tmp], verbose)
+    os.replace(tmp, FASTCALL)
+    return FASTCALL
+
+
 def build(extra_defines=(), out: str = LIB, verbose: bool = False, force: bool = False, jobs: int = 8) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     base = [*HIPCC_FLAGS, "-I", INCLUDE, "-I", CSRC]
@@ -86,8 +107,10 @@ def build(extra_defines=(), out: str = LIB, verbose: bool = False, force: bool =
     if not os.path.exists(inc) or os.path.getmtime(inc) < os.path.getmtime(gen):
         _run([sys.executable, gen, inc], verbose)
 
-    with ThreadPoolExecutor(max_workers=max(1, jobs)) as pool:
+    with ThreadPoolExecutor(max_workers=max(1, jobs) + 1) as pool:
+        fast = pool.submit(build_fastcall, verbose, force)
         objs = list(pool.map(compile_one, SOURCES))
+        fast.result()
     tmp = out + ".tmp.%d" % os.getpid()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp], verbose)
     os.replace(tmp, out)
