@@ -64,8 +64,8 @@ int gemm_nt_f16(const void *a, const void *b, void *c, int M, int N, int K, void
 int gemm_nt_bf16(const void *a, const void *b, void *c, int M, int N, int K, void *stream);
 
 /*
- * The kernels that gemm_nt chooses from, by the tile of C of a workgroup: 0 = 256 x 256, 1 = 64 x 64, 2 = 128 x 128 with
- * two workgroups per compute unit, 3 = 128 x 128 with more waves.  gemm_nt_shape says which one a product takes (-1 for sizes that
+ * The kernels that gemm_nt chooses from, by the tile of C of a workgroup: 0 = 256 x 256, 1 = 64 x 64, or 32 x 32 or
+ * 16 x 16 where that makes few of them, 2 = 128 x 128 with two workgroups per compute unit, 3 = 128 x 128 with more waves.  gemm_nt_shape says which one a product takes (-1 for sizes that
  * no call accepts), gemm_nt_by_shape takes the one the caller names (for tests and measurements): GEMM_NT_ERR_SHAPE for any
  * other value, and for shape 0 with K < 64.
  */

@@ -26,7 +26,8 @@ FASTCALL = os.path.join(HERE, "_fastcall.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["attn_fwd_kernel.hip", "attn_fwd_pipe_kernel.hip", "attn_fwd_fp8_kernel.hip", "mfma_probe.hip", "attn_api.cpp",
-           "gemm_nt_kernel.hip", "gemm_nt_fp8_kernel.hip", "gemm_nt_tile_kernel.hip", "gemm_api.cpp"]
+           "gemm_nt_kernel.hip", "gemm_nt_fp8_kernel.hip", "gemm_nt_tile_kernel.hip", "gemm_nt_narrow_kernel.hip",
+           "gemm_api.cpp"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -20,6 +20,10 @@ int gemm_tile_launch(const GemmLaunchArgs& a, int in_type, int shape);
 // The shape for rows of row_bytes (K elements).
 int gemm_tile_shape(int M, int N, long long row_bytes);
 
+// The smallest tiles of C (gemm_nt_narrow_kernel.hip), which shape 1 takes where gemm_narrow_tile says 32 or 16 and not 0 (64 x 64).
+int gemm_narrow_tile(int M, int N, long long row_bytes, bool fp8);
+int gemm_narrow_launch(const GemmLaunchArgs& a, int in_type, int tile);
+
 // Rows of C per workgroup (0), columns (1), K tile (2), LDS stages (3), threads per workgroup (4).
 int gemm_launch_tile_param(int which);
 

@@ -226,6 +226,19 @@ def test_wide_kernel_ring():
             run_wide_kernel(40, 40, **broken)
 
 
+def test_narrow_kernel_ring():
+    for nk in range(1, 41):
+        run_tile_kernel(nk, nk, 4, 2)
+    src = open(os.path.join(CSRC, "gemm_nt_narrow_kernel.hip")).read()
+    for needle in [
+            "constexpr int NARROW_STAGES = 4;", "NW = 8, PPW = 2, S = NARROW_STAGES;",
+            "for (int s = 0; s < S; ++s)\n        if (s < nk) issue(s);\n    wait_out(min(S - 1, nk - 1));",
+            "if (out == 3) wait_vmcnt<3 * PPW>();\n        else if (out == 2) wait_vmcnt<2 * PPW>();\n        else if (out == 1) wait_vmcnt<1 * PPW>();\n        else wait_vmcnt<0>();",
+            "if (STEADY) wait_vmcnt<(S - 2) * PPW>(); else wait_out(min(S - 2, nk - 2 - j));\n        __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0)\n        ring_barrier();",
+            "if (STEADY || j + S < nk) issue(j + S);", "for (; j + 1 + S < nk; j += 2) {"]:
+        assert needle in src, "gemm_nt_narrow_kernel.hip no longer contains `%s`" % needle
+
+
 def test_default_kernels_spell_out_the_waits_the_model_assumes():
     src = open(os.path.join(CSRC, "gemm_nt_tile_kernel.hip")).read()
     for needle in [

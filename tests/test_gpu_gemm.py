@@ -102,6 +102,49 @@ def test_small_tile_shapes(env, shape, M, N, Ks, dtype):
                   "shape %d M%d N%d K%d" % (shape, M, N, K))
 
 
+# Shape 1's smaller tiles: 16 x 16 (512-byte stages) up to 256 of them, else 32 x 32 (256-byte stages, E4M3 always) up to 256, and two
+# to a CU from 4096-byte rows on (16-bit); beside them 64 x 64 again.  One to six stages around the ring depth of four and more, last
+# stages of every length (multiples of 64 bytes), tiles that overhang by all but one row and column; rows of C on
+# and off 16-byte boundaries, nothing outside C written.
+@pytest.mark.parametrize("kind", ["fp16", "bf16", "e4m3"])
+@pytest.mark.parametrize("M,N,rows", [(1, 1, (64, 512, 2112)), (17, 33, tuple(range(64, 1089, 64)) + (1536, 2048, 2112, 2560, 2624, 3072, 6208)),
+                                      (250, 203, (64, 448, 576, 4160)), (256, 256, (512, 1984)), (33, 8191, (64, 320, 1024)),
+                                      (300, 301, tuple(range(64, 577, 64)) + (768, 832, 1024, 1088, 1280, 1344, 1536, 4032)), (512, 505, (192, 2112)),
+                                      (641, 577, (64, 128, 192, 256, 512, 576, 640, 1408, 4032, 4096, 4160)), (1040, 488, (4096,))])
+def test_smallest_tiles(env, kind, M, N, rows):
+    torch, binding, G = env
+    lib = binding.load_library()
+    f8, dtype = kind == "e4m3", I.BF16 if kind == "bf16" else I.FP16
+    launch, shape_of = (lib.gemm_nt_fp8_by_shape, lib.gemm_nt_fp8_shape) if f8 else (lib.gemm_nt_by_shape, lib.gemm_nt_shape)
+    view = {"fp16": torch.float16, "bf16": torch.bfloat16, "e4m3": torch.float8_e4m3fn}[kind]
+    out = torch.bfloat16 if kind == "bf16" else torch.float16
+    for row_bytes in rows:
+        K = row_bytes if f8 else row_bytes // 2
+        print("case gemm smallest tiles %s M%d N%d K%d" % (kind, M, N, K), flush=True)
+        gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+        a, b = (torch.randn((r, K), generator=gen, device="cuda").to(view) for r in (M, N))
+        buf = torch.full((M * N + 256,), 7.0, dtype=out, device="cuda")
+        skew = (M + K // 32) % 2                 # C on a 256-byte boundary, or one element behind it
+        c = buf[128 + skew:128 + skew + M * N].view(M, N)
+        c.fill_(float("nan"))
+        assert launch(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, torch.cuda.current_stream().cuda_stream, dtype, 1) == 0
+        if f8:                                   # one order of summation in every kernel
+            want = torch.empty((M, N), dtype=out, device="cuda")
+            binding.gemm_nt_fp8(a, b, want, M, N, K, out_dtype=dtype, config=1)
+            assert torch.equal(c, want)
+        else:
+            ref = a.double() @ b.double().T
+            check(c.double().cpu().numpy(), ref.cpu().numpy(), dtype, K, "smallest tiles %s M%d N%d K%d" % (kind, M, N, K))
+        if shape_of(M, N, K) == 1:               # what a plain call takes
+            d = torch.empty((M, N), dtype=out, device="cuda")
+            if f8:
+                binding.gemm_nt_fp8(a, b, d, M, N, K, out_dtype=dtype)
+            else:
+                binding.gemm_nt(a, b, d, M, N, K)
+            assert torch.equal(c, d)
+        assert bool((buf[:128 + skew] == 7.0).all()) and bool((buf[128 + skew + M * N:] == 7.0).all())
+
+
 # The 256 x 256 kernel with whole lines per row, called directly: one to six 128-byte steps (ring of two and a half), with and
 # without a half-filled last one, many steps; tiles that overhang by little and by nearly all.  On E4M3 it
 # adds the k-steps in the order of the fixed configurations, so its results are theirs, bit for bit (16-bit operands take
