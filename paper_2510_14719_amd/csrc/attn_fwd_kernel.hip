@@ -107,20 +107,19 @@ __device__ unsigned long long attn_dbg[DBG_WGS * 8 * DBG_SLOTS];
 #endif
 
 // Exchange with lane^32 (v_permlane32_swap swaps the upper 32 lanes of its first operand with the
-// lower 32 lanes of its second): afterwards `a` holds the lower half's values on every lane and `b`
-// the upper half's, so op(a, b) is the two-lane reduction on all 64 lanes.  Written as inline asm
-// because clang 22 folds the two results of __builtin_amdgcn_permlane32_swap into one
-// (fmax(r[0], r[1]) is compiled as r[0]), which silently drops the partner lane.  The s_nop covers
+// lower 32 lanes of its second).  Written as inline asm because clang 22 folds the two results of __builtin_amdgcn_permlane32_swap into one
+// when both inputs are the same value (fmax(r[0], r[1]) is compiled as r[0]), which silently drops the partner lane.  The s_nop covers
 // the VALU-write -> permlane-read hazard the compiler would otherwise handle.
 __device__ __forceinline__ void swap32(float& a, float& b) {
     asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
-__device__ __forceinline__ float xor32_max(float x) {
-    float a = x, b = x;
-    swap32(a, b);
-    return __builtin_fmaxf(a, b);
+// The lower half's values of x on every lane, and the upper half's.
+__device__ __forceinline__ void both_halves(float x, float& lower, float& upper) {
+    lower = x;
+    upper = x;
+    swap32(lower, upper);
 }
-// The same with lane^16 (v_permlane16_swap: odd rows of 16 lanes of the first operand against even rows of the second).
+// Maximum with lane^16 (v_permlane16_swap: odd rows of 16 lanes of the first operand against even rows of the second).
 __device__ __forceinline__ float xor16_max(float x) {
     float a = x, b = x;
     asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
@@ -415,25 +414,32 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                     for (int i = 0; i < 4; ++i) mx[qb] = __builtin_fmaxf(mx[qb], S[kb][qb][i]);
                 if (!FIRST) over |= __builtin_fmaf(mx[qb], scale_log2e, neg_mc[qb]) > RESCALE_LOG2;
             }
-            if (FIRST) {
+            if (FIRST || __builtin_amdgcn_ballot_w64(over) != 0) {
+                // Two 16-query blocks at a time: after the first exchange the lower half of the wave carries the first, the upper half the second.
+                // (Where keys eight times as long keep moving the reference, 2 x 32 heads, N 8192, causal: 982 us with each block by itself, 947 so.)
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb) {
-                    m_run[qb] = __builtin_fmaxf(m_none, xor32_max(xor16_max(mx[qb])));
-                    neg_mc[qb] = -m_run[qb] * scale_log2e;
-                }
-            } else if (__builtin_amdgcn_ballot_w64(over) != 0) {
+                for (int mb = 0; mb < MB; ++mb) {
+                    float &m0 = m_run[2 * mb], &m1 = m_run[2 * mb + 1];
+                    float a = mx[2 * mb], b = mx[2 * mb + 1];
+                    swap32(a, b);
+                    const float row_max = xor16_max(__builtin_fmaxf(a, b));
+                    const float m_old = lane < 32 ? m0 : m1;
+                    const bool moves = FIRST ? row_max > m_none : __builtin_fmaf(row_max, scale_log2e, lane < 32 ? neg_mc[2 * mb] : neg_mc[2 * mb + 1]) > RESCALE_LOG2;
+                    const float m_use = moves ? row_max : m_old;
+                    both_halves(m_use, m0, m1);
+                    neg_mc[2 * mb] = -m0 * scale_log2e;
+                    neg_mc[2 * mb + 1] = -m1 * scale_log2e;
+                    if (FIRST) continue;
+                    float alpha[2];
+                    both_halves(__builtin_amdgcn_exp2f((m_old - m_use) * scale_log2e), alpha[0], alpha[1]);
+                    const unsigned long long moved = __builtin_amdgcn_ballot_w64(moves);
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb) {
-                    const float row_max = xor32_max(xor16_max(mx[qb]));
-                    const bool upd = __builtin_fmaf(row_max, scale_log2e, neg_mc[qb]) > RESCALE_LOG2;
-                    const float m_use = upd ? row_max : m_run[qb];
-                    const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_use) * scale_log2e);
-                    if (__builtin_amdgcn_ballot_w64(upd) == 0) continue;
-                    m_run[qb] = m_use;
-                    neg_mc[qb] = -m_use * scale_log2e;
-                    L[qb] = L[qb] * alpha;
+                    for (int h = 0; h < 2; ++h) {
+                        if ((unsigned)(moved >> (32 * h)) == 0) continue;
+                        L[2 * mb + h] = L[2 * mb + h] * alpha[h];
 #pragma unroll
-                    for (int fb = 0; fb < FB; ++fb) O[fb][qb] = O[fb][qb] * alpha;
+                        for (int fb = 0; fb < FB; ++fb) O[fb][2 * mb + h] = O[fb][2 * mb + h] * alpha[h];
+                    }
                 }
             }
         }
