@@ -114,13 +114,13 @@ __device__ __forceinline__ f32x16 mfma_fp8(i32x8 a, i32x8 b, f32x16 c) {
 }
 
 __device__ __forceinline__ float xor32_max_fp8(float x) {
-    // v_permlane32_swap swaps the upper 32 lanes of its first operand with the lower 32 lanes of its
+    // (NaN if either is.)  v_permlane32_swap swaps the upper 32 lanes of its first operand with the lower 32 lanes of its
     // second: afterwards a holds the lower half's value on every lane and b the upper half's.
     // (inline asm: the compiler folds the two results of the builtin into one when both inputs are
     // the same value; the s_nop covers the VALU-write -> permlane-read hazard)
     float a = x, b = x;
     asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-    return __builtin_fmaxf(a, b);
+    return __builtin_elementwise_maximum(a, b);
 }
 
 // KS = 2 (few tiles): a workgroup covers 128 query rows, a stage holds KS * BN keys, and the waves w and w + 4 work on
@@ -270,6 +270,7 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
     // queries, told apart by the quarter.  A row therefore holds ones in the even quarters and zeros in the odd ones, or the other way
     // round, by turns of four rows: a lane's four elements of the result are all the sum of its own query.  (A 32x32x64 block of
     // ones takes twice the cycles and 16 accumulators instead of 4, which the kernels at d = 128 spilled.)
+    // The zeros only keep the other query out while its P is a number (0 x NaN is NaN), so no P is ever NaN: see softmax_head.
     i32x8 ones;
     {
         int w = ((lane >> 2) & 1) == ((lane >> 4) & 1) ? 0x38383838 : 0;
@@ -344,20 +345,28 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
         }
         // The maximum of the lane's own keys (two chains), compared with the reference right away: some lane of a row exceeds the
         // limit exactly when the row does, so the lane exchange and the new reference are only needed when it moves.
+        // The maximum is the one that passes NaN on (v_maximum3_f32, as fast as v_max3_f32), and the comparison takes it into the
+        // branch: a row with a NaN score becomes NaN by its rescaling factor and has no P of its own (softmax_rescale), since a NaN among the P
+        // would reach the row sum of the query 16 rows away.
         float mc[2] = {S[P][0][0], S[P][0][8]};
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) mc[i / 8] = __builtin_fmaxf(mc[i / 8], S[P][kb][i]);
-        const float mx = __builtin_fmaxf(mc[0], mc[1]);
+            for (int i = 0; i < 16; ++i) mc[i / 8] = __builtin_elementwise_maximum(mc[i / 8], S[P][kb][i]);
+        const float mx = __builtin_elementwise_maximum(mc[0], mc[1]);
         sm_negmc = -m_run * scale_log2e;        // (afresh: kept across tiles it costs a register, and so does an old alpha)
         sm_alpha = __builtin_nondeterministic_value(sm_alpha);
-        sm_upd = __builtin_amdgcn_ballot_w64(__builtin_fmaf(mx, scale_log2e, sm_negmc) > RESCALE_LOG2_FP8) != 0;
+        sm_upd = __builtin_amdgcn_ballot_w64(!(__builtin_fmaf(mx, scale_log2e, sm_negmc) <= RESCALE_LOG2_FP8)) != 0;
         if (sm_upd) {
             const float row_max = xor32_max_fp8(mx);
             const bool moves = __builtin_fmaf(row_max, scale_log2e, sm_negmc) > RESCALE_LOG2_FP8;
-            const float m_use = moves ? row_max : m_run;
+            float m_use = moves ? row_max : m_run;
             sm_alpha = __builtin_amdgcn_exp2f((m_run - m_use) * scale_log2e);
+            // (a reference beyond the range of the scaled scores would make the probabilities infinite)
+            if (!(row_max == row_max && -m_use * scale_log2e < __builtin_inff())) {
+                m_use = 0.f;
+                sm_alpha = __builtin_nanf("");
+            }
             sm_negmc = -m_use * scale_log2e;
             m_run = m_use;
         }
@@ -379,12 +388,15 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
         asm volatile("" : "+v"(w));
         pw[P][kb * 4 + t] = w;
     };
-    // after the U of the previous tile: move O and L to the new reference (rare after the first tiles)
-    auto softmax_rescale = [&]() __attribute__((always_inline)) {
+    // after the U of the previous tile: move O and L to the new reference (rare after the first tiles), or to NaN
+    auto softmax_rescale = [&](auto par) __attribute__((always_inline)) {
+        constexpr int P = decltype(par)::value;
         if (sm_upd) {
 #pragma unroll
             for (int db = 0; db < DB; ++db) O[db] = O[db] * sm_alpha;
             L = L * sm_alpha;
+#pragma unroll
+            for (int w = 0; w < KB * 4; ++w) pw[P][w] = sm_alpha == sm_alpha ? pw[P][w] : 0;
         }
     };
 
@@ -464,7 +476,7 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
 #pragma unroll
             for (int s = 0; s < NG; ++s) softmax_group(par, s);
         }
-        if (C) softmax_rescale();
+        if (C) softmax_rescale(par);
     };
 
     // Barrier j: every wave's share of the stages up to j has landed (the copies of the stages after
@@ -559,7 +571,7 @@ void attn_fwd_fp8_kernel(const uint8_t* __restrict__ q, const uint8_t* __restric
             softmax_group(par, s);
             __builtin_amdgcn_sched_barrier(0);
         }
-        softmax_rescale();
+        softmax_rescale(par);
         pass(Y, NO, NO, NO, parx, stage_ptr(j), j + 1);                 // U_j
     };
     if (j & 1) tail(P1, P0); else tail(P0, P1);

@@ -239,6 +239,47 @@ def test_large_scores_exercise_rescaling(G, oracle):
         _full(G, oracle, B, H, N, d, causal, seed=0, scale=0.3, what="large-scores", qkv=(q, k, v))
 
 
+# A NaN stays in its row: a NaN query spoils its own row of O and LSE, a NaN key the rows that see it, and every other row is what it
+# is without the NaN, bit for bit.  Whole and split tiles; NaN in the first tile of a row and in the last, in both halves of a wave's 32 rows.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,N,rows", [(3, 333, 128), (300, 577, 256)])
+def test_nan_stays_in_its_rows(G, oracle, H, N, rows, d, causal):
+    from paper_2510_14719_amd import binding
+    assert binding.load_library().attn_fwd_fp8_call_rows(1, H, N, d, causal) == rows
+    q, k, v = I.make_qkv(1, H, N, d, E4M3, 1900 + N + d)
+    scale, nan = 1.0 / math.sqrt(d), 0x7F
+    o0, l0 = G.run_gpu_fp8(q, k, v, I.FP16, scale, causal)
+    assert np.isfinite(o0).all() and np.isfinite(l0).all()
+    places = [(0, 20), (0, 37), (0, N - 1), (1, 0), (H - 1, 131), (H - 1, N - 5)]
+    for what in ("query", "key"):
+        x = (q if what == "query" else k).copy()
+        seen = np.zeros((1, H, N), dtype=bool)           # rows that meet a NaN
+        for h, i in places:
+            if what == "key" and (h, i) not in ((0, 37), (H - 1, N - 5)): continue
+            x[0, h, i, (5 * i) % d] = nan
+            if what == "query": seen[0, h, i] = True
+            else: seen[0, h, i if causal else 0:] = True
+        print("case fp8 NaN %s H%d N%d d%d causal%d" % (what, H, N, d, causal), flush=True)
+        o, l = G.run_gpu_fp8(*((x, k, v) if what == "query" else (q, x, v)), I.FP16, scale, causal)
+        sl = (slice(0, 1), slice(0, 1))
+        o_ref, _ = oracle.attn_ref(*(np.ascontiguousarray(y[sl]) for y in ((x, k, v) if what == "query" else (q, x, v))), E4M3, scale, causal)
+        assert np.array_equal(np.isnan(o_ref).all(-1), seen[sl]) and np.array_equal(np.isnan(o_ref).any(-1), seen[sl])
+        assert np.array_equal(np.isnan(o).all(-1), seen) and np.array_equal(np.isnan(l), seen)
+        assert np.array_equal(o[~seen], o0[~seen]) and np.array_equal(l[~seen], l0[~seen])
+
+
+def test_a_row_beyond_the_range_of_the_scaled_scores_stays_by_itself(G):
+    # query 20: scores of -128 whose scaled value is beyond fp32; the others: scores of 0, whose O is the mean of V
+    N, d = 64, 64
+    q = np.zeros((1, 1, N, d), dtype=np.float32)
+    q[0, 0, 20] = -2.0
+    k, v = np.ones((1, 1, N, d), dtype=np.float32), np.full((1, 1, N, d), 3.0, dtype=np.float32)
+    o, l = G.run_gpu_fp8(*(I.f32_to_e4m3_bits(x) for x in (q, k, v)), I.FP16, 1e37, False)
+    others = np.arange(N) != 20
+    assert (o[0, 0, others] == 3.0).all() and np.abs(l[0, 0, others] - math.log(N)).max() < 1e-5
+
+
 def test_repeat_runs_are_bit_identical(G):
     q, k, v = I.make_qkv(1, 3, 900, 128, E4M3, 198)
     o1, l1 = G.run_gpu_fp8(q, k, v, I.BF16, 0.1, True)

@@ -167,6 +167,35 @@ def test_keys_that_score_minus_infinity(G, oracle, dtype, low, H, N, d, causal):
             G.check(o[sl][:, :, rows], l[sl][:, :, rows], o_ref[:, :, rows], l_ref[:, :, rows], "-inf keys %d..%d head %d" % (first, last, h))
 
 
+# A NaN query spoils its own row of O and LSE, a NaN key the rows that see it; every other row is what it is without the NaN, bit for bit.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,N,rows", [(3, 333, 128), (300, 577, 256)])
+def test_nan_stays_in_its_rows(G, oracle, H, N, rows, d, causal):
+    from paper_2510_14719_amd import binding
+    assert binding.load_library().attn_fwd_call_rows(1, H, N, d, causal) == rows
+    dtype = I.BF16 if d == 64 else I.FP16
+    q, k, v = I.make_qkv(1, H, N, d, dtype, 2400 + N + d)
+    scale, nan = 1.0 / math.sqrt(d), 0x7FC0 if dtype == I.BF16 else 0x7E00
+    o0, l0 = G.run_gpu(q, k, v, dtype, scale, causal)
+    places = [(0, 20), (0, 37), (0, N - 1), (1, 0), (H - 1, 131), (H - 1, N - 5)]
+    for what in ("query", "key"):
+        x = (q if what == "query" else k).copy()
+        seen = np.zeros((1, H, N), dtype=bool)           # rows that meet a NaN
+        for h, i in places:
+            if what == "key" and (h, i) not in ((0, 37), (H - 1, N - 5)): continue
+            x[0, h, i, (5 * i) % d] = nan
+            if what == "query": seen[0, h, i] = True
+            else: seen[0, h, i if causal else 0:] = True
+        print("case NaN %s H%d N%d d%d causal%d" % (what, H, N, d, causal), flush=True)
+        o, l = G.run_gpu(*((x, k, v) if what == "query" else (q, x, v)), dtype, scale, causal)
+        sl = (slice(0, 1), slice(0, 1))
+        o_ref, _ = oracle.attn_ref(*(np.ascontiguousarray(y[sl]) for y in ((x, k, v) if what == "query" else (q, x, v))), dtype, scale, causal)
+        assert np.array_equal(np.isnan(o_ref).all(-1), seen[sl]) and np.array_equal(np.isnan(o_ref).any(-1), seen[sl])
+        assert np.array_equal(np.isnan(o).all(-1), seen) and np.array_equal(np.isnan(l), seen)
+        assert np.array_equal(o[~seen], o0[~seen]) and np.array_equal(l[~seen], l0[~seen])
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("H", [1, 130])
