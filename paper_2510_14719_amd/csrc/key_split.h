@@ -28,6 +28,10 @@
 
 #include "tile_schedule.h"                      // CHIP_CUS
 
+// A grid has less than 2^32 threads in a dimension, 512 per split tile.  Whole tiles under the mask at d = 64 are persistent and so
+// know no such limit: beyond it the calls are theirs.
+constexpr long long MAX_SPLIT_TILES = (1ll << 32) / 512 - 1;
+
 // heads = batch size x heads.
 inline bool attn_splits_keys(int d, int N, long long heads, bool causal, bool fp8)
 {
@@ -36,6 +40,7 @@ inline bool attn_splits_keys(int d, int N, long long heads, bool causal, bool fp
     // split tiles at `cost` of a whole one each
     auto fewer_rounds = [&](double cost) { return cost * rounds(split, CHIP_CUS) < 0.97 * rounds(whole, CHIP_CUS); };
 
+    if (split > MAX_SPLIT_TILES) return false;
     if (split <= CHIP_CUS) {
         if (!fp8) return true;
         if (d == 64) return N > 128;                                     // (a stage holds 128 keys)

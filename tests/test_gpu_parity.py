@@ -295,6 +295,22 @@ def test_large_scores_with_many_heads(G, oracle, causal, d):
         G.check(o[sl], l[sl], o_ref, l_ref, "large-scores head %d" % h, tol_o_max=4e-2, tol_lse=2e-2)
 
 
+def test_more_heads_than_a_grid_has_workgroups(G):
+    # 2^23 rows of one token: a grid of that many workgroups of 512 threads would be too large.  O is V, LSE the one score.
+    import torch
+    H, d = 2 ** 23, 64
+    print("case one token, 2^23 heads, causal", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v = (torch.randn((1, H, 1, d), generator=gen, device="cuda", dtype=torch.float16) for _ in range(3))
+    o = torch.full_like(v, float("nan"))
+    lse = torch.full((1, H, 1), float("nan"), device="cuda")
+    G.binding.attn_fwd(q, k, v, o, lse, 1, H, 1, d, 0.125, True)
+    torch.cuda.synchronize()
+    assert torch.equal(o, v)
+    # (sums of 64 products of N(0,1) values in fp32, |score| < 10)
+    assert (lse[0, :, 0] - (q[0, :, 0].float() * k[0, :, 0].float()).sum(-1) * 0.125).abs().max().item() < 1e-4
+
+
 def test_score_shift_moves_lse_only(G):
     B, H, N, d = 1, 1, 512, 64
     scale, c = 0.125, 24.0

@@ -60,6 +60,17 @@ def test_the_faster_form_is_taken(lib, d, N, heads, causal, fp8, whole, split):
     assert (split if rows == 128 else whole) <= 1.03 * min(whole, split)
 
 
+def test_whole_tiles_beyond_the_largest_grid(lib):
+    # one workgroup of 512 threads per split tile, less than 2^32 threads in a grid: whole tiles (persistent at d = 64 under the mask) take
+    # what is larger, whatever the rule says of speed
+    most = 2 ** 32 // 512 - 1
+    for N, tiles in ((1, 1), (66, 1), (130, 2)):
+        for f in (lib.attn_fwd_call_rows, lib.attn_fwd_fp8_call_rows):
+            for causal in (0, 1):
+                assert f(1, most // tiles + 1, N, 64, causal) == 256 and f(1, most // tiles + 1, N, 128, causal) == 256
+        assert lib.attn_fwd_call_rows(1, most // tiles, N, 64, 1) == 128
+
+
 def test_heads_count_over_the_batch_and_sizes_are_checked(lib):
     for f in (lib.attn_fwd_call_rows, lib.attn_fwd_fp8_call_rows):
         assert f(4, 2, 7424, 128, 1) == f(1, 8, 7424, 128, 1) == 128
