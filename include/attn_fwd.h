@@ -136,6 +136,16 @@ int attn_fwd_call_rows(int B, int H, int N, int d, int causal);
 int attn_fwd_fp8_call_rows(int B, int H, int N, int d, int causal);
 
 /*
+ * attn_fwd and attn_fwd_fp8 with the kernel named by its query rows per workgroup, 128 or those of attn_fwd_tile_param (256 for
+ * attn_fwd_fp8), for tests and measurements: ATTN_FWD_ERR_SHAPE for any other value, ATTN_FWD_ERR_OVERFLOW where 128 rows would take more
+ * workgroups than a grid can have.
+ */
+int attn_fwd_by_rows(const void *q, const void *k, const void *v, void *o, float *lse,
+                     int B, int H, int N, int d, float scale, int causal, void *stream, int dtype, int rows);
+int attn_fwd_fp8_by_rows(const void *q, const void *k, const void *v, void *o, float *lse,
+                         int B, int H, int N, int d, float scale, int causal, void *stream, int out_dtype, int rows);
+
+/*
  * The static tile schedule of the launch (host-side copy of what the kernel evaluates; the paper's
  * Section 4.2 describes persistent kernels that walk a tile queue).  A launch covers `total` logical
  * tiles (logical tile t = (batch*head t / nqt, query tile t % nqt), nqt = ceil(N / attn_fwd_call_rows); under the

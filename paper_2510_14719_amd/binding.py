@@ -66,6 +66,9 @@ def load_library() -> ctypes.CDLL:
         for rows in (lib.attn_fwd_call_rows, lib.attn_fwd_fp8_call_rows):
             rows.restype = ci
             rows.argtypes = [ci, ci, ci, ci, ci]
+        for by_rows in (lib.attn_fwd_by_rows, lib.attn_fwd_fp8_by_rows):
+            by_rows.restype = ci
+            by_rows.argtypes = common + [ci, ci]
         lib.attn_fwd_tile_schedule.restype = ci
         lib.attn_fwd_tile_schedule.argtypes = [ci, ci, ci, ci]
         lib.attn_fwd_mfma_probe.restype = ci

@@ -7,6 +7,7 @@
 #include <cstdint>
 
 #include "attn_launch.h"
+#include "key_split.h"
 #include "tile_schedule.h"
 
 namespace {
@@ -55,6 +56,17 @@ int attn_fwd(const void* q, const void* k, const void* v, void* o, float* lse,
     return attn_launch(a) == 0 ? ATTN_FWD_OK : ATTN_FWD_ERR_LAUNCH;
 }
 
+int attn_fwd_by_rows(const void* q, const void* k, const void* v, void* o, float* lse,
+                     int B, int H, int N, int d, float scale, int causal, void* stream, int dtype, int rows)
+{
+    const int rc = attn_fwd_check_args(q, k, v, o, lse, B, H, N, d, scale, dtype);
+    if (rc != ATTN_FWD_OK) return rc;
+    if (!attn_launch_has_rows(d, causal != 0, rows)) return ATTN_FWD_ERR_SHAPE;
+    if (rows == 128 && (N + 127LL) / 128 * B * H > MAX_SPLIT_TILES) return ATTN_FWD_ERR_OVERFLOW;
+    AttnLaunchArgs a{q, k, v, o, lse, B, H, N, d, scale, causal != 0, dtype, stream, rows};
+    return attn_launch(a) == 0 ? ATTN_FWD_OK : ATTN_FWD_ERR_LAUNCH;
+}
+
 int attn_fwd_f16(const void* q, const void* k, const void* v, void* o, float* lse,
                  int B, int H, int N, int d, float scale, int causal, void* stream)
 {
@@ -99,6 +111,17 @@ int attn_fwd_fp8(const void* q, const void* k, const void* v, void* o, float* ls
     const int rc = attn_fwd_fp8_check_args(q, k, v, o, lse, B, H, N, d, scale, out_dtype);
     if (rc != ATTN_FWD_OK) return rc;
     AttnLaunchArgs a{q, k, v, o, lse, B, H, N, d, scale, causal != 0, out_dtype, stream};
+    return attn_fp8_launch(a) == 0 ? ATTN_FWD_OK : ATTN_FWD_ERR_LAUNCH;
+}
+
+int attn_fwd_fp8_by_rows(const void* q, const void* k, const void* v, void* o, float* lse,
+                         int B, int H, int N, int d, float scale, int causal, void* stream, int out_dtype, int rows)
+{
+    const int rc = attn_fwd_fp8_check_args(q, k, v, o, lse, B, H, N, d, scale, out_dtype);
+    if (rc != ATTN_FWD_OK) return rc;
+    if (!attn_fp8_launch_has_rows(d, rows)) return ATTN_FWD_ERR_SHAPE;
+    if (rows == 128 && (N + 127LL) / 128 * B * H > MAX_SPLIT_TILES) return ATTN_FWD_ERR_OVERFLOW;
+    AttnLaunchArgs a{q, k, v, o, lse, B, H, N, d, scale, causal != 0, out_dtype, stream, rows};
     return attn_fp8_launch(a) == 0 ? ATTN_FWD_OK : ATTN_FWD_ERR_LAUNCH;
 }
 

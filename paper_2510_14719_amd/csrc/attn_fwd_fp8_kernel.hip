@@ -732,7 +732,7 @@ int launch_fp8_d(const AttnLaunchArgs& a)
     constexpr int BN = D == 128 ? ATTN8_CFG_BN_D128 : ATTN8_CFG_BN_D64;
     // (A step of split tiles takes 0.91 us for 128 keys, one of whole tiles 0.83 us for 64, at d = 128.)
     if constexpr (HAS_SPLIT<D>) {
-        if (attn_splits_keys(D, a.N, (long long)a.B * a.H, a.causal != 0, true))
+        if (a.rows ? a.rows == 128 : attn_splits_keys(D, a.N, (long long)a.B * a.H, a.causal != 0, true))
             return a.causal ? launch_fp8<OUT, D, BN, true, false, 2>(a) : launch_fp8<OUT, D, BN, false, false, 2>(a);
     }
     if (a.causal) return ATTN8_PERSISTENT ? launch_fp8<OUT, D, BN, true, true>(a) : launch_fp8<OUT, D, BN, true, false>(a);
@@ -752,6 +752,8 @@ int attn_fp8_launch_call_rows(int d, int N, long long heads, int causal)
 {
     return (d == 128 ? HAS_SPLIT<128> : HAS_SPLIT<64>) && attn_splits_keys(d, N, heads, causal != 0, true) ? 128 : 256;
 }
+
+bool attn_fp8_launch_has_rows(int d, int rows) { return rows == 256 || (rows == 128 && (d == 128 ? HAS_SPLIT<128> : HAS_SPLIT<64>)); }
 
 int attn_fp8_launch_tile_param(int d, int which)
 {

@@ -808,17 +808,15 @@ int launch(const AttnLaunchArgs& a)
     return e == hipSuccess ? 0 : -1;
 }
 
-// The rule, where this build has the form.
-bool splits_keys(int d, int N, long long heads, bool causal)
-{
-    return ATTN_KEY_SPLIT && (d == 64 || ATTN_CFG_NW == 8) && ATTN_CFG_STAGES == 4 && attn_splits_keys(d, N, heads, causal, false);
-}
+// Whether this build has the form that splits keys, and the rule.
+constexpr bool has_split(int d) { return ATTN_KEY_SPLIT && (d == 64 || ATTN_CFG_NW == 8) && ATTN_CFG_STAGES == 4 && !(ATTN_CFG_PIPE && d == 128); }
+bool splits_keys(int d, int N, long long heads, bool causal) { return has_split(d) && attn_splits_keys(d, N, heads, causal, false); }
 
 template <int DTYPE, int D>
 int launch_d(const AttnLaunchArgs& a)
 {
     constexpr int NW = D == 128 ? ATTN_CFG_NW : 8, MB = D == 64 ? ATTN_CFG_MB_D64 : ATTN_CFG_MB, BN = ATTN_CFG_BN, STAGES = ATTN_CFG_STAGES;
-    if (splits_keys(D, a.N, (long long)a.B * a.H, a.causal != 0))
+    if (a.rows ? a.rows == 128 : splits_keys(D, a.N, (long long)a.B * a.H, a.causal != 0))
         return a.causal ? launch<DTYPE, D, 8, 1, BN, STAGES, true, false, 2>(a) : launch<DTYPE, D, 8, 1, BN, STAGES, false, false, 2>(a);
     // When the persistent form is used.  d = 128: always; with the mask it balances the tile lengths, and the next prologue
     // goes on under the epilogue (4 x 16 heads, N = 4096, no mask, bf16: 447.7 -> 445.6 us, N = 16384, 16 heads, fp16 1773 -> 1767;
@@ -849,9 +847,11 @@ extern "C" int attn_dbg_read(unsigned long long* host, int n)
 
 int attn_launch_call_rows(int d, int N, long long heads, int causal)
 {
-    if (!(ATTN_CFG_PIPE && d == 128) && splits_keys(d, N, heads, causal != 0)) return 128;
+    if (splits_keys(d, N, heads, causal != 0)) return 128;
     return attn_launch_tile_param(d, causal, 0);
 }
+
+bool attn_launch_has_rows(int d, int causal, int rows) { return rows == attn_launch_tile_param(d, causal, 0) || (rows == 128 && has_split(d)); }
 
 int attn_launch_tile_param(int d, int causal, int which)
 {

@@ -53,6 +53,7 @@ struct AttnLaunchArgs {
     int causal;
     int dtype;      // 0 = fp16, 1 = bf16 (16-bit kernels: of Q, K, V and O; 8-bit-float kernel: of O)
     void* stream;   // hipStream_t
+    int rows = 0;   // query rows per workgroup; 0 = chosen by the sizes
 };
 
 // Enqueue the kernel for already-validated arguments.  0 on success, -1 if HIP refused the launch.
@@ -61,8 +62,9 @@ int attn_launch(const AttnLaunchArgs& a);
 // Query rows per workgroup (0), keys per tile (1), LDS stages (2), threads per workgroup (3).
 int attn_launch_tile_param(int d, int causal, int which);
 
-// Query rows per workgroup of the kernel that a call takes.
+// Query rows per workgroup of the kernel that a call takes, and whether there is one with that many.
 int attn_launch_call_rows(int d, int N, long long heads, int causal);
+bool attn_launch_has_rows(int d, int causal, int rows);
 
 // The in-wave pipelined kernel (attn_fwd_pipe_kernel.hip), d = 128 only; same contract as attn_launch.
 int attn_pipe_launch(const AttnLaunchArgs& a);
@@ -72,6 +74,7 @@ int attn_fp8_launch(const AttnLaunchArgs& a);
 // Query rows per workgroup (0), keys per tile (1), LDS stages (2), threads per workgroup (3).
 int attn_fp8_launch_tile_param(int d, int which);
 int attn_fp8_launch_call_rows(int d, int N, long long heads, int causal);
+bool attn_fp8_launch_has_rows(int d, int rows);
 
 // Register-only MFMA stream (mfma_probe.hip): `workgroups` workgroups of mfma_probe_threads() threads,
 // every wave issuing iters * 8 MFMAs of the given element type; one float per thread is written to sink.

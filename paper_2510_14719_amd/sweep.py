@@ -152,6 +152,9 @@ def _load(path):
     lib.attn_fwd.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, cf, ci, vp, ci]
     lib.attn_fwd_fp8.restype = ci
     lib.attn_fwd_fp8.argtypes = [vp, vp, vp, vp, vp, ci, ci, ci, ci, cf, ci, vp, ci]
+    for by_rows in (lib.attn_fwd_by_rows, lib.attn_fwd_fp8_by_rows):
+        by_rows.restype = ci
+        by_rows.argtypes = lib.attn_fwd.argtypes + [ci]
     lib.gemm_nt.restype = ci
     lib.gemm_nt.argtypes = [vp, vp, vp, ci, ci, ci, vp, ci]
     lib.gemm_nt_fp8.restype = ci

@@ -43,7 +43,15 @@ def check_guards(obuf, lbuf, n_o: int, n_l: int, pad: int):
     assert bool((li[:pad] == LSE_FILL_BITS).all()) and bool((li[pad + n_l:] == LSE_FILL_BITS).all()), "LSE guard words overwritten"
 
 
-def run_gpu(q, k, v, dtype, scale, causal, guard=True):
+def _launch(call, by_rows, q, k, v, o, lse, sizes, scale, causal, dtype, rows):
+    """The plain call of the binding, or with ``rows`` the kernel of that many query rows per workgroup."""
+    if rows is None:
+        call(q, k, v, o, lse, *sizes, scale, causal, None, dtype)
+    else:
+        assert by_rows(*(x.data_ptr() for x in (q, k, v, o, lse)), *sizes, scale, int(causal), torch.cuda.current_stream().cuda_stream, dtype, rows) == 0
+
+
+def run_gpu(q, k, v, dtype, scale, causal, guard=True, rows=None):
     """Launch the library on [B,H,N,d] uint16 numpy inputs.  Returns (O f64, LSE f64).
 
     The outputs start out as NaN (an unwritten element stays NaN and fails the finiteness check of
@@ -53,7 +61,7 @@ def run_gpu(q, k, v, dtype, scale, causal, guard=True):
     n_o, n_l = B * H * N * d, B * H * N
     pad = 256 if guard else 0
     obuf, lbuf, o, lse = fresh_outputs(n_o, n_l, pad)
-    binding.attn_fwd(dq, dk, dv, o, lse, B, H, N, d, scale, causal, dtype=dtype)
+    _launch(binding.attn_fwd, binding.load_library().attn_fwd_by_rows, dq, dk, dv, o, lse, (B, H, N, d), scale, causal, dtype, rows)
     torch.cuda.synchronize()
     check_guards(obuf, lbuf, n_o, n_l, pad)
     return bits_to_f64(o.reshape(B, H, N, d), dtype), lse.reshape(B, H, N).to(torch.float64).cpu().numpy()
@@ -72,7 +80,7 @@ def check(o_gpu, lse_gpu, o_ref, lse_ref, what="", tol_o_max=TOL_O_MAX, tol_o_me
 
 
 # ---------------------------------------------------------------- 8-bit-float (E4M3) inputs
-def run_gpu_fp8(q, k, v, out_dtype, scale, causal):
+def run_gpu_fp8(q, k, v, out_dtype, scale, causal, rows=None):
     """Launch ``attn_fwd_fp8`` on [B,H,N,d] uint8 numpy inputs (E4M3 patterns).  Returns (O f64, LSE f64);
     the outputs sit inside larger buffers whose margins are checked for stray writes."""
     B, H, N, d = q.shape
@@ -80,7 +88,7 @@ def run_gpu_fp8(q, k, v, out_dtype, scale, causal):
     n_o, n_l = B * H * N * d, B * H * N
     pad = 256
     obuf, lbuf, o, lse = fresh_outputs(n_o, n_l, pad)
-    binding.attn_fwd_fp8(dq, dk, dv, o, lse, B, H, N, d, scale, causal, out_dtype=out_dtype)
+    _launch(binding.attn_fwd_fp8, binding.load_library().attn_fwd_fp8_by_rows, dq, dk, dv, o, lse, (B, H, N, d), scale, causal, out_dtype, rows)
     torch.cuda.synchronize()
     check_guards(obuf, lbuf, n_o, n_l, pad)
     return bits_to_f64(o.reshape(B, H, N, d), out_dtype), lse.reshape(B, H, N).to(torch.float64).cpu().numpy()

@@ -98,6 +98,12 @@ def test_entry_points_return_argument_errors_without_launching(lib):
     assert lib.attn_fwd_f16(None, None, None, None, None, 1, 1, 64, 64, 0.125, 0, None) == -1
     assert lib.attn_fwd_bf16(0x1000, 0x2000, 0x3000, 0x4000, 0x5000, 1, 1, 64, 48, 0.125, 0, None) == -2
     assert lib.attn_fwd(0x1000, 0x2000, 0x3000, 0x4000, 0x5000, 1, 1, 64, 64, 0.125, 0, None, 7) == -2
+    for f in (lib.attn_fwd_by_rows, lib.attn_fwd_fp8_by_rows):
+        assert f(None, 0x2000, 0x3000, 0x4000, 0x5000, 1, 1, 64, 64, 0.125, 0, None, 0, 128) == -1
+        for rows in (-1, 0, 64, 512):                                          # unknown kernel
+            assert f(1 << 28, 2 << 28, 3 << 28, 4 << 28, 5 << 28, 1, 1, 64, 64, 0.125, 0, None, 0, rows) == -2
+        q, k, v, o, l = (i << 44 for i in range(1, 6))                         # more than a grid holds
+        assert f(q, k, v, o, l, 2 ** 13, 2 ** 10, 1, 64, 0.125, 1, None, 0, 128) == -5
 
 
 def test_mfma_probe_validation_needs_no_gpu(lib):

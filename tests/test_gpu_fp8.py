@@ -52,16 +52,16 @@ def test_many_tiles_ragged_tail(G, oracle, causal):
     _full(G, oracle, 1, 2, 1531, 64, causal, seed=178, out_dtype=I.BF16, what="ragged")
 
 
-# Few tiles: 128-row tiles whose 128-key stages two halves of a workgroup share (the upper half sees keys 64 ... 127 of every
-# 128, none at all in the first rows of a causal head); many tiles: 256-row tiles.  Lengths around those borders.
+# Few tiles, 128-row tiles whose 128-key stages two halves of a workgroup share (the upper half sees keys 64 ... 127 of every
+# 128, none at all in the first rows of a causal head); many tiles, 256-row tiles: each form by name, whatever a plain call would take.  Lengths around those borders.
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d", [128, 64])
-@pytest.mark.parametrize("H,lengths", [(2, (257, 319, 321, 383, 385, 449, 513, 2049)), (300, (97, 257))])
-def test_few_and_many_tiles(G, oracle, H, lengths, d, causal):
+@pytest.mark.parametrize("H,lengths,rows", [(2, (33, 65, 127, 129, 257, 319, 321, 383, 385, 449, 513, 2049), 128), (300, (97, 257), 256), (300, (97, 545), 128)])
+def test_few_and_many_tiles(G, oracle, H, lengths, rows, d, causal):
     for N in lengths:
         q, k, v = I.make_qkv(1, H, N, d, E4M3, 1500 + N + d, peaky=N % 2 == 1)
-        print("case fp8 few/many tiles H%d N%d d%d causal%d" % (H, N, d, causal), flush=True)
-        o, l = G.run_gpu_fp8(q, k, v, I.FP16, 1.0 / math.sqrt(d), causal)
+        print("case fp8 few/many tiles H%d N%d d%d causal%d rows%d" % (H, N, d, causal, rows), flush=True)
+        o, l = G.run_gpu_fp8(q, k, v, I.FP16, 1.0 / math.sqrt(d), causal, rows=rows)
         for h in (0, H - 1):
             sl = (slice(0, 1), slice(h, h + 1))
             qh, kh, vh = (np.ascontiguousarray(x[sl]) for x in (q, k, v))
@@ -70,23 +70,21 @@ def test_few_and_many_tiles(G, oracle, H, lengths, d, causal):
             G.check_fp8(o[sl], l[sl], o_ref, l_ref, bo, bl, "H%d N%d d%d head %d" % (H, N, d, h))
 
 
-# Enough heads for the 256-row kernel: its steady state followed by a ragged end, with ends that put the epilogue's pieces in each of the
+# The 256-row kernel: its steady state followed by a ragged end, with ends that put the epilogue's pieces in each of the
 # ring's slots; keys whose norm grows, so that the reference keeps moving up to the end.  The first and the last head.
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("growing", [False, True])
 def test_ragged_ends_with_many_heads(G, oracle, growing, d, causal):
-    from paper_2510_14719_amd import binding
     for N in (700,) if growing else (577, 700, 800, 1000, 1531):
         H = 300 if N <= 700 else 70
-        assert binding.load_library().attn_fwd_fp8_call_rows(1, H, N, d, causal) == 256
         q, k, v = I.make_qkv(1, H, N, d, E4M3, 1600 + N + d)
         if growing:
             rng = np.random.Generator(np.random.Philox(1700 + d))
             k = I.f32_to_e4m3_bits(rng.standard_normal((1, H, N, d), dtype=np.float32) * np.linspace(0.2, 6.0, N, dtype=np.float32)[None, None, :, None])
         scale = 0.3 if growing else 1.0 / math.sqrt(d)
         print("case fp8 ragged many heads H%d N%d d%d causal%d growing%d" % (H, N, d, causal, growing), flush=True)
-        o, l = G.run_gpu_fp8(q, k, v, I.FP16, scale, causal)
+        o, l = G.run_gpu_fp8(q, k, v, I.FP16, scale, causal, rows=256)
         assert np.isfinite(o).all() and np.isfinite(l).all()
         for h in (0, H - 1):
             sl = (slice(0, 1), slice(h, h + 1))
@@ -99,12 +97,10 @@ def test_ragged_ends_with_many_heads(G, oracle, growing, d, causal):
 # ... and for the epilogue of the split form above 4 MiB of O
 @pytest.mark.parametrize("causal", [False, True])
 def test_split_form_with_a_large_result(G, oracle, causal):
-    from paper_2510_14719_amd import binding
     H, N, d = 8, 3900, 128
-    assert binding.load_library().attn_fwd_fp8_call_rows(1, H, N, d, causal) == 128
     q, k, v = I.make_qkv(1, H, N, d, E4M3, 1800)
     print("case fp8 split, large result causal%d" % causal, flush=True)
-    o, l = G.run_gpu_fp8(q, k, v, I.BF16, 1.0 / math.sqrt(d), causal)
+    o, l = G.run_gpu_fp8(q, k, v, I.BF16, 1.0 / math.sqrt(d), causal, rows=128)
     assert np.isfinite(o).all() and np.isfinite(l).all()
     sl = (slice(0, 1), slice(H - 1, H))
     qh, kh, vh = (np.ascontiguousarray(x[sl]) for x in (q, k, v))
@@ -245,11 +241,9 @@ def test_large_scores_exercise_rescaling(G, oracle):
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("H,N,rows", [(3, 333, 128), (300, 577, 256)])
 def test_nan_stays_in_its_rows(G, oracle, H, N, rows, d, causal):
-    from paper_2510_14719_amd import binding
-    assert binding.load_library().attn_fwd_fp8_call_rows(1, H, N, d, causal) == rows
     q, k, v = I.make_qkv(1, H, N, d, E4M3, 1900 + N + d)
     scale, nan = 1.0 / math.sqrt(d), 0x7F
-    o0, l0 = G.run_gpu_fp8(q, k, v, I.FP16, scale, causal)
+    o0, l0 = G.run_gpu_fp8(q, k, v, I.FP16, scale, causal, rows=rows)
     assert np.isfinite(o0).all() and np.isfinite(l0).all()
     places = [(0, 20), (0, 37), (0, N - 1), (1, 0), (H - 1, 131), (H - 1, N - 5)]
     for what in ("query", "key"):
@@ -260,8 +254,8 @@ def test_nan_stays_in_its_rows(G, oracle, H, N, rows, d, causal):
             x[0, h, i, (5 * i) % d] = nan
             if what == "query": seen[0, h, i] = True
             else: seen[0, h, i if causal else 0:] = True
-        print("case fp8 NaN %s H%d N%d d%d causal%d" % (what, H, N, d, causal), flush=True)
-        o, l = G.run_gpu_fp8(*((x, k, v) if what == "query" else (q, x, v)), I.FP16, scale, causal)
+        print("case fp8 NaN %s H%d N%d d%d causal%d rows%d" % (what, H, N, d, causal, rows), flush=True)
+        o, l = G.run_gpu_fp8(*((x, k, v) if what == "query" else (q, x, v)), I.FP16, scale, causal, rows=rows)
         sl = (slice(0, 1), slice(0, 1))
         o_ref, _ = oracle.attn_ref(*(np.ascontiguousarray(y[sl]) for y in ((x, k, v) if what == "query" else (q, x, v))), E4M3, scale, causal)
         assert np.array_equal(np.isnan(o_ref).all(-1), seen[sl]) and np.array_equal(np.isnan(o_ref).any(-1), seen[sl])

@@ -97,18 +97,18 @@ def test_whole_heads_of_the_large_configs(G, oracle, name):
 
 
 # ------------------------------------------------------------ the forms for few and for many tiles
-# Few heads: 128-row tiles whose keys two wave groups share (group B sees keys 32 ... 63 of every 64, none at all up
-# to N = 32 and in the first rows of a causal head); many heads: 256-row tiles.  Lengths around the 32-key shares, the 64-key tiles
+# Few heads, 128-row tiles whose keys two wave groups share (group B sees keys 32 ... 63 of every 64, none at all up
+# to N = 32 and in the first rows of a causal head); many heads, 256-row tiles: each form by name, whatever a plain call would take.  Lengths around the 32-key shares, the 64-key tiles
 # and the 128- and 256-row tiles; keys with a few dominant rows, so that the two groups end with different references.
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("H,lengths", [(2, (1, 32, 33, 64, 65, 96, 97, 127, 129, 161, 2049)), (300, (33, 97, 129, 257))])
-def test_few_and_many_tiles(G, oracle, H, lengths, d, causal):
+@pytest.mark.parametrize("H,lengths,rows", [(2, (1, 32, 33, 64, 65, 96, 97, 127, 129, 161, 2049), 128), (300, (33, 97, 129, 257), 256), (300, (33, 129, 545), 128)])
+def test_few_and_many_tiles(G, oracle, H, lengths, rows, d, causal):
     for N in lengths:
         dtype = I.BF16 if N % 3 == 0 else I.FP16
         q, k, v = I.make_qkv(1, H, N, d, dtype, 2000 + N + d, peaky=True)
-        print("case few/many tiles H%d N%d d%d causal%d dtype%d" % (H, N, d, causal, dtype), flush=True)
-        o, l = G.run_gpu(q, k, v, dtype, 1.0 / math.sqrt(d), causal)
+        print("case few/many tiles H%d N%d d%d causal%d dtype%d rows%d" % (H, N, d, causal, dtype, rows), flush=True)
+        o, l = G.run_gpu(q, k, v, dtype, 1.0 / math.sqrt(d), causal, rows=rows)
         for h in (0, H - 1):
             sl = (slice(0, 1), slice(h, h + 1))
             o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]),
@@ -148,17 +148,17 @@ def test_zero_q_gives_running_mean(G, oracle, causal):
 # form for few tiles), whole tiles.  Rows that see no other key have no defined result and are left out.
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("H,N", [(2, 333), (300, 300)])
+@pytest.mark.parametrize("H,N,tile", [(2, 333, 128), (300, 300, 256)])
 @pytest.mark.parametrize("dtype,low", [(I.FP16, -np.inf), (I.BF16, -3e38)])
-def test_keys_that_score_minus_infinity(G, oracle, dtype, low, H, N, d, causal):
+def test_keys_that_score_minus_infinity(G, oracle, dtype, low, H, N, tile, d, causal):
     for first, last in ((0, 32), (32, 64), (0, 64), (0, 128), (64, 192)):
         q, k, v = I.make_qkv(1, H, N, d, dtype, 2100 + first + last)
         four, bad = I.to_bits(np.array([4.0, low], dtype=np.float32), dtype)
         q[..., 0] = four
         k[..., 0] = 0
         k[:, :, first:last, 0] = bad
-        print("case -inf keys %d..%d H%d N%d d%d causal%d dtype%d" % (first, last, H, N, d, causal, dtype), flush=True)
-        o, l = G.run_gpu(q, k, v, dtype, 1.0 / math.sqrt(d), causal)
+        print("case -inf keys %d..%d H%d N%d d%d causal%d dtype%d rows%d" % (first, last, H, N, d, causal, dtype, tile), flush=True)
+        o, l = G.run_gpu(q, k, v, dtype, 1.0 / math.sqrt(d), causal, rows=tile)
         rows = np.arange(last if causal and first == 0 else 0, N)
         for h in (0, H - 1):
             sl = (slice(0, 1), slice(h, h + 1))
@@ -172,12 +172,10 @@ def test_keys_that_score_minus_infinity(G, oracle, dtype, low, H, N, d, causal):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("H,N,rows", [(3, 333, 128), (300, 577, 256)])
 def test_nan_stays_in_its_rows(G, oracle, H, N, rows, d, causal):
-    from paper_2510_14719_amd import binding
-    assert binding.load_library().attn_fwd_call_rows(1, H, N, d, causal) == rows
     dtype = I.BF16 if d == 64 else I.FP16
     q, k, v = I.make_qkv(1, H, N, d, dtype, 2400 + N + d)
     scale, nan = 1.0 / math.sqrt(d), 0x7FC0 if dtype == I.BF16 else 0x7E00
-    o0, l0 = G.run_gpu(q, k, v, dtype, scale, causal)
+    o0, l0 = G.run_gpu(q, k, v, dtype, scale, causal, rows=rows)
     places = [(0, 20), (0, 37), (0, N - 1), (1, 0), (H - 1, 131), (H - 1, N - 5)]
     for what in ("query", "key"):
         x = (q if what == "query" else k).copy()
@@ -187,8 +185,8 @@ def test_nan_stays_in_its_rows(G, oracle, H, N, rows, d, causal):
             x[0, h, i, (5 * i) % d] = nan
             if what == "query": seen[0, h, i] = True
             else: seen[0, h, i if causal else 0:] = True
-        print("case NaN %s H%d N%d d%d causal%d" % (what, H, N, d, causal), flush=True)
-        o, l = G.run_gpu(*((x, k, v) if what == "query" else (q, x, v)), dtype, scale, causal)
+        print("case NaN %s H%d N%d d%d causal%d rows%d" % (what, H, N, d, causal, rows), flush=True)
+        o, l = G.run_gpu(*((x, k, v) if what == "query" else (q, x, v)), dtype, scale, causal, rows=rows)
         sl = (slice(0, 1), slice(0, 1))
         o_ref, _ = oracle.attn_ref(*(np.ascontiguousarray(y[sl]) for y in ((x, k, v) if what == "query" else (q, x, v))), dtype, scale, causal)
         assert np.array_equal(np.isnan(o_ref).all(-1), seen[sl]) and np.array_equal(np.isnan(o_ref).any(-1), seen[sl])
@@ -198,11 +196,11 @@ def test_nan_stays_in_its_rows(G, oracle, H, N, rows, d, causal):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("H", [1, 130])
-def test_a_dominating_key_at_every_place_of_a_tile(G, H, causal, d):
+@pytest.mark.parametrize("H,rows", [(1, 128), (130, 256)])
+def test_a_dominating_key_at_every_place_of_a_tile(G, H, rows, causal, d):
     # Query i looks at key 64 + i % 64 (its features are a scaled copy of that key's, the key rows being nearly orthogonal sign
     # patterns): the reference moves in the second tile, through whichever lane holds that key, and O is that key's row of V.
-    # H = 130: 256-row tiles, H = 1: split ones.  Bounds: the score gap is d * gain / sqrt(d) against cross terms
+    # Bounds: the score gap is d * gain / sqrt(d) against cross terms
     # of at most gain * sqrt(d) * 5.5 / sqrt(d) (5.5 standard deviations over the 64 x 447 pairs), so the other keys weigh less than
     # 512 exp(-gain (sqrt(d) - 5.5)) < 1e-12 and O is V[key] rounded to 16 bits, which it is already: equal.
     import torch
@@ -213,10 +211,10 @@ def test_a_dominating_key_at_every_place_of_a_tile(G, H, causal, d):
     place = 64 + torch.arange(N) % 64
     q = k[:, :, place] * gain
     q, k, v = (x.to(torch.float16).cuda() for x in (q, k, v))
-    print("dominating key H%d d%d causal%d rows%d" % (H, d, causal, G.binding.load_library().attn_fwd_call_rows(1, H, N, d, int(causal))), flush=True)
+    print("case dominating key H%d d%d causal%d rows%d" % (H, d, causal, rows), flush=True)
     o = torch.full_like(v, float("nan"))
     lse = torch.full((1, H, N), float("nan"), device="cuda")
-    G.binding.attn_fwd(q, k, v, o, lse, 1, H, N, d, 1.0 / math.sqrt(d), causal)
+    G._launch(None, G.binding.load_library().attn_fwd_by_rows, q, k, v, o, lse, (1, H, N, d), 1.0 / math.sqrt(d), causal, I.FP16, rows)
     torch.cuda.synchronize()
     seen = slice(128, N) if causal else slice(0, N)     # rows that see the key in either mask
     place = place.cuda()
@@ -241,19 +239,17 @@ def test_large_scores_exercise_rescaling(G, oracle, dtype):
     G.check(o, l, o_ref, l_ref, "large-scores", tol_o_max=4e-2 if dtype == I.BF16 else 2e-2, tol_lse=2e-2)
 
 
-# Enough heads for the 256-row kernels (few heads take 128-row tiles, whatever the length): their steady state, more than eight key
+# The 256-row kernels: their steady state, more than eight key
 # tiles, followed by a ragged end, with row tiles that end at different places; ends that put the epilogue's pieces in each of the
 # ring's slots.  The first and the last head, and every element written.
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d,dtype", [(64, I.FP16), (64, I.BF16), (128, I.FP16)])
 def test_ragged_ends_with_many_heads(G, oracle, d, dtype, causal):
-    from paper_2510_14719_amd import binding
     for N in (577, 700, 800, 1000, 1531):
         H = 300 if N <= 700 else 70
-        assert binding.load_library().attn_fwd_call_rows(1, H, N, d, causal) == 256
         q, k, v = I.make_qkv(1, H, N, d, dtype, 2200 + N + d)
         print("case ragged many heads H%d N%d d%d causal%d dtype%d" % (H, N, d, causal, dtype), flush=True)
-        o, l = G.run_gpu(q, k, v, dtype, 1.0 / math.sqrt(d), causal)
+        o, l = G.run_gpu(q, k, v, dtype, 1.0 / math.sqrt(d), causal, rows=256)
         assert np.isfinite(o).all() and np.isfinite(l).all()
         for h in (0, H - 1):
             sl = (slice(0, 1), slice(h, h + 1))
@@ -265,18 +261,16 @@ def test_ragged_ends_with_many_heads(G, oracle, d, dtype, causal):
 # The split form above 4 MiB of O (another way of storing it), one round and two
 @pytest.mark.parametrize("d,H,N,causal", [(128, 8, 3900, False), (128, 8, 3900, True), (64, 16, 2005, False), (64, 16, 2005, True), (128, 16, 2700, True)])
 def test_split_form_with_a_large_result(G, oracle, d, H, N, causal):
-    from paper_2510_14719_amd import binding
-    assert binding.load_library().attn_fwd_call_rows(1, H, N, d, causal) == 128
     q, k, v = I.make_qkv(1, H, N, d, I.FP16, 2300 + N)
     print("case split, large result H%d N%d d%d causal%d" % (H, N, d, causal), flush=True)
-    o, l = G.run_gpu(q, k, v, I.FP16, 1.0 / math.sqrt(d), causal)
+    o, l = G.run_gpu(q, k, v, I.FP16, 1.0 / math.sqrt(d), causal, rows=128)
     assert np.isfinite(o).all() and np.isfinite(l).all()
     sl = (slice(0, 1), slice(H - 1, H))
     o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]), I.FP16, 1.0 / math.sqrt(d), causal)
     G.check(o[sl], l[sl], o_ref, l_ref, "split, large result H%d N%d d%d" % (H, N, d))
 
 
-# The same growing keys as above over enough heads for the 256-row kernels; the first heads keep the tolerances.
+# The same growing keys as above with 256-row tiles; the first heads keep the tolerances.
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("causal", [False, True])
 def test_large_scores_with_many_heads(G, oracle, causal, d):
@@ -288,7 +282,7 @@ def test_large_scores_with_many_heads(G, oracle, causal, d):
     k = I.to_bits(kf, dtype)
     v = I.normal_bits((1, H, N, d), dtype, 194)
     print("case large scores many heads d%d causal%d" % (d, causal), flush=True)
-    o, l = G.run_gpu(q, k, v, dtype, scale, causal)
+    o, l = G.run_gpu(q, k, v, dtype, scale, causal, rows=256)
     for h in (0, H - 1):
         sl = (slice(0, 1), slice(h, h + 1))
         o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]), dtype, scale, causal)

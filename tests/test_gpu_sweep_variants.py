@@ -39,15 +39,17 @@ def _cases(op):
     return [pytest.param(op, p, id=sweep.variant_name(op, p)) for p in sweep.TEST_VARIANTS[op]]
 
 
-def _attn(torch, lib, q, k, v, dtype, scale, causal, fp8=False):
+def _attn(torch, lib, q, k, v, dtype, scale, causal, fp8=False, rows=None):
     B, H, N, d = q.shape
     dq, dk, dv = (torch.from_numpy(x if fp8 else x.view(np.int16)).cuda() for x in (q, k, v))
     o = torch.full((B, H, N, d), 0x7FFF, dtype=torch.int16, device="cuda")
     lse = torch.full((B, H, N), float("nan"), dtype=torch.float32, device="cuda")
     stream = torch.cuda.current_stream().cuda_stream
-    fn = lib.attn_fwd_fp8 if fp8 else lib.attn_fwd
-    rc = fn(dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), o.data_ptr(), lse.data_ptr(), B, H, N, d, scale, int(causal), stream,
-            0 if fp8 else dtype)
+    args = (dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), o.data_ptr(), lse.data_ptr(), B, H, N, d, scale, int(causal), stream, 0 if fp8 else dtype)
+    if rows is None:
+        rc = (lib.attn_fwd_fp8 if fp8 else lib.attn_fwd)(*args)
+    else:
+        rc = (lib.attn_fwd_fp8_by_rows if fp8 else lib.attn_fwd_by_rows)(*args, rows)
     torch.cuda.synchronize()
     assert rc == 0
     of = o.view(torch.bfloat16 if (dtype == I.BF16 and not fp8) else torch.float16).double().cpu().numpy()
@@ -78,9 +80,8 @@ def test_attention_variants_against_the_oracle(env, op, point):
     # (those take 128-row tiles where the build has them; the kernels the knobs select, with a ragged end: many heads, the
     # first and the last)
     for (H, N, dtype, causal, seed) in [(90, 577, I.FP16, False, 307), (60, 1000, I.BF16, True, 308)]:
-        assert ((N + 127) // 128) * H > 256
         q, k, v = I.make_qkv(1, H, N, 128, dtype, seed)
-        of, lf = _attn(torch, lib, q, k, v, dtype, 1.0 / math.sqrt(128), causal)
+        of, lf = _attn(torch, lib, q, k, v, dtype, 1.0 / math.sqrt(128), causal, rows=lib.attn_fwd_tile_param(128, int(causal), 0))
         for h in (0, H - 1):
             sl = (slice(0, 1), slice(h, h + 1))
             o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]), dtype, 1.0 / math.sqrt(128), causal)
@@ -113,7 +114,7 @@ def test_fp8_attention_variants_against_the_oracle(env, op, point):
     # the 256-row kernel with a ragged end, its first and last head
     H, N = 60, 1000
     q, k, v = I.make_qkv(1, H, N, 128, I.E4M3, 309)
-    of, lf = _attn(torch, lib, q, k, v, I.E4M3, scale, True, fp8=True)
+    of, lf = _attn(torch, lib, q, k, v, I.E4M3, scale, True, fp8=True, rows=256)
     for h in (0, H - 1):
         sl = (slice(0, 1), slice(h, h + 1))
         o_ref, l_ref = oracle.attn_ref(np.ascontiguousarray(q[sl]), np.ascontiguousarray(k[sl]), np.ascontiguousarray(v[sl]), I.E4M3, scale, True)
