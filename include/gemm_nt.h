@@ -64,13 +64,18 @@ int gemm_nt_f16(const void *a, const void *b, void *c, int M, int N, int K, void
 int gemm_nt_bf16(const void *a, const void *b, void *c, int M, int N, int K, void *stream);
 
 /*
- * The kernels that gemm_nt chooses from, by the tile of C of a workgroup: 0 = 256 x 256, 1 = 64 x 64, or 32 x 32 or
- * 16 x 16 where that makes few of them, 2 = 128 x 128 with two workgroups per compute unit, 3 = 128 x 128 with more waves.  gemm_nt_shape says which one a product takes (-1 for sizes that
- * no call accepts), gemm_nt_by_shape takes the one the caller names (for tests and measurements): GEMM_NT_ERR_SHAPE for any
- * other value, and for shape 0 with K < 64.
+ * The kernels that gemm_nt chooses from, by the tile of C of a workgroup: 0 = 256 x 256, 1 = 64 x 64 or less, 2 = 128 x 128 with two
+ * workgroups per compute unit, 3 = 128 x 128 with more waves.  gemm_nt_shape says which one a product takes (-1 for sizes that
+ * no call accepts), gemm_nt_by_shape takes the one the caller names (for tests and measurements; 1 is then 64 x 64): GEMM_NT_ERR_SHAPE
+ * for any other value, and for shape 0 with K < 64.
+ * Where 64 x 64 tiles are few a product of shape 1 takes 32 x 32 or 16 x 16 ones: gemm_nt_narrow_tile is 32 or 16 for such a product,
+ * else 0; gemm_nt_by_narrow_tile takes the tile the caller names, for any product: GEMM_NT_ERR_SHAPE for other values, GEMM_NT_ERR_OVERFLOW
+ * where a grid cannot have as many workgroups.
  */
 int gemm_nt_shape(int M, int N, int K);
 int gemm_nt_by_shape(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int dtype, int shape);
+int gemm_nt_narrow_tile(int M, int N, int K);
+int gemm_nt_by_narrow_tile(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int dtype, int tile);
 
 /* Host-only argument check: what gemm_nt would return before launching. */
 int gemm_nt_check_args(const void *a, const void *b, const void *c, int M, int N, int K, int dtype);
@@ -101,9 +106,11 @@ int gemm_nt_fp8(const void *a, const void *b, void *c, int M, int N, int K, void
  */
 int gemm_nt_fp8_config(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int out_dtype, int config);
 
-/* The same as gemm_nt_shape and gemm_nt_by_shape for gemm_nt_fp8 (shape 0 needs K >= 128). */
+/* The same for gemm_nt_fp8 (shape 0 needs K >= 128, the narrow tile is 32). */
 int gemm_nt_fp8_shape(int M, int N, int K);
 int gemm_nt_fp8_by_shape(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int out_dtype, int shape);
+int gemm_nt_fp8_narrow_tile(int M, int N, int K);
+int gemm_nt_fp8_by_narrow_tile(const void *a, const void *b, void *c, int M, int N, int K, void *stream, int out_dtype, int tile);
 
 /* Host-only argument check: what gemm_nt_fp8 would return before launching. */
 int gemm_nt_fp8_check_args(const void *a, const void *b, const void *c, int M, int N, int K, int out_dtype);

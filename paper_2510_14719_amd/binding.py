@@ -83,10 +83,10 @@ def load_library() -> ctypes.CDLL:
         lib.gemm_nt.argtypes = [vp, vp, vp, ci, ci, ci, vp, ci]
         lib.gemm_nt_config.restype = ci
         lib.gemm_nt_config.argtypes = [vp, vp, vp, ci, ci, ci, vp, ci, ci]
-        for shape_of in (lib.gemm_nt_shape, lib.gemm_nt_fp8_shape):
+        for shape_of in (lib.gemm_nt_shape, lib.gemm_nt_fp8_shape, lib.gemm_nt_narrow_tile, lib.gemm_nt_fp8_narrow_tile):
             shape_of.restype = ci
             shape_of.argtypes = [ci, ci, ci]
-        for by_shape in (lib.gemm_nt_by_shape, lib.gemm_nt_fp8_by_shape):
+        for by_shape in (lib.gemm_nt_by_shape, lib.gemm_nt_fp8_by_shape, lib.gemm_nt_by_narrow_tile, lib.gemm_nt_fp8_by_narrow_tile):
             by_shape.restype = ci
             by_shape.argtypes = [vp, vp, vp, ci, ci, ci, vp, ci, ci]
         lib.gemm_nt_f16.restype = ci

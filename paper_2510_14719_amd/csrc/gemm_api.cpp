@@ -14,6 +14,10 @@ bool overlaps(const void* a, unsigned long long na, const void* b, unsigned long
     return pa < pb + nb && pb < pa + na;
 }
 
+// A grid has less than 2^32 threads, 512 per narrow tile.
+constexpr long long MAX_NARROW_TILES = (1ll << 32) / 512 - 1;
+long long narrow_tiles(int M, int N, int tile) { return ((M + tile - 1LL) / tile) * ((N + tile - 1LL) / tile); }
+
 }  // namespace
 
 extern "C" {
@@ -62,6 +66,17 @@ int gemm_nt_by_shape(const void* a, const void* b, void* c, int M, int N, int K,
     return gemm_tile_launch({a, b, c, M, N, K, dtype, stream}, dtype, shape) == 0 ? GEMM_NT_OK : GEMM_NT_ERR_LAUNCH;
 }
 
+int gemm_nt_narrow_tile(int M, int N, int K) { return gemm_nt_shape(M, N, K) == 1 ? gemm_narrow_tile(M, N, 2LL * K, false) : 0; }
+
+int gemm_nt_by_narrow_tile(const void* a, const void* b, void* c, int M, int N, int K, void* stream, int dtype, int tile)
+{
+    const int rc = gemm_nt_check_args(a, b, c, M, N, K, dtype);
+    if (rc != GEMM_NT_OK) return rc;
+    if (tile != 16 && tile != 32) return GEMM_NT_ERR_SHAPE;
+    if (narrow_tiles(M, N, tile) > MAX_NARROW_TILES) return GEMM_NT_ERR_OVERFLOW;
+    return gemm_narrow_launch({a, b, c, M, N, K, dtype, stream}, dtype, tile) == 0 ? GEMM_NT_OK : GEMM_NT_ERR_LAUNCH;
+}
+
 int gemm_nt_fp8_shape(int M, int N, int K)
 {
     if (M < 1 || N < 1 || K < 64 || K % 64 != 0) return -1;
@@ -74,6 +89,17 @@ int gemm_nt_fp8_by_shape(const void* a, const void* b, void* c, int M, int N, in
     if (rc != GEMM_NT_OK) return rc;
     if (shape < 0 || shape > 3 || (shape == 0 && K < 128)) return GEMM_NT_ERR_SHAPE;
     return gemm_tile_launch({a, b, c, M, N, K, out_dtype, stream}, 2, shape) == 0 ? GEMM_NT_OK : GEMM_NT_ERR_LAUNCH;
+}
+
+int gemm_nt_fp8_narrow_tile(int M, int N, int K) { return gemm_nt_fp8_shape(M, N, K) == 1 ? gemm_narrow_tile(M, N, K, true) : 0; }
+
+int gemm_nt_fp8_by_narrow_tile(const void* a, const void* b, void* c, int M, int N, int K, void* stream, int out_dtype, int tile)
+{
+    const int rc = gemm_nt_fp8_check_args(a, b, c, M, N, K, out_dtype);
+    if (rc != GEMM_NT_OK) return rc;
+    if (tile != 32) return GEMM_NT_ERR_SHAPE;
+    if (narrow_tiles(M, N, tile) > MAX_NARROW_TILES) return GEMM_NT_ERR_OVERFLOW;
+    return gemm_narrow_launch({a, b, c, M, N, K, out_dtype, stream}, 2, tile) == 0 ? GEMM_NT_OK : GEMM_NT_ERR_LAUNCH;
 }
 
 int gemm_nt_fp8_check_args(const void* a, const void* b, const void* c, int M, int N, int K, int out_dtype)

@@ -14,13 +14,14 @@ struct GemmLaunchArgs {
 // Enqueue the kernel for already-validated arguments.  0 on success, -1 if HIP refused the launch.
 int gemm_launch(const GemmLaunchArgs& a);
 
-// The kernels that configuration 0 takes (gemm_nt_tile_kernel.hip): shape 0 (256 x 256 of C per workgroup), 1, 2 or 3;
-// in_type 0 = fp16, 1 = bf16, 2 = E4M3 operands.
+// What configuration 0 takes; in_type 0 = fp16, 1 = bf16, 2 = E4M3 operands.
+int gemm_default_launch(const GemmLaunchArgs& a, int in_type);
+// The kernels it chooses from (gemm_nt_tile_kernel.hip): shape 0 (256 x 256 of C per workgroup), 1 (64 x 64), 2 or 3 (128 x 128).
 int gemm_tile_launch(const GemmLaunchArgs& a, int in_type, int shape);
 // The shape for rows of row_bytes (K elements).
 int gemm_tile_shape(int M, int N, long long row_bytes);
 
-// The smallest tiles of C (gemm_nt_narrow_kernel.hip), which shape 1 takes where gemm_narrow_tile says 32 or 16 and not 0 (64 x 64).
+// The smallest tiles of C (gemm_nt_narrow_kernel.hip), in the place of shape 1 where gemm_narrow_tile says 32 or 16 and not 0.
 int gemm_narrow_tile(int M, int N, long long row_bytes, bool fp8);
 int gemm_narrow_launch(const GemmLaunchArgs& a, int in_type, int tile);
 

@@ -366,7 +366,7 @@ int launch8_out(const GemmLaunchArgs& a)
 
 int gemm_fp8_launch(const GemmLaunchArgs& a)
 {
-    if (GEMM8_CONFIG == 0 && a.config == 0) return gemm_tile_launch(a, 2, gemm_tile_shape(a.M, a.N, a.K));
+    if (GEMM8_CONFIG == 0 && a.config == 0) return gemm_default_launch(a, 2);
     return a.dtype == 0 ? launch8_out<0>(a) : launch8_out<1>(a);
 }
 

@@ -404,7 +404,7 @@ extern "C" int gemm_dbg_read(unsigned long long* host, int n)
 
 int gemm_launch(const GemmLaunchArgs& a)
 {
-    if (GEMM_CONFIG == 0 && a.config == 0) return gemm_tile_launch(a, a.dtype, gemm_tile_shape(a.M, a.N, 2LL * a.K));
+    if (GEMM_CONFIG == 0 && a.config == 0) return gemm_default_launch(a, a.dtype);
     return a.dtype == 0 ? launch_dtype<0>(a) : launch_dtype<1>(a);
 }
 

@@ -1,5 +1,5 @@
 // NT matrix products with the smallest tiles of C for gfx950 (MI355X), 16-bit and E4M3 operands: the same contract as
-// gemm_nt_tile_kernel.hip, whose shape 1 they are where 64 x 64 tiles are few.
+// gemm_nt_tile_kernel.hip, in the place of its shape 1 where 64 x 64 tiles are few.
 //
 // 32 x 32 or 16 x 16 of C per workgroup (T), for products with few 64 x 64 tiles.
 //
@@ -200,7 +200,7 @@ int gemm_narrow_launch(const GemmLaunchArgs& a, int in_type, int tile)
     return a.dtype == 0 ? launch_narrow_of<2, 0>(a, tile) : launch_narrow_of<2, 1>(a, tile);
 }
 
-// Which tiles of C shape 1 takes: T of gemm_nt_narrow_kernel, or 0 for 64 x 64.  The smaller ones while they fit the chip in one round,
+// Which tiles of C a product takes in the place of shape 1: T of gemm_nt_narrow_kernel, or 0 for the 64 x 64 ones.  The smaller ones while they fit the chip in one round,
 // however long the rows are; 32 x 32 also two to a CU where the rows are long, for 16-bit operands (for E4M3 one wave does the
 // MFMAs, and two such workgroups lose).  us, 64 x 64 / 32 x 32 / 16 x 16, M x N x K:
 //    bf16   64 x 64 x 64        4.05 / 3.87 / 3.91         64 x 64 x 16384     43.2 / 22.1 / 12.5

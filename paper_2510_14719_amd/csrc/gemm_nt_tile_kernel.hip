@@ -464,6 +464,8 @@ int launch_wide(const GemmLaunchArgs& a)
 //    3000 x 3000 x 256     13.1  17.6  [13.4] 17.1        3000 x 3000 x 512  [17.0] 21.8  18.8 22.1
 //    2048 x 2048 x 256     11.2   8.6   [6.3]  7.1        2048 x 2048 x 4096   70    50    41  [32]
 //    1000 x 777 x 512      30    [5.0]   9.3   8.5        64 x 64 x 16384     245   [35]   92   68
+// Where shape 1 is chosen the smallest products go on to 32 x 32 or 16 x 16 tiles (gemm_nt_narrow_kernel.hip: 12.5 us for the last one).  Its
+// model knows 64 x 64 tiles only, which decides nothing: wherever the smaller tiles apply, 64 x 64 ones are the model's choice too.
 struct ShapeModel { int tile; float start, per_tile, step_idle, step_full; };
 constexpr ShapeModel T_MODEL[4] = {
     {256, 1.5f, 8.5f, 0.95f, 1.30f},        // 0: gemm_nt_wide_kernel
@@ -491,12 +493,16 @@ int launch_shape(const GemmLaunchArgs& a, int shape)
 
 int gemm_tile_launch(const GemmLaunchArgs& a, int in_type, int shape)
 {
-    if (shape == 1) {
-        if (const int tile = gemm_narrow_tile(a.M, a.N, (long long)a.K * (in_type == 2 ? 1 : 2), in_type == 2)) return gemm_narrow_launch(a, in_type, tile);
-    }
     if (in_type == 0) return launch_shape<0, 0>(a, shape);
     if (in_type == 1) return launch_shape<1, 1>(a, shape);
     return a.dtype == 0 ? launch_shape<2, 0>(a, shape) : launch_shape<2, 1>(a, shape);
+}
+
+int gemm_default_launch(const GemmLaunchArgs& a, int in_type)
+{
+    const long long row_bytes = (long long)a.K * (in_type == 2 ? 1 : 2);
+    const int shape = gemm_tile_shape(a.M, a.N, row_bytes), narrow = shape == 1 ? gemm_narrow_tile(a.M, a.N, row_bytes, in_type == 2) : 0;
+    return narrow ? gemm_narrow_launch(a, in_type, narrow) : gemm_tile_launch(a, in_type, shape);
 }
 
 int gemm_tile_shape(int M, int N, long long row_bytes)

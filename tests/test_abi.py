@@ -162,6 +162,17 @@ def test_gemm_argument_validation_needs_no_gpu(lib):
         assert lib.gemm_nt_by_shape(a, b, c, 8, 8, 64, None, 0, bad) == -2     # unknown kernel
     assert lib.gemm_nt_by_shape(a, b, c, 8, 8, 32, None, 0, 0) == -2           # rows shorter than a line
     assert lib.gemm_nt_by_shape(None, b, c, 8, 8, 64, None, 0, 1) == -1
+    for f in (lib.gemm_nt_by_narrow_tile, lib.gemm_nt_fp8_by_narrow_tile):
+        for bad in (0, 1, 8, 64):
+            assert f(a, b, c, 8, 8, 64, None, 0, bad) == -2
+        assert f(a, b, None, 8, 8, 64, None, 0, 32) == -1
+        assert f(1 << 40, 2 << 40, 3 << 40, 2 ** 20, 2 ** 13, 64, None, 0, 32) == (-5)   # 2^23 workgroups of 512 threads
+    assert lib.gemm_nt_fp8_by_narrow_tile(a, b, c, 8, 8, 64, None, 0, 16) == -2
+    # tiles up to 256, 32 x 32 ones up to 512 with long rows (16-bit); never where another shape is taken
+    for M, N, K, tile, tile8 in ((1, 1, 64, 16, 32), (256, 256, 64, 16, 32), (257, 256, 64, 32, 32), (512, 512, 4096, 32, 32), (513, 512, 1024, 0, 0),
+                                 (513, 512, 2048, 32, 0), (1024, 512, 2048, 32, 0), (1025, 512, 2048, 0, 0), (8192, 8192, 8192, 0, 0), (8, 8, 48, 0, 0)):
+        assert lib.gemm_nt_narrow_tile(M, N, K) == tile and lib.gemm_nt_fp8_narrow_tile(M, N, K) == tile8
+        assert tile == 0 or lib.gemm_nt_shape(M, N, K) == 1
     assert lib.gemm_nt_shape(8, 8, 48) == -1 and lib.gemm_nt_shape(0, 8, 64) == -1
     for M, N, K in ((1, 1, 32), (64, 64, 32), (8192, 8192, 32), (300, 4000, 1024), (8192, 8192, 8192)):
         assert lib.gemm_nt_shape(M, N, K) in ((1, 2, 3) if K < 64 else (0, 1, 2, 3))

@@ -26,7 +26,7 @@ def env():
     return torch, binding, gemm_ref
 
 
-def run_gpu(env, a, b, dtype, pad=512, config=None, finite=True):
+def run_gpu(env, a, b, dtype, pad=512, config=None, finite=True, shape=None):
     torch, binding, _ = env
     M, K = a.shape
     N = b.shape[0]
@@ -34,7 +34,10 @@ def run_gpu(env, a, b, dtype, pad=512, config=None, finite=True):
     db = torch.from_numpy(b.view(np.int16)).cuda()
     buf = torch.full((M * N + 2 * pad,), 0x7FFF, dtype=torch.int16, device="cuda")
     c = buf[pad:pad + M * N]
-    binding.gemm_nt(da, db, c, M, N, K, dtype=dtype, config=config)
+    if shape is None:
+        binding.gemm_nt(da, db, c, M, N, K, dtype=dtype, config=config)
+    else:                                    # the kernel by name, whatever a plain call would take
+        assert binding.load_library().gemm_nt_by_shape(da.data_ptr(), db.data_ptr(), c.data_ptr(), M, N, K, torch.cuda.current_stream().cuda_stream, dtype, shape) == 0
     torch.cuda.synchronize()
     assert bool((buf[:pad] == 0x7FFF).all()) and bool((buf[pad + M * N:] == 0x7FFF).all()), "guard words overwritten"
     # (the buffer started out as NaN patterns: a finite C proves that every element was written)
@@ -93,7 +96,7 @@ def test_small_tile_shapes(env, shape, M, N, Ks, dtype):
         assert binding.load_library().gemm_nt_shape(M, N, K) == shape
         a, b = I.make_ab(M, N, K, dtype, seed=1100 + M + N + K)
         print("case gemm shape%d M%d N%d K%d dtype%d" % (shape, M, N, K, dtype), flush=True)
-        c = run_gpu(env, a, b, dtype)
+        c = run_gpu(env, a, b, dtype, shape=shape)
         if M * N * K < 1e9:
             check(c.double().cpu().numpy(), G.gemm_nt(a, b, dtype), dtype, K, "shape %d M%d N%d K%d" % (shape, M, N, K))
         else:
@@ -102,8 +105,8 @@ def test_small_tile_shapes(env, shape, M, N, Ks, dtype):
                   "shape %d M%d N%d K%d" % (shape, M, N, K))
 
 
-# Shape 1's smaller tiles: 16 x 16 (512-byte stages) up to 256 of them, else 32 x 32 (256-byte stages, E4M3 always) up to 256, and two
-# to a CU from 4096-byte rows on (16-bit); beside them 64 x 64 again.  One to six stages around the ring depth of four and more, last
+# The smallest tiles, each by name: 16 x 16 (512-byte stages, 16-bit operands) and 32 x 32 (256-byte stages); and what a plain call takes: 16 x 16
+# up to 256 of them, else 32 x 32 up to 256, and two to a CU from 4096-byte rows on (16-bit), else 64 x 64 again.  One to six stages around the ring depth of four and more, last
 # stages of every length (multiples of 64 bytes), tiles that overhang by all but one row and column; rows of C on
 # and off 16-byte boundaries, nothing outside C written.
 @pytest.mark.parametrize("kind", ["fp16", "bf16", "e4m3"])
@@ -115,7 +118,8 @@ def test_smallest_tiles(env, kind, M, N, rows):
     torch, binding, G = env
     lib = binding.load_library()
     f8, dtype = kind == "e4m3", I.BF16 if kind == "bf16" else I.FP16
-    launch, shape_of = (lib.gemm_nt_fp8_by_shape, lib.gemm_nt_fp8_shape) if f8 else (lib.gemm_nt_by_shape, lib.gemm_nt_shape)
+    launch, tile_of, by_shape = ((lib.gemm_nt_fp8_by_narrow_tile, lib.gemm_nt_fp8_narrow_tile, lib.gemm_nt_fp8_by_shape) if f8 else
+                                 (lib.gemm_nt_by_narrow_tile, lib.gemm_nt_narrow_tile, lib.gemm_nt_by_shape))
     view = {"fp16": torch.float16, "bf16": torch.bfloat16, "e4m3": torch.float8_e4m3fn}[kind]
     out = torch.bfloat16 if kind == "bf16" else torch.float16
     for row_bytes in rows:
@@ -123,26 +127,34 @@ def test_smallest_tiles(env, kind, M, N, rows):
         print("case gemm smallest tiles %s M%d N%d K%d" % (kind, M, N, K), flush=True)
         gen = torch.Generator(device="cuda").manual_seed(M + N + K)
         a, b = (torch.randn((r, K), generator=gen, device="cuda").to(view) for r in (M, N))
-        buf = torch.full((M * N + 256,), 7.0, dtype=out, device="cuda")
+        stream = torch.cuda.current_stream().cuda_stream
         skew = (M + K // 32) % 2                 # C on a 256-byte boundary, or one element behind it
-        c = buf[128 + skew:128 + skew + M * N].view(M, N)
-        c.fill_(float("nan"))
-        assert launch(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, torch.cuda.current_stream().cuda_stream, dtype, 1) == 0
         if f8:                                   # one order of summation in every kernel
             want = torch.empty((M, N), dtype=out, device="cuda")
             binding.gemm_nt_fp8(a, b, want, M, N, K, out_dtype=dtype, config=1)
-            assert torch.equal(c, want)
         else:
-            ref = a.double() @ b.double().T
-            check(c.double().cpu().numpy(), ref.cpu().numpy(), dtype, K, "smallest tiles %s M%d N%d K%d" % (kind, M, N, K))
-        if shape_of(M, N, K) == 1:               # what a plain call takes
-            d = torch.empty((M, N), dtype=out, device="cuda")
+            ref = (a.double() @ b.double().T).cpu().numpy()
+        results = {}
+        for tile in (32,) if f8 else (16, 32):
+            buf = torch.full((M * N + 256,), 7.0, dtype=out, device="cuda")
+            c = buf[128 + skew:128 + skew + M * N].view(M, N)
+            c.fill_(float("nan"))
+            assert launch(a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, stream, dtype, tile) == 0
             if f8:
-                binding.gemm_nt_fp8(a, b, d, M, N, K, out_dtype=dtype)
+                assert torch.equal(c, want)
             else:
-                binding.gemm_nt(a, b, d, M, N, K)
-            assert torch.equal(c, d)
-        assert bool((buf[:128 + skew] == 7.0).all()) and bool((buf[128 + skew + M * N:] == 7.0).all())
+                check(c.double().cpu().numpy(), ref, dtype, K, "tiles of %d, %s M%d N%d K%d" % (tile, kind, M, N, K))
+            assert bool((buf[:128 + skew] == 7.0).all()) and bool((buf[128 + skew + M * N:] == 7.0).all())
+            results[tile] = c
+        d, e = (torch.empty((M, N), dtype=out, device="cuda") for _ in range(2))
+        if f8:
+            binding.gemm_nt_fp8(a, b, d, M, N, K, out_dtype=dtype)
+        else:
+            binding.gemm_nt(a, b, d, M, N, K)
+        tile = tile_of(M, N, K)
+        if tile == 0:
+            assert by_shape(a.data_ptr(), b.data_ptr(), e.data_ptr(), M, N, K, stream, dtype, 1) == 0
+        assert torch.equal(d, results[tile] if tile else e)
 
 
 # The 256 x 256 kernel with whole lines per row, called directly: one to six 128-byte steps (ring of two and a half), with and

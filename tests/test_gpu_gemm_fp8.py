@@ -34,14 +34,17 @@ def env():
     return torch, binding, gemm_ref
 
 
-def run_gpu(env, a, b, out_dtype, pad=512, config=None, finite=True):
+def run_gpu(env, a, b, out_dtype, pad=512, config=None, finite=True, shape=None):
     torch, binding, _ = env
     M, K = a.shape
     N = b.shape[0]
     da, db = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
     buf = torch.full((M * N + 2 * pad,), 0x7FFF, dtype=torch.int16, device="cuda")
     c = buf[pad:pad + M * N]
-    binding.gemm_nt_fp8(da, db, c, M, N, K, out_dtype=out_dtype, config=config)
+    if shape is None:
+        binding.gemm_nt_fp8(da, db, c, M, N, K, out_dtype=out_dtype, config=config)
+    else:                                    # the kernel by name, whatever a plain call would take
+        assert binding.load_library().gemm_nt_fp8_by_shape(da.data_ptr(), db.data_ptr(), c.data_ptr(), M, N, K, torch.cuda.current_stream().cuda_stream, out_dtype, shape) == 0
     torch.cuda.synchronize()
     assert bool((buf[:pad] == 0x7FFF).all()) and bool((buf[pad + M * N:] == 0x7FFF).all()), "guard words overwritten"
     # (the buffer started out as NaN patterns: a finite C proves that every element was written)
@@ -104,7 +107,7 @@ def test_small_tile_shapes(env, shape, M, N, Ks):
         assert binding.load_library().gemm_nt_fp8_shape(M, N, K) == shape
         a, b = I.make_ab(M, N, K, I.E4M3, seed=1100 + M + N + K)
         print("case gemm_fp8 shape%d M%d N%d K%d" % (shape, M, N, K), flush=True)
-        c = run_gpu(env, a, b, I.FP16)
+        c = run_gpu(env, a, b, I.FP16, shape=shape)
         # one order of summation in every kernel
         assert bool((c == run_gpu(env, a, b, I.FP16, config=1)).all())
         idx = np.asarray(I.sample_entries(M, N, min(4096, M * N // 2), seed=K, always=[(0, 0), (M - 1, N - 1), (0, N - 1), (M - 1, 0)]))
