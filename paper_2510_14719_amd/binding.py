@@ -9,11 +9,11 @@ for the tensors, the calls raise.
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libattn_fwd.so")
-FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
 
 FP16 = 0
 BF16 = 1
@@ -111,15 +111,22 @@ def load_library() -> ctypes.CDLL:
     return _lib
 
 
+def torch_build() -> str:
+    """The torch of this process, as the extension names the one that it was compiled against."""
+    import torch
+    return "%s %s" % (torch.__version__, torch.version.git_version)
+
+
 def _load_fast():
     """The extension that makes the plain calls without the interpreter's share (csrc/fastcall.cpp); like the library it has
     to have been built.  Whatever it does not take (NotImplemented) goes through the general code below."""
     global _fast
     if _fast is None:
         lib = load_library()
-        if not os.path.exists(FASTCALL_PATH):
-            raise ImportError("%s is missing: build it with `python -m paper_2510_14719_amd.build`" % FASTCALL_PATH)
-        from . import _fastcall
+        _fastcall = importlib.import_module("._fastcall", __package__)
+        if _fastcall.built_for != torch_build():
+            raise ImportError("%s was built for torch %s, this is %s: build it again with `python -m paper_2510_14719_amd.build`"
+                              % (_fastcall.__file__, _fastcall.built_for, torch_build()))
         _fastcall.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.attn_fwd, lib.attn_fwd_fp8, lib.gemm_nt, lib.gemm_nt_fp8)))
         os.register_at_fork(after_in_child=_fastcall.disable)
         _fast = _fastcall

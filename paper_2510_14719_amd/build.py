@@ -15,6 +15,7 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 import threading
 from concurrent.futures import ThreadPoolExecutor
 
@@ -22,7 +23,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libattn_fwd.so")
-FASTCALL = os.path.join(HERE, "_fastcall.so")
+FASTCALL = os.path.join(HERE, "_fastcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 OBJ_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["attn_fwd_kernel.hip", "attn_fwd_pipe_kernel.hip", "attn_fwd_fp8_kernel.hip", "mfma_probe.hip", "attn_api.cpp",
@@ -62,21 +63,32 @@ def _text_with_includes(path: str, seen=None) -> str:
 
 
 def build_fastcall(verbose: bool = False, force: bool = False) -> str:
-    """The Python extension of csrc/fastcall.cpp (host code; it reads torch's tensors through torch's C++ headers)."""
-    src = os.path.join(CSRC, "fastcall.cpp")
-    if not force and os.path.exists(FASTCALL) and os.path.getmtime(FASTCALL) > os.path.getmtime(src):
-        return FASTCALL
-    import sysconfig
+    """The Python extension of csrc/fastcall.cpp (host code; it reads torch's tensors through torch's C++ headers).  It is reused
+    when it is newer than its sources and was made by the same compiler and flags for the same torch and Python."""
     import torch
+    from .binding import torch_build
+    src = os.path.join(CSRC, "fastcall.cpp")
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     base = os.path.dirname(torch.__file__)
-    tmp = FASTCALL + ".tmp.%d.%d" % (os.getpid(), threading.get_ident())
     # (the HIP runtime is the one torch has loaded, through libc10_hip)
-    _run([hipcc, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-no-hip-rt", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-x", "c++", src,
-          "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
-          "-isystem", os.path.join(os.path.dirname(os.path.dirname(hipcc)), "include"), "-isystem", sysconfig.get_paths()["include"],
-          "-L", os.path.join(base, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-o", tmp], verbose)
+    cmd = [hipcc, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-no-hip-rt", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           '-DFASTCALL_TORCH="%s"' % torch_build(), "-x", "c++", src, "-I", INCLUDE,
+           "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           "-isystem", os.path.join(os.path.dirname(os.path.dirname(hipcc)), "include"), "-isystem", sysconfig.get_paths()["include"],
+           "-L", os.path.join(base, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    key = hashlib.sha1(" ".join(cmd + [sys.version, FASTCALL]).encode()).hexdigest()
+    stamp = os.path.join(OBJ_DIR, "fastcall.key")
+    newest = max(os.path.getmtime(f) for f in [src] + [os.path.join(INCLUDE, h) for h in os.listdir(INCLUDE)])
+    if (not force and os.path.exists(FASTCALL) and os.path.getmtime(FASTCALL) > newest and
+            os.path.exists(stamp) and open(stamp).read() == key):
+        return FASTCALL
+    os.makedirs(OBJ_DIR, exist_ok=True)
+    tmp = FASTCALL + ".tmp.%d.%d" % (os.getpid(), threading.get_ident())
+    _run(cmd + ["-o", tmp], verbose)
     os.replace(tmp, FASTCALL)
+    with open(stamp + ".tmp", "w") as f:
+        f.write(key)
+    os.replace(stamp + ".tmp", stamp)
     return FASTCALL
 
 

@@ -16,11 +16,16 @@
 
 #include <climits>
 #include <cstdint>
+#include <type_traits>
+
+#include "attn_fwd.h"
+#include "gemm_nt.h"
 
 namespace {
 
-typedef int (*attn_fn)(const void*, const void*, const void*, void*, float*, int, int, int, int, float, int, void*, int);
-typedef int (*gemm_fn)(const void*, const void*, void*, int, int, int, void*, int);
+typedef decltype(&::attn_fwd) attn_fn;
+typedef decltype(&::gemm_nt) gemm_fn;
+static_assert(std::is_same<attn_fn, decltype(&::attn_fwd_fp8)>::value && std::is_same<gemm_fn, decltype(&::gemm_nt_fp8)>::value, "pairs of calls");
 
 attn_fn attn_calls[2];          // attn_fwd, attn_fwd_fp8
 gemm_fn gemm_calls[2];          // gemm_nt, gemm_nt_fp8
@@ -203,4 +208,13 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall(void) { return PyModule_Create(&module); }
+// built_for: the torch that the extension was compiled against, whose object layouts it knows (binding.py compares).
+PyMODINIT_FUNC PyInit__fastcall(void)
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", FASTCALL_TORCH) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

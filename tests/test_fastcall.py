@@ -1,6 +1,7 @@
 """The extension that makes the plain calls (csrc/fastcall.cpp): what it takes it hands to the C ABI unchanged, everything else it
 leaves, having done nothing, to the general code of binding.py."""
 import os
+import sysconfig
 
 import pytest
 import torch
@@ -34,6 +35,16 @@ def test_addresses_reach_the_c_abi_in_order(fast):
         assert f(Q, K, V, 0, *ok[4:]) == -2 and f(Q, K, V, 256, 0, *ok[5:]) == -2 and f(*ok[:5], 48, *ok[6:]) == -2 and f(*ok[:7], 2) == -2
         assert f(Q + 8, *ok[1:]) == -4 and f(Q, K, V + 1, *ok[3:]) == -4
         assert f(Q, K, Q, *ok[3:]) == -7
+
+
+def test_it_names_the_torch_it_was_built_for(fast, monkeypatch):
+    # it reads torch's objects by the layout of the headers it was compiled with: another torch is refused before anything is read
+    assert fast.built_for == binding.torch_build() and torch.__version__ in fast.built_for
+    assert fast.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    monkeypatch.setattr(binding, "_fast", None)
+    monkeypatch.setattr(torch.version, "git_version", "0" * 40)
+    with pytest.raises(ImportError, match="built for torch"):
+        binding._load_fast()
 
 
 class Sub(torch.Tensor):
