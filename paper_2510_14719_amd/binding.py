@@ -11,6 +11,7 @@ from __future__ import annotations
 import ctypes
 import importlib
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libattn_fwd.so")
@@ -117,19 +118,30 @@ def torch_build() -> str:
     return "%s %s" % (torch.__version__, torch.version.git_version)
 
 
+class _NoExtension:
+    """In the place of the extension where there is none: takes nothing."""
+    attn_fwd = attn_fwd_fp8 = gemm_nt = gemm_nt_fp8 = staticmethod(lambda *args: NotImplemented)
+
+
 def _load_fast():
-    """The extension that makes the plain calls without the interpreter's share (csrc/fastcall.cpp); like the library it has
-    to have been built.  Whatever it does not take (NotImplemented) goes through the general code below."""
+    """The extension that makes the plain calls without the interpreter's share (csrc/fastcall.cpp).  Whatever it does not take
+    (NotImplemented) goes through the general code below, and so does every call, with one warning, where it has not been built for this
+    torch and Python: the same kernels, 2 to 4 us more per call on the host."""
     global _fast
     if _fast is None:
         lib = load_library()
-        _fastcall = importlib.import_module("._fastcall", __package__)
-        if _fastcall.built_for != torch_build():
-            raise ImportError("%s was built for torch %s, this is %s: build it again with `python -m paper_2510_14719_amd.build`"
-                              % (_fastcall.__file__, _fastcall.built_for, torch_build()))
-        _fastcall.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.attn_fwd, lib.attn_fwd_fp8, lib.gemm_nt, lib.gemm_nt_fp8)))
-        os.register_at_fork(after_in_child=_fastcall.disable)
-        _fast = _fastcall
+        try:
+            ext = importlib.import_module("._fastcall", __package__)
+            if ext.built_for != torch_build():
+                raise ImportError("%s was built for torch %s, this is %s" % (ext.__file__, ext.built_for, torch_build()))
+        except ImportError as e:
+            warnings.warn("calls take the general code, which costs 2 to 4 us more each: %s (`python -m paper_2510_14719_amd.build` builds "
+                          "the extension)" % e, RuntimeWarning, stacklevel=3)
+            _fast = _NoExtension
+            return _fast
+        ext.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (lib.attn_fwd, lib.attn_fwd_fp8, lib.gemm_nt, lib.gemm_nt_fp8)))
+        os.register_at_fork(after_in_child=ext.disable)
+        _fast = ext
     return _fast
 
 

@@ -64,12 +64,21 @@ def _text_with_includes(path: str, seen=None) -> str:
 
 def build_fastcall(verbose: bool = False, force: bool = False) -> str:
     """The Python extension of csrc/fastcall.cpp (host code; it reads torch's tensors through torch's C++ headers).  It is reused
-    when it is newer than its sources and was made by the same compiler and flags for the same torch and Python."""
-    import torch
+    when it is newer than its sources and was made by the same compiler and flags for the same torch and Python.  Without torch, its C++ headers or
+    Python's there is none, and the binding does without."""
+    try:
+        import torch
+    except ImportError:
+        print("no torch: the extension is not built", flush=True)
+        return ""
     from .binding import torch_build
     src = os.path.join(CSRC, "fastcall.cpp")
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     base = os.path.dirname(torch.__file__)
+    for header in (os.path.join(base, "include", "torch", "csrc", "autograd", "python_variable.h"), os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        if not os.path.exists(header):
+            print("no %s: the extension is not built" % header, flush=True)
+            return ""
     # (the HIP runtime is the one torch has loaded, through libc10_hip)
     cmd = [hipcc, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-no-hip-rt", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            '-DFASTCALL_TORCH="%s"' % torch_build(), "-x", "c++", src, "-I", INCLUDE,
@@ -121,12 +130,13 @@ def build(extra_defines=(), out: str = LIB, verbose: bool = False, force: bool =
         _run([sys.executable, gen, inc], verbose)
 
     with ThreadPoolExecutor(max_workers=max(1, jobs) + 1) as pool:
-        fast = pool.submit(build_fastcall, verbose, force)
+        fast = pool.submit(build_fastcall, verbose, force) if out == LIB else None
         objs = list(pool.map(compile_one, SOURCES))
-        fast.result()
-    tmp = out + ".tmp.%d" % os.getpid()
-    _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp], verbose)
-    os.replace(tmp, out)
+        tmp = out + ".tmp.%d" % os.getpid()
+        _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", tmp], verbose)
+        os.replace(tmp, out)
+        if fast:
+            fast.result()                       # (the library is there by then, whatever becomes of the extension)
     return out
 
 

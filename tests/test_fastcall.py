@@ -1,12 +1,13 @@
 """The extension that makes the plain calls (csrc/fastcall.cpp): what it takes it hands to the C ABI unchanged, everything else it
 leaves, having done nothing, to the general code of binding.py."""
 import os
+import sys
 import sysconfig
 
 import pytest
 import torch
 
-from paper_2510_14719_amd import binding
+from paper_2510_14719_amd import binding, build
 
 Q, K, V, O, L = 0x10000000, 0x20000000, 0x30000000, 0x40000000, 0x50000000     # validation never dereferences them
 
@@ -43,8 +44,28 @@ def test_it_names_the_torch_it_was_built_for(fast, monkeypatch):
     assert fast.__file__.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
     monkeypatch.setattr(binding, "_fast", None)
     monkeypatch.setattr(torch.version, "git_version", "0" * 40)
-    with pytest.raises(ImportError, match="built for torch"):
-        binding._load_fast()
+    with pytest.warns(RuntimeWarning, match="built for torch"):
+        assert binding._load_fast() is binding._NoExtension
+
+
+def test_calls_do_without_the_extension(monkeypatch):
+    monkeypatch.setattr(binding, "_fast", None)
+    monkeypatch.setitem(sys.modules, "paper_2510_14719_amd._fastcall", None)     # (as where it has not been built)
+    with pytest.warns(RuntimeWarning, match="general code"), pytest.raises(binding.AttnFwdError) as e:
+        binding.attn_fwd(0, K, V, O, L, 1, 1, 64, 64, 0.125, False, stream=0, dtype=0)
+    assert e.value.code == -1
+    for f, args in ((binding.attn_fwd_fp8, (Q, K, V, O, L, 1, 1, 64, 96, 0.125, False, 0, 0)), (binding.gemm_nt, (Q, K, V, 64, 64, 48, 0, 0)),
+                    (binding.gemm_nt_fp8, (Q, K, V, 64, 64, 48, 0, 0))):
+        with pytest.raises(RuntimeError) as e:
+            f(*args)
+        assert e.value.code == -2
+
+
+def test_the_library_builds_without_the_headers_of_the_extension(monkeypatch, capsys, tmp_path):
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_fastcall() == "" and "not built" in capsys.readouterr().out
+    monkeypatch.setitem(sys.modules, "torch", None)
+    assert build.build_fastcall() == "" and "no torch" in capsys.readouterr().out
 
 
 class Sub(torch.Tensor):
