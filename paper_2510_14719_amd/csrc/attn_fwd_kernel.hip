@@ -148,6 +148,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     constexpr int KK = D / 32;                  // contraction steps of Q K^T
     constexpr int FB = D / 16;                  // 16-wide feature blocks of O
     constexpr bool AHEAD = KS == 2;             // see fetch_ahead
+    constexpr bool BLOCK_BY_BLOCK = KS == 2 && D == 128;                 // see softmax_tile
     constexpr int ROW_BYTES = D * 2;
     constexpr int TILE_BYTES = BN * ROW_BYTES;  // one K or one V tile
     constexpr int STAGE_BYTES = 2 * TILE_BYTES;
@@ -291,7 +292,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     u32x4 pw[KB / 2][QB];                       // P of the current tile as packed 16-bit pairs: the B operands of U
     // reference of a row and what it adds to every exponent (-reference * scale * log2 e); both the same in the four lanes of a query
     float m_run[QB], neg_mc[QB];
-    f32x4 L[QB];                                // row sums of P (all elements alike)
+    f32x4 L[QB];                                // row sums of P: the first element (the others miss the rescaling)
     s16x8 ones;
 #pragma unroll
     for (int e = 0; e < 8; ++e) ones[e] = E::ONE;
@@ -405,6 +406,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             // A lane looks at its own part of the keys only: some lane of a row exceeds the limit exactly when the row does.
             float mx[QB];
             bool over = false;
+            unsigned long long over_of[QB] = {}, any = 0;
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 mx[qb] = S[0][qb][0];
@@ -412,9 +414,37 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                 for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) mx[qb] = __builtin_fmaxf(mx[qb], S[kb][qb][i]);
-                if (!FIRST) over |= __builtin_fmaf(mx[qb], scale_log2e, neg_mc[qb]) > RESCALE_LOG2;
+                if (FIRST) continue;
+                const bool o = __builtin_fmaf(mx[qb], scale_log2e, neg_mc[qb]) > RESCALE_LOG2;
+                if (BLOCK_BY_BLOCK) over_of[qb] = __builtin_amdgcn_ballot_w64(o);
+                any |= over_of[qb];
+                over |= o;
             }
-            if (FIRST || __builtin_amdgcn_ballot_w64(over) != 0) {
+            // (of the row sums only the first element is read, so only that one is rescaled: 43.5 -> 43.1 us at 24 heads, N 1596, causal, where
+            // keys eight times as long as the others keep moving the reference)
+            if (BLOCK_BY_BLOCK) {
+                // Only the 16-query blocks in which a row exceeds the limit, each by itself; such a block takes the present maximum of all its rows,
+                // which it is rescaled for anyway.  A split tile is a chain of latencies, and this is the shorter one (such keys, us, with the
+                // form below / so: 7 heads, N 1851, causal 33.9 / 32.8, other keys 26.8 / 26.9; 8 heads, N 2309, causal 41.0 / 39.5, 32.0 / 32.1); whole
+                // tiles gain from it with such keys (24 heads, N 1596, causal 43.1 / 42.8) what they lose with others (35.8 / 36.1), and
+                // split ones at d = 64 lose (27 heads, N 700, causal 12.3 / 12.5, 10.9 / 11.1).
+                if (FIRST || any != 0) {
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) {
+                        if (!FIRST && over_of[qb] == 0) continue;
+                        const float m_old = m_run[qb];
+                        float a, b;
+                        both_halves(xor16_max(__builtin_fmaxf(mx[qb], m_old)), a, b);
+                        m_run[qb] = __builtin_fmaxf(a, b);
+                        neg_mc[qb] = -m_run[qb] * scale_log2e;
+                        if (FIRST) continue;
+                        const float alpha = __builtin_amdgcn_exp2f((m_old - m_run[qb]) * scale_log2e);
+                        L[qb][0] *= alpha;
+#pragma unroll
+                        for (int fb = 0; fb < FB; ++fb) O[fb][qb] = O[fb][qb] * alpha;
+                    }
+                }
+            } else if (FIRST || __builtin_amdgcn_ballot_w64(over) != 0) {
                 // Two 16-query blocks at a time: after the first exchange the lower half of the wave carries the first, the upper half the second.
                 // (Where keys eight times as long keep moving the reference, 2 x 32 heads, N 8192, causal: 982 us with each block by itself, 947 so.)
 #pragma unroll
@@ -436,7 +466,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         if ((unsigned)(moved >> (32 * h)) == 0) continue;
-                        L[2 * mb + h] = L[2 * mb + h] * alpha[h];
+                        L[2 * mb + h][0] *= alpha[h];
 #pragma unroll
                         for (int fb = 0; fb < FB; ++fb) O[fb][2 * mb + h] = O[fb][2 * mb + h] * alpha[h];
                     }
