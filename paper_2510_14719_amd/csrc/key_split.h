@@ -17,7 +17,8 @@
 //                E4M3    65 heads, N 239 9.1 / 8.5; 127 heads, N 148 7.8 / 8.5; causal: 100 heads, N 150 8.0 / 7.7; 101 heads, N 123 6.7 / 7.4;
 //                        d 64: 100 heads, N 200 7.1 / 6.1, N 100 4.9 / 5.1
 //   no mask      16-bit  70 heads, N 865 51 / 35; 109 heads, N 722 47 / 46; 77 heads, N 1944 159 / 166; 64 heads, N 1024 32 / 39;
-//                        N <= 128: 268 heads, N 71 15.3 / 14.1; 1168 heads, N 38 24.7 / 26.5
+//                        N <= 128: 268 heads, N 71 15.3 / 14.1; 900 heads, N 96 31.7 / 30.4; 1500 heads, N 128 58 / 61; 400 heads, N 64 11.7 / 12.3;
+//                        the same with the mask: 900 heads, N 66 29.5 / 27.9; 400 heads, N 64 12.2 / 12.6
 //                        d 64: 187 heads, N 596 35 / 29; 174 heads, N 775 44 / 43; 85 heads, N 1154 41 / 47; 340 heads, N 123 9.6 / 8.9
 //                E4M3    44 heads, N 1390 51 / 35; 67 heads, N 1140 43 / 44; 120 heads, N 583 29 / 33;
 //                        d 64: 73 heads, N 841 28 / 20; 106 heads, N 759 25 / 27
@@ -45,8 +46,11 @@ inline bool attn_splits_keys(int d, int N, long long heads, bool causal, bool fp
 
     if (split > MAX_SPLIT_TILES) return false;
     if (split <= CHIP_CUS) return !fp8 || N > (d == 64 || causal ? 128 : 192);
+    // One tile per head, half of it or more empty where it is a whole one: split tiles while the rounds are few, and while more than half
+    // of theirs is in use.
+    if (!fp8 && d == 128 && N <= 128) return N > 64 && whole <= 4 * CHIP_CUS;
     if (!causal) {
-        if (!fp8 && N <= 128) return d == 64 || whole <= 2 * CHIP_CUS;   // (half of a whole tile would be empty)
+        if (!fp8 && N <= 128) return true;
         const double cost = fp8 ? (d == 64 ? 0.51 : 0.525) + 230. / (N + 300) : d == 64 ? 0.56 + 10. / N : 0.60 + 45. / N;
         return cost * rounds(split) < 0.97 * rounds(whole);
     }
@@ -56,7 +60,7 @@ inline bool attn_splits_keys(int d, int N, long long heads, bool causal, bool fp
         // short tiles pair evenly are the exception.
         if (d == 64) return per_head < 2 || (per_head & (per_head - 1)) != 0 || (whole + 2 * CHIP_CUS - 1) / (2 * CHIP_CUS) * (2 * CHIP_CUS) - whole > 8;
         if (fp8) return N > 2048 && whole > CHIP_CUS * 3 / 2 && whole <= CHIP_CUS * 15 / 8;
-        return split <= 2 * CHIP_CUS || (N > 1536 && whole <= CHIP_CUS * 11 / 6);
+        return (N > 128 && split <= 2 * CHIP_CUS) || (N > 1536 && whole <= CHIP_CUS * 11 / 6);
     }
     if (d == 64) return N > 512;
     if (N <= 2048 || split > 2 * CHIP_CUS) return false;
