@@ -17,7 +17,7 @@
 //                E4M3    65 heads, N 239 9.1 / 8.5; 127 heads, N 148 7.8 / 8.5; causal: 100 heads, N 150 8.0 / 7.7; 101 heads, N 123 6.7 / 7.4;
 //                        d 64: 100 heads, N 200 7.1 / 6.1, N 100 4.9 / 5.1
 //   no mask      16-bit  70 heads, N 865 51 / 35; 109 heads, N 722 47 / 46; 77 heads, N 1944 159 / 166; 64 heads, N 1024 32 / 39;
-//                        N <= 128: 268 heads, N 71 15.3 / 14.1; 900 heads, N 96 31.7 / 30.4; 1500 heads, N 128 58 / 61; 400 heads, N 64 11.7 / 12.3;
+//                        N <= 128: 268 heads, N 71 15.3 / 14.1; 900 heads, N 96 31.7 / 30.4; 1500 heads, N 128 58 / 61; 400 heads, N 64 11.7 / 12.3; 700 heads, N 20 14.7 / 13.8;
 //                        the same with the mask: 900 heads, N 66 29.5 / 27.9; 400 heads, N 64 12.2 / 12.6
 //                        d 64: 187 heads, N 596 35 / 29; 174 heads, N 775 44 / 43; 85 heads, N 1154 41 / 47; 340 heads, N 123 9.6 / 8.9
 //                E4M3    44 heads, N 1390 51 / 35; 67 heads, N 1140 43 / 44; 120 heads, N 583 29 / 33;
@@ -46,9 +46,9 @@ inline bool attn_splits_keys(int d, int N, long long heads, bool causal, bool fp
 
     if (split > MAX_SPLIT_TILES) return false;
     if (split <= CHIP_CUS) return !fp8 || N > (d == 64 || causal ? 128 : 192);
-    // One tile per head, half of it or more empty where it is a whole one: split tiles while the rounds are few, and while more than half
-    // of theirs is in use.
-    if (!fp8 && d == 128 && N <= 128) return N > 64 && whole <= 4 * CHIP_CUS;
+    // One tile per head, half of it or more empty where it is a whole one: split tiles while the rounds are few.  (From 33 to 64 keys,
+    // one tile of keys, both halves of the workgroup do work for rows that a whole tile leaves to one of its waves.)
+    if (!fp8 && d == 128 && N <= 128) return (N <= 32 || N > 64) && whole <= 4 * CHIP_CUS;
     if (!causal) {
         if (!fp8 && N <= 128) return true;
         const double cost = fp8 ? (d == 64 ? 0.51 : 0.525) + 230. / (N + 300) : d == 64 ? 0.56 + 10. / N : 0.60 + 45. / N;
