@@ -425,7 +425,8 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             if (BLOCK_BY_BLOCK) {
                 // Only the 16-query blocks in which a row exceeds the limit, each by itself; such a block takes the present maximum of all its rows,
                 // which it is rescaled for anyway.  A split tile is a chain of latencies, and this is the shorter one (such keys, us, with the
-                // form below / so: 7 heads, N 1851, causal 33.9 / 32.8, other keys 26.8 / 26.9; 8 heads, N 2309, causal 41.0 / 39.5, 32.0 / 32.1); whole
+                // form below / so: 7 heads, N 1851, causal 33.9 / 32.8, 8 heads, N 2309, causal 41.0 / 39.5, 4 heads, N 5000 78.7 / 75.7; other keys 26.8 / 26.9,
+                // 32.0 / 32.1, 63.8 / 64.0, at the worst, 8 heads, N 900, 17.3 / 17.6); whole
                 // tiles gain from it with such keys (24 heads, N 1596, causal 43.1 / 42.8) what they lose with others (35.8 / 36.1), and
                 // split ones at d = 64 lose (27 heads, N 700, causal 12.3 / 12.5, 10.9 / 11.1).
                 if (FIRST || any != 0) {

@@ -46,8 +46,8 @@ inline bool attn_splits_keys(int d, int N, long long heads, bool causal, bool fp
 
     if (split > MAX_SPLIT_TILES) return false;
     if (split <= CHIP_CUS) return !fp8 || N > (d == 64 || causal ? 128 : 192);
-    // One tile per head, half of it or more empty where it is a whole one: split tiles while the rounds are few.  (From 33 to 64 keys,
-    // one tile of keys, both halves of the workgroup do work for rows that a whole tile leaves to one of its waves.)
+    // One tile per head, half of it or more empty where it is a whole one: split tiles while the rounds are few.  (From 33 to 64
+    // keys, a single tile of keys to share out, whole tiles are the faster ones.)
     if (!fp8 && d == 128 && N <= 128) return (N <= 32 || N > 64) && whole <= 4 * CHIP_CUS;
     if (!causal) {
         if (!fp8 && N <= 128) return true;
