@@ -32,6 +32,8 @@
  * validates its arguments on the host, enqueues one kernel on `stream` on the
  * current device and returns.  Calls are thread safe.
  *
+ * NaN: a NaN in a row of Q makes that row of O and LSE NaN, one in a row of K every row that sees that key; no other row changes.
+ *
  * Return value: ATTN_FWD_OK or a negative error code; attn_fwd_strerror gives
  * its text.  Argument validation happens before any HIP call, so the argument
  * errors can be provoked on a machine without a GPU.  Nothing is enqueued when
