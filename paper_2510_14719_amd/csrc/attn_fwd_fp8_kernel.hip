@@ -730,7 +730,6 @@ template <int OUT, int D>
 int launch_fp8_d(const AttnLaunchArgs& a)
 {
     constexpr int BN = D == 128 ? ATTN8_CFG_BN_D128 : ATTN8_CFG_BN_D64;
-    // (A step of split tiles takes 0.91 us for 128 keys, one of whole tiles 0.83 us for 64, at d = 128.)
     if constexpr (HAS_SPLIT<D>) {
         if (a.rows ? a.rows == 128 : attn_splits_keys(D, a.N, (long long)a.B * a.H, a.causal != 0, true))
             return a.causal ? launch_fp8<OUT, D, BN, true, false, 2>(a) : launch_fp8<OUT, D, BN, false, false, 2>(a);
